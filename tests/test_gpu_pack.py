@@ -1,0 +1,112 @@
+"""The packed grid byte for byte: occupancy words, rank maps, padded voxels
+and distance bytes, against NumPy (exact: every value is an integer or a
+copy)."""
+import numpy as np
+import pytest
+import torch
+from scipy import ndimage
+
+from paper_2103_14645_amd import snerg as S
+from tests import gpu_helpers as H
+
+pytestmark = pytest.mark.gpu
+
+
+def align256(x):
+    return (x + 255) & ~255
+
+
+def expected(N, B, ind, dens, rgb, feat):
+    """(bits, ranks) of the occupancy words, rank_lin, rank_id, distance bytes
+    [r, z, y, x] and padded voxels [r, z, y, x, 8]."""
+    G, n = N // B, len(dens)
+    lin = np.nonzero((ind >= 0) & (ind < n))[0]
+    occ = np.zeros(-(-G ** 3 // 32) * 32, np.uint8)
+    occ[lin] = 1
+    bits = np.packbits(occ.reshape(-1, 32), axis=1, bitorder="little").view(np.uint32).reshape(-1)
+    ranks = np.concatenate([[0], np.cumsum(occ.reshape(-1, 32).sum(1))[:-1]]).astype(np.int32)
+    rank_lin = np.full(n, -1, np.int32)
+    rank_id = np.full(n, -1, np.int32)
+    lin = lin[:n]
+    rank_lin[:len(lin)] = lin
+    rank_id[:len(lin)] = ind[lin]
+    full = np.zeros((N + 2,) * 3 + (8,), dens.dtype)
+    for b in np.nonzero((ind >= 0) & (ind < n))[0]:
+        z, y, x = (1 + B * int(c) for c in (b // (G * G), b // G % G, b % G))
+        full[z:z + B, y:y + B, x:x + B] = np.concatenate(
+            [dens[ind[b]][..., None], rgb[ind[b]], feat[ind[b]]], -1)
+    vox = np.zeros((n, B + 2, B + 2, B + 2, 8), dens.dtype)
+    dist = np.full((n, B + 1, B + 1, B + 1), 255, np.uint8)
+    for r, b in enumerate(lin):
+        z, y, x = (B * int(c) for c in (b // (G * G), b // G % G, b % G))
+        vox[r] = full[z:z + B + 2, y:y + B + 2, x:x + B + 2]
+        d = vox[r, ..., 0] != 0
+        act = np.zeros((B + 1,) * 3, bool)
+        for c in range(8):
+            act |= d[c >> 2:B + 1 + (c >> 2), (c >> 1) & 1:B + 1 + ((c >> 1) & 1), c & 1:B + 1 + (c & 1)]
+        if act.any():
+            dist[r] = ndimage.distance_transform_cdt(~act, metric="chessboard")
+    return bits, ranks, rank_lin, rank_id, dist, vox
+
+
+def check(N, B, ind, dens, rgb, feat):
+    dg = S.DeviceGrid(H.handle(), N, B, ind, dens, rgb, feat)
+    torch.cuda.synchronize()
+    raw = dg.packed.cpu().numpy()
+    n, G = len(dens), N // B
+    words = -(-G ** 3 // 32)
+    bits, ranks, rank_lin, rank_id, dist, vox = expected(N, B, ind, dens, rgb, feat)
+    occ = raw[:8 * words].view(np.uint32).reshape(-1, 2)
+    assert np.array_equal(occ[:, 0], bits)
+    assert np.array_equal(occ[:, 1].view(np.int32), ranks)
+    off = align256(8 * words)
+    assert np.array_equal(raw[off:off + 4 * n].view(np.int32), rank_lin)
+    off += align256(4 * n)
+    assert np.array_equal(raw[off:off + 4 * n].view(np.int32), rank_id)
+    off += align256(4 * n)
+    cells, item = (B + 1) ** 3, dens.dtype.itemsize
+    dist_bytes = (cells + 15) & ~15
+    size = (B + 2) ** 3 * 8 * item
+    stride = align256(dist_bytes + size)
+    for r in range(n):
+        rec = raw[off + r * stride:off + (r + 1) * stride]
+        assert np.array_equal(rec[:cells].reshape(dist[r].shape), dist[r]), (N, B, r)
+        got = rec[dist_bytes:dist_bytes + size].view(dens.dtype).reshape(vox[r].shape)
+        assert np.array_equal(got, vox[r]), (N, B, r)
+
+
+@pytest.mark.parametrize("f32", [False, True])
+@pytest.mark.parametrize("N,B", [(2, 2), (14, 2), (20, 4), (24, 8), (64, 8), (48, 16), (32, 32), (96, 32), (128, 64)])
+def test_packed_bytes(N, B, f32):
+    H.say(f"pack N={N} B={B} f32={f32}")
+    rng = np.random.default_rng(N * 100 + B)
+    G = N // B
+    n = max(1, min(G ** 3, 20))
+    ind = np.full(G ** 3, -1, np.int32)
+    ind[rng.choice(G ** 3, n, replace=False)] = rng.permutation(n)
+    dens = np.where(rng.random((n, B, B, B)) < 0.3, rng.integers(1, 256, (n, B, B, B)), 0)
+    # blocks that are empty, hold one voxel at a corner, or a lone plane: the longest distances
+    dens[0] = 0
+    if n > 2:
+        dens[1] = 0
+        dens[1, 0, 0, 0] = 7
+        dens[2] = 0
+        dens[2, B - 1] = 9
+    t = np.float32 if f32 else np.uint8
+    rgb, feat = rng.integers(0, 256, (n, B, B, B, 3)), rng.integers(0, 256, (n, B, B, B, 4))
+    check(N, B, ind, dens.astype(t), rgb.astype(t), feat.astype(t))
+
+
+@pytest.mark.parametrize("f32", [False, True])
+def test_packed_bytes_odd_indirection(f32):
+    """Atlas ids out of range, unused and repeated; more macroblocks than one pass of the table."""
+    B, G = 2, 40
+    N, n = B * G, 300
+    rng = np.random.default_rng(5)
+    ind = np.where(rng.random(G ** 3) < 0.004, rng.integers(0, n, G ** 3), -1).astype(np.int32)
+    ind[::997] = n + 3
+    t = np.float32 if f32 else np.uint8
+    dens, rgb, feat = (rng.integers(0, 3, (n, B, B, B) + c).astype(t) for c in ((), (3,), (4,)))
+    check(N, B, ind, dens, rgb, feat)
+    # every macroblock names one of few ids: ranks beyond n_blocks are dropped
+    check(N, B, (np.arange(G ** 3) % n).astype(np.int32), dens, rgb, feat)

@@ -845,19 +845,24 @@ int log2i(int v) {
 
 // Handle-owned baking scratch for G3 macroblocks (grown on demand): the
 // per-block largest density (float), visibility words (uint64), the
-// kept-block count and the atlas-id map (int32).
+// kept-block count and the atlas-id map (int32); for the culls also n_cells
+// entries of the cell table and the field's statistics.
 struct BakeScratch {
     float* bmax;
     uint64_t* depth_bits;
     int32_t* count;
     int32_t* lin_of;
+    uint2* cells;
+    uint32_t* stats;
 };
 
-int bake_scratch(snerg_handle* h, int64_t G3, BakeScratch* out) {
+int bake_scratch(snerg_handle* h, int64_t G3, int64_t n_cells, BakeScratch* out) {
     const size_t off_depth = (size_t(G3) + 1) & ~size_t(1);  // in 4-byte words, 8-byte aligned
     const size_t off_count = off_depth + 2 * size_t(G3);
     const size_t off_map = off_count + 2;
-    const size_t need = off_map + size_t(G3);
+    const size_t off_cells = (off_map + size_t(G3) + 1) & ~size_t(1);
+    const size_t off_stats = off_cells + 2 * size_t(n_cells);
+    const size_t need = off_stats + 2;
     if (need > h->bake_cap) {
         HIP_TRY(hipDeviceSynchronize());
         if (h->d_bake) HIP_TRY(hipFree(h->d_bake));
@@ -870,6 +875,8 @@ int bake_scratch(snerg_handle* h, int64_t G3, BakeScratch* out) {
     out->depth_bits = reinterpret_cast<uint64_t*>(h->d_bake + off_depth);
     out->count = reinterpret_cast<int32_t*>(h->d_bake + off_count);
     out->lin_of = reinterpret_cast<int32_t*>(h->d_bake + off_map);
+    out->cells = n_cells > 0 ? reinterpret_cast<uint2*>(h->d_bake + off_cells) : nullptr;
+    out->stats = reinterpret_cast<uint32_t*>(h->d_bake + off_stats);
     return SNERG_OK;
 }
 
@@ -887,7 +894,8 @@ int snerg_bake_cull(snerg_handle* h, int32_t N, int32_t B, const float* sigma, c
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int64_t G = N / B, G3 = G * G * G;
     BakeScratch sc;
-    if ((rc = bake_scratch(h, G3, &sc))) return rc;
+    const int64_t M = N / 8;
+    if ((rc = bake_scratch(h, G3, B >= 8 && N <= 2048 ? M * M * M : 0, &sc))) return rc;
     if (!h->h_bake_count) HIP_TRY(hipHostMalloc(&h->h_bake_count, 256, hipHostMallocDefault));
     int64_t total_tiles = 0;
     rc = upload_cams(h, cams, n_cams, h->tuning.tile_w, h->tuning.tile_h, s, &total_tiles);
@@ -909,6 +917,8 @@ int snerg_bake_cull(snerg_handle* h, int32_t N, int32_t B, const float* sigma, c
     p.sum_thr = -double(N) * std::log(double(opts->tau_vis));
     p.bmax = sc.bmax;
     p.depth_bits = sc.depth_bits;
+    p.cells = sc.cells;
+    p.stats = sc.stats;
     p.block_alpha = block_alpha;
     p.block_vis = block_vis;
     p.indirection = indirection;
@@ -933,7 +943,7 @@ int snerg_bake_quantize(snerg_handle* h, int32_t N, int32_t B, const float* sigm
     if (n_blocks == 0) return SNERG_OK;
     hipStream_t s = static_cast<hipStream_t>(stream);
     BakeScratch sc;
-    if ((rc = bake_scratch(h, G3, &sc))) return rc;
+    if ((rc = bake_scratch(h, G3, 0, &sc))) return rc;
     BakeQuantPlan p;
     p.sigma = sigma;
     p.rgb = rgb;

@@ -13,6 +13,10 @@
 //                     double, which orders like the value).  The ray stops
 //                     once the prefix sum passes the visibility threshold:
 //                     later samples cannot make a block visible.
+//  k_bake_cells,      the same two for macroblocks of 8^3 and more: the first
+//  k_bake_visibility_cells
+//                     pass also notes which 8^3 cells and whole macroblocks
+//                     hold one value, and the march takes those in one step.
 //  k_bake_compact     the two culls and the atlas numbering in scan order
 //                     (one workgroup: a ballot prefix per wavefront, then
 //                     across wavefronts).
@@ -88,7 +92,65 @@ struct BakeVisArgs {
     int32_t tile_w, tile_h;
     double sum_thr;  // stop once the density prefix sum exceeds this
     uint64_t* depth_bits;
+    const uint2* cells;     // k_bake_visibility_cells: the cell table and the field's statistics
+    const uint32_t* stats;
 };
+
+// Per-workgroup cache of bounds on the blocks' minima: 256 slots indexed by
+// the low 8 bits of the block index, each one 32-bit word (read and written
+// whole, so no reader sees half an update): the block index's high 10 bits,
+// then a 22-bit code whose value is an upper bound of a prefix sum already
+// folded into that block's minimum (the sum rounded up to float, then its
+// bits rounded up to a multiple of 2^10).  A block entry whose prefix sum is
+// at least that bound needs no global access: the block's minimum is already
+// no larger.  A racing overwrite only costs a later global check.
+constexpr int kVisSlots = 256;
+
+__device__ __forceinline__ void vis_cache_clear(uint32_t* vcache) {
+    for (int i = threadIdx.x; i < kVisSlots; i += blockDim.x)
+        vcache[i] = (0x3ffu << 22) | (0x7f800000u >> 10);  // bound +inf: never skips
+}
+
+// Folds a prefix sum into the minimum of the macroblock a ray enters with it.
+__device__ __forceinline__ void vis_enter(uint32_t* vcache, uint64_t* depth_bits, uint32_t lin, double sum) {
+    const uint32_t key = vcache[lin & 255];
+    if ((key >> 22) != (lin >> 8) || double(__uint_as_float((key & 0x3fffffu) << 10)) > sum) {
+        const uint64_t bits = uint64_t(__double_as_longlong(sum));
+        uint64_t* w = depth_bits + lin;
+        uint64_t g = __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (bits < g) {
+            atomicMin(reinterpret_cast<unsigned long long*>(w), (unsigned long long)bits);
+            g = bits;
+        }
+        const double gv = __longlong_as_double((long long)g);
+        float gf = float(gv);
+        if (double(gf) < gv) gf = __uint_as_float(__float_as_uint(gf) + 1u);
+        const uint32_t code = (__float_as_uint(gf) + 0x3ffu) >> 10;
+        vcache[lin & 255] = ((lin >> 8) << 22) | code;
+    }
+}
+
+// The ray of lane `lane` in tile t and its samples inside the grid: position
+// of the first (Q16), step, count.  False: the pixel overhangs the image or
+// the ray misses the grid.
+__device__ __forceinline__ bool vis_ray(const BakeVisArgs& a, int64_t t, int lane, int32_t P[3], int32_t s[3],
+                                        int32_t& n) {
+    const int ci = find_camera_by_tile(a.cams, a.n_cams, t);
+    const DevCamera& c = a.cams[ci];
+    const int64_t tl = t - c.tile_offset;
+    const int px = int(tl % c.tiles_x) * a.tile_w + lane % a.tile_w;
+    const int py = int(tl / c.tiles_x) * a.tile_h + lane / a.tile_w;
+    if (px >= c.W || py >= c.H) return false;
+    int64_t o[3];
+    float d[3];
+    ray_setup(c, a.N, px, py, o, s, d);
+    int64_t klo, khi;
+    if (!entry_range(o, s, int64_t(a.N) << 16, klo, khi)) return false;
+#pragma unroll
+    for (int q = 0; q < 3; ++q) P[q] = int32_t(o[q] + klo * int64_t(s[q]));  // inside [0, N 2^16)
+    n = int32_t(khi - klo + 1);
+    return true;
+}
 
 // Samples loaded ahead of the sequential prefix sum.
 constexpr int kVisAhead = 4;
@@ -102,38 +164,14 @@ enum { kIdx64 = 0, kIdx32 = 1, kIdxPow2 = 2 };
 
 template <int IDX>
 __global__ __launch_bounds__(256) void k_bake_visibility(BakeVisArgs a) {
-    // Per-workgroup cache of bounds on the blocks' minima: 256 slots indexed
-    // by the low 8 bits of the block index, each one 32-bit word (read and
-    // written whole, so no reader sees half an update): the block index's
-    // high 10 bits, then a 22-bit code whose value is an upper bound of a
-    // prefix sum already folded into that block's minimum (the sum rounded
-    // up to float, then its bits rounded up to a multiple of 2^10).  A block
-    // entry whose prefix sum is at least that bound needs no global access:
-    // the block's minimum is already no larger.  A racing overwrite only
-    // costs a later global check.
-    __shared__ uint32_t vcache[256];
-    vcache[threadIdx.x & 255] = (0x3ffu << 22) | (0x7f800000u >> 10);  // bound +inf: never skips
+    __shared__ uint32_t vcache[kVisSlots];
+    vis_cache_clear(vcache);
     __syncthreads();
     const int lane = threadIdx.x & 63;
     const int64_t t = int64_t(blockIdx.x) * (blockDim.x >> 6) + (threadIdx.x >> 6);
     if (t >= a.total_tiles) return;  // wave-uniform
-    const int ci = find_camera_by_tile(a.cams, a.n_cams, t);
-    const DevCamera& c = a.cams[ci];
-    const int64_t tl = t - c.tile_offset;
-    const int px = int(tl % c.tiles_x) * a.tile_w + lane % a.tile_w;
-    const int py = int(tl / c.tiles_x) * a.tile_h + lane / a.tile_w;
-    if (px >= c.W || py >= c.H) return;
-    int64_t o[3];
-    int32_t s[3];
-    float d[3];
-    ray_setup(c, a.N, px, py, o, s, d);
-    const int64_t L = int64_t(a.N) << 16;
-    int64_t klo, khi;
-    if (!entry_range(o, s, L, klo, khi)) return;
-    int32_t P[3];
-#pragma unroll
-    for (int q = 0; q < 3; ++q) P[q] = int32_t(o[q] + klo * int64_t(s[q]));  // inside [0, N 2^16)
-    const int32_t n = int32_t(khi - klo + 1);
+    int32_t P[3], s[3], n;
+    if (!vis_ray(a, t, lane, P, s, n)) return;
     const uint32_t N = uint32_t(a.N), G = uint32_t(a.G);
     const int bs = 16 + a.logB;
     int lg = 0;
@@ -183,7 +221,6 @@ __global__ __launch_bounds__(256) void k_bake_visibility(BakeVisArgs a) {
                 if (bk[u] != prev) {
                     prev = bk[u];
                     if (sum <= thr) {
-                        const uint64_t bits = uint64_t(__double_as_longlong(sum));
                         uint32_t bx, by, bz;
                         if (IDX == kIdxPow2) {
                             bx = (bk[u] >> a.logB) & (G - 1);
@@ -195,20 +232,7 @@ __global__ __launch_bounds__(256) void k_bake_visibility(BakeVisArgs a) {
                             bz = bk[u] >> 16;
                         }
                         const uint32_t lin = __umul24(__umul24(bz, G) + by, G) + bx;
-                        const uint32_t key = vcache[lin & 255];
-                        if ((key >> 22) != (lin >> 8) || double(__uint_as_float((key & 0x3fffffu) << 10)) > sum) {
-                            uint64_t* w = a.depth_bits + lin;
-                            uint64_t g = __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                            if (bits < g) {
-                                atomicMin(reinterpret_cast<unsigned long long*>(w), (unsigned long long)bits);
-                                g = bits;
-                            }
-                            const double gv = __longlong_as_double((long long)g);
-                            float gf = float(gv);
-                            if (double(gf) < gv) gf = __uint_as_float(__float_as_uint(gf) + 1u);
-                            const uint32_t code = (__float_as_uint(gf) + 0x3ffu) >> 10;
-                            vcache[lin & 255] = ((lin >> 8) << 22) | code;
-                        }
+                        vis_enter(vcache, a.depth_bits, lin, sum);
                     }
                 }
                 sum += double(sv[u]);
@@ -224,6 +248,206 @@ __global__ __launch_bounds__(256) void k_bake_visibility(BakeVisArgs a) {
         if (sum > thr || last < kVisAhead) break;
 #pragma unroll
         for (int q = 0; q < 3; ++q) P[q] += kVisAhead * s[q];
+    }
+}
+
+// Cells of one value.  Most of a baked field is empty or constant, yet the
+// march above pays 21 instructions and a dependent add for each of its
+// samples.  k_bake_cells reads the field once, as k_bake_block_max does, and
+// notes for every 8^3 cell whether all its voxels hold the same bits: the
+// entry is {value, edge shift}, the shift that of the whole macroblock where
+// that holds one value, {kMixed, cell shift} where the cell does not.  It
+// also collects the field's largest bits and smallest non-zero ones (stats,
+// zero on entry: largest bits; complement of the smallest).
+constexpr uint32_t kMixed = 0x7fc00000u;  // a NaN: no field value (one that is NaN reads as mixed)
+constexpr int kCellLog = 3;
+constexpr int kCell = 1 << kCellLog;
+
+// One workgroup per macroblock, B >= 8.  A wavefront takes a slab of cells at
+// a time, all cells along x of one (y, z): every step its lanes read whole
+// rows of the block, 16 bytes each, `rows` of the slab's 64 rows at once.
+__global__ __launch_bounds__(256) void k_bake_cells(const float* __restrict__ sigma, int32_t N, int32_t logB, int32_t G,
+                                                    float* __restrict__ bmax, uint64_t* __restrict__ depth_bits,
+                                                    uint2* __restrict__ cells, uint32_t* __restrict__ stats) {
+    __shared__ uint32_t lo[512], hi[512];  // per cell: smallest and largest bits (B = 64: 8^3 cells)
+    __shared__ float part[4];
+    __shared__ uint32_t part_lo[4], part_hi[4], part_nz[4];
+    const int64_t lin = blockIdx.x;
+    const int32_t bx = int32_t(lin % G), by = int32_t((lin / G) % G), bz = int32_t(lin / (int64_t(G) * G));
+    const int32_t B = 1 << logB, cb = B >> kCellLog, lrow = logB - 2, rowq = 1 << lrow;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n_waves = blockDim.x >> 6;
+    const int q = lane & (rowq - 1);
+    float m = -INFINITY;
+    uint32_t all_lo = 0xffffffffu, all_hi = 0, nz = 0xffffffffu;
+    for (int slab = wave; slab < cb * cb; slab += n_waves) {
+        const int cy = slab % cb, cz = slab / cb;
+        uint32_t l = 0xffffffffu, h = 0;
+#pragma unroll 8
+        for (int st = 0; st < rowq; ++st) {
+            const int row = (st << (6 - lrow)) + (lane >> lrow);
+            const int ly = cy * kCell + (row & 7), lz = cz * kCell + (row >> 3);
+            const int64_t at = (int64_t(bz * B + lz) * N + (by * B + ly)) * N + bx * B + 4 * q;
+            float v[4];
+            __builtin_memcpy(v, sigma + at, 16);  // one 16-byte load at any float alignment
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                m = fmaxf(m, v[i]);
+                const uint32_t bits = v[i] == 0.0f ? 0u : __float_as_uint(v[i]);
+                l = min(l, bits);
+                h = max(h, bits);
+                nz = min(nz, bits != 0 ? bits : 0xffffffffu);
+            }
+        }
+        // lanes of one cell: all rows, and the two loads of a row that lie in it
+        for (int x = 1; x < 64; x = x == 1 ? (rowq > 2 ? rowq : 2) : 2 * x) {
+            l = min(l, uint32_t(__shfl_xor(int(l), x)));
+            h = max(h, uint32_t(__shfl_xor(int(h), x)));
+        }
+        if (lane < rowq && (lane & 1) == 0) {
+            lo[slab * cb + (q >> 1)] = l;
+            hi[slab * cb + (q >> 1)] = h;
+        }
+        all_lo = min(all_lo, l);
+        all_hi = max(all_hi, h);
+    }
+    m = wave_max(m);
+#pragma unroll
+    for (int x = 32; x >= 1; x >>= 1) {
+        all_lo = min(all_lo, uint32_t(__shfl_xor(int(all_lo), x)));
+        all_hi = max(all_hi, uint32_t(__shfl_xor(int(all_hi), x)));
+        nz = min(nz, uint32_t(__shfl_xor(int(nz), x)));
+    }
+    if (lane == 0) {
+        part[wave] = m;
+        part_lo[wave] = all_lo;
+        part_hi[wave] = all_hi;
+        part_nz[wave] = nz;
+    }
+    __syncthreads();
+    for (int w = 0; w < n_waves; ++w) {
+        m = fmaxf(m, part[w]);
+        all_lo = min(all_lo, part_lo[w]);
+        all_hi = max(all_hi, part_hi[w]);
+        nz = min(nz, part_nz[w]);
+    }
+    if (threadIdx.x == 0) {
+        bmax[lin] = m;
+        depth_bits[lin] = kInfBits;
+        // reads first: after the first blocks hardly any still has to write
+        if (__hip_atomic_load(stats, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < all_hi) atomicMax(stats, all_hi);
+        if (__hip_atomic_load(stats + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < ~nz) atomicMax(stats + 1, ~nz);
+    }
+    const bool whole = all_lo == all_hi;
+    const int32_t M = N >> kCellLog;
+    for (int c = threadIdx.x; c < cb * cb * cb; c += blockDim.x) {
+        const int cx = c % cb, cy = c / cb % cb, cz = c / (cb * cb);
+        uint2 e = make_uint2(kMixed, uint32_t(16 + kCellLog));
+        if (lo[c] == hi[c]) e = make_uint2(lo[c], uint32_t(16 + (whole ? logB : kCellLog)));
+        cells[(int64_t(bz * cb + cz) * M + (by * cb + cy)) * M + bx * cb + cx] = e;
+    }
+}
+
+// Steps of a ray at Q16 position P until it leaves the aligned cube of edge
+// 2^sh on some axis (at least 1); mag = |s|, inv = 1 / |s|.
+__device__ __forceinline__ int32_t steps_in_cube(const int32_t P[3], const int32_t s[3], const int32_t mag[3],
+                                                 const float inv[3], uint32_t sh) {
+    const int32_t W = int32_t(1u << sh), low = W - 1;
+    int32_t n = 0x7fffffff;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        const int32_t f = P[a] & low;
+        const int32_t D = s[a] > 0 ? W - f : f + 1;  // in [1, W], W <= 2^22
+        // smallest k with k mag >= D: the estimate is off by at most one
+        int32_t k = int32_t(__builtin_ceilf(float(D) * inv[a])) & 0xffffff;
+        k += (__mul24(k, mag[a]) < D) ? 1 : 0;
+        k -= (__mul24(k - 1, mag[a]) >= D) ? 1 : 0;
+        n = min(n, mag[a] != 0 ? k : 0x7fffffff);
+    }
+    return n;
+}
+
+// The march of k_bake_visibility over the cell table: a step of a ray is a
+// whole cell (or macroblock) of one value, whose samples add n times that
+// value to the prefix sum, or the samples of a mixed cell, read four at a
+// time.  The sums keep every bit of the sample-by-sample ones: a run of
+// zeros changes nothing, and n c may stand for n additions of c where no
+// addition rounds.  That holds for all of the field when, with 2^e the last
+// place of its smallest non-zero value (all values are multiples of it), no
+// sum of interest reaches 2^(53+e); sums stop mattering past the threshold,
+// so four times that plus twice the largest value bounds them.  Where the
+// field does not satisfy this, only cells of zeros are skipped.
+// Bound by instruction issue (about 65 per step and 12 per mixed sample).
+template <int IDX>
+__global__ __launch_bounds__(256) void k_bake_visibility_cells(BakeVisArgs a) {
+    __shared__ uint32_t vcache[kVisSlots];
+    vis_cache_clear(vcache);
+    __syncthreads();
+    const int lane = threadIdx.x & 63;
+    const int64_t t = int64_t(blockIdx.x) * (blockDim.x >> 6) + (threadIdx.x >> 6);
+    if (t >= a.total_tiles) return;  // wave-uniform
+    const double thr = a.sum_thr;
+    const uint32_t top = a.stats[0], least = ~a.stats[1];
+    bool exact = top < 0x7f800000u;  // finite and none negative
+    if (exact && top != 0) {
+        const int e = int(max(least >> 23, 1u)) - 127 - 23;
+        exact = 4.0 * thr + 2.0 * double(__uint_as_float(top)) < __builtin_ldexp(1.0, 53 + e);
+    }
+    int32_t P[3], s[3], left;
+    if (!vis_ray(a, t, lane, P, s, left)) return;
+    int32_t mag[3];
+    float inv[3];
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+        mag[q] = s[q] < 0 ? -s[q] : s[q];
+        inv[q] = mag[q] != 0 ? 1.0f / float(mag[q]) : 0.0f;
+    }
+    const uint32_t N = uint32_t(a.N), G = uint32_t(a.G), M = N >> kCellLog;
+    const int bs = 16 + a.logB;
+    int lg = 0;
+    while ((1 << lg) < a.N) ++lg;
+    double sum = 0.0;
+    uint32_t prev = 0xffffffffu;
+    while (left > 0 && sum <= thr) {
+        const uint32_t cell = ((uint32_t(P[2]) >> (16 + kCellLog)) * M + (uint32_t(P[1]) >> (16 + kCellLog))) * M +
+                              (uint32_t(P[0]) >> (16 + kCellLog));
+        const uint2 e = a.cells[cell];
+        const uint32_t lin = __umul24(__umul24(uint32_t(P[2]) >> bs, G) + (uint32_t(P[1]) >> bs), G) +
+                             (uint32_t(P[0]) >> bs);
+        if (lin != prev) {  // the ray's smallest prefix sum in this macroblock
+            prev = lin;
+            vis_enter(vcache, a.depth_bits, lin, sum);
+        }
+        const int32_t n = min(steps_in_cube(P, s, mag, inv, e.y), left);
+        const float c = __uint_as_float(e.x);
+        if (c == 0.0f || (exact && e.x != kMixed)) {
+            sum = fma(double(n), double(c), sum);
+        } else {
+            uint32_t Q[3] = {uint32_t(P[0]), uint32_t(P[1]), uint32_t(P[2])};
+            for (int32_t j = 0; j < n; j += kVisAhead) {
+                // samples past the last are clamped onto it, so every load is in bounds
+                const int32_t last = n - 1 - j;
+                float sv[kVisAhead];
+#pragma unroll
+                for (int u = 0; u < kVisAhead; ++u) {
+                    if (u > 0 || j > 0) {
+                        const uint32_t m = u <= last ? 0xffffffffu : 0u;
+#pragma unroll
+                        for (int q = 0; q < 3; ++q) Q[q] += uint32_t(s[q]) & m;
+                    }
+                    if (IDX == kIdxPow2)
+                        sv[u] = a.sigma[(Q[0] >> 16) | ((Q[1] >> 16) << lg) | ((Q[2] >> 16) << (2 * lg))];
+                    else if (IDX == kIdx32)
+                        sv[u] = a.sigma[__umul24(__umul24(Q[2] >> 16, N) + (Q[1] >> 16), N) + (Q[0] >> 16)];
+                    else
+                        sv[u] = a.sigma[(uint64_t(Q[2] >> 16) * N + (Q[1] >> 16)) * N + (Q[0] >> 16)];
+                }
+#pragma unroll
+                for (int u = 0; u < kVisAhead; ++u) sum += u <= last ? double(sv[u]) : 0.0;
+            }
+        }
+        left -= n;
+#pragma unroll
+        for (int q = 0; q < 3; ++q) P[q] += __mul24(n, s[q]);  // |n s| <= B 2^16 + 2^15
     }
 }
 
@@ -376,14 +600,22 @@ __global__ __launch_bounds__(256) void k_bake_quantize(BakeQuantArgs a) {
 
 hipError_t launch_bake_cull(const BakeCullPlan& p, hipStream_t s) {
     const int64_t G3 = int64_t(p.G) * p.G * p.G;
-    if (p.vec4)
+    hipError_t e;
+    // Macroblocks of 8^3 and more on grids of up to 2048^3 (128 MB of cells)
+    // go through the cell table; smaller ones would pay a step for every few
+    // voxels, and past that the table would crowd a field of 275 GB.
+    if (p.cells) {
+        if ((e = launch_fill_i32(reinterpret_cast<int32_t*>(p.stats), 2, 0, s)) != hipSuccess) return e;
+        hipLaunchKernelGGL(k_bake_cells, dim3(unsigned(G3)), dim3(p.logB == 3 ? 64 : 256), 0, s, p.sigma, p.N, p.logB,
+                           p.G, p.bmax, p.depth_bits, p.cells, p.stats);
+    } else if (p.vec4) {
         hipLaunchKernelGGL(k_bake_block_max<4>, dim3(unsigned(G3)), dim3(256), 0, s, p.sigma, p.N, p.logB, p.G,
                            p.bmax, p.depth_bits);
-    else
+    } else {
         hipLaunchKernelGGL(k_bake_block_max<1>, dim3(unsigned(G3)), dim3(256), 0, s, p.sigma, p.N, p.logB, p.G,
                            p.bmax, p.depth_bits);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
+    }
+    if ((e = hipGetLastError()) != hipSuccess) return e;
     if (p.total_tiles > 0) {
         BakeVisArgs v;
         v.sigma = p.sigma;
@@ -397,13 +629,21 @@ hipError_t launch_bake_cull(const BakeCullPlan& p, hipStream_t s) {
         v.tile_h = p.tile_h;
         v.sum_thr = p.sum_thr;
         v.depth_bits = p.depth_bits;
-        const unsigned blocks = unsigned((p.total_tiles + 3) / 4);
-        if ((p.N & (p.N - 1)) == 0 && p.N <= 1024)
-            hipLaunchKernelGGL(k_bake_visibility<kIdxPow2>, dim3(blocks), dim3(256), 0, s, v);
-        else if (int64_t(p.N) * p.N * p.N <= int64_t(0xffffffffu))
-            hipLaunchKernelGGL(k_bake_visibility<kIdx32>, dim3(blocks), dim3(256), 0, s, v);
-        else
-            hipLaunchKernelGGL(k_bake_visibility<kIdx64>, dim3(blocks), dim3(256), 0, s, v);
+        v.cells = p.cells;
+        v.stats = p.stats;
+        const dim3 blocks(unsigned((p.total_tiles + 3) / 4));
+        const int idx = (p.N & (p.N - 1)) == 0 && p.N <= 1024
+                            ? kIdxPow2
+                            : (int64_t(p.N) * p.N * p.N <= int64_t(0xffffffffu) ? kIdx32 : kIdx64);
+        if (p.cells) {
+            if (idx == kIdxPow2) hipLaunchKernelGGL(k_bake_visibility_cells<kIdxPow2>, blocks, dim3(256), 0, s, v);
+            else if (idx == kIdx32) hipLaunchKernelGGL(k_bake_visibility_cells<kIdx32>, blocks, dim3(256), 0, s, v);
+            else hipLaunchKernelGGL(k_bake_visibility_cells<kIdx64>, blocks, dim3(256), 0, s, v);
+        } else {
+            if (idx == kIdxPow2) hipLaunchKernelGGL(k_bake_visibility<kIdxPow2>, blocks, dim3(256), 0, s, v);
+            else if (idx == kIdx32) hipLaunchKernelGGL(k_bake_visibility<kIdx32>, blocks, dim3(256), 0, s, v);
+            else hipLaunchKernelGGL(k_bake_visibility<kIdx64>, blocks, dim3(256), 0, s, v);
+        }
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     BakeCompactArgs c;

@@ -163,3 +163,47 @@ def test_bake_full_size_sampled():
         np.testing.assert_array_equal(res.rgb[bid].cpu().numpy(), K.quantize(f.rgb[sl]))
         np.testing.assert_array_equal(res.feat[bid].cpu().numpy(), K.quantize(f.feat[sl]))
     say(f"  20 views of 800x800: kept {res.n_blocks}/{ind.size}")
+
+
+@pytest.mark.parametrize("N,B,kind", [(64, 8, "zeros"), (64, 16, "haze"), (96, 32, "steps"), (128, 64, "zeros"),
+                                      (40, 8, "tiny"), (72, 8, "whole"), (56, 8, "huge")])
+def test_bake_cells_of_one_value(N, B, kind):
+    """Fields with constant cells and macroblocks, which the visibility march
+    takes in one step: zeros, a constant haze, a different constant per
+    macroblock, values too small or too large beside the others for sums that
+    never round (then only zeros are skipped), a constant field; with a base
+    address that is no multiple of 16 bytes."""
+    say(f"bake cells N={N} B={B} {kind}")
+    rng = np.random.default_rng(N + B)
+    c = (np.arange(N) + 0.5) * 2 / N - 1
+    r = np.sqrt(c[:, None, None] ** 2 + c[None, :, None] ** 2 + c[None, None, :] ** 2)
+    shell = np.abs(r - 0.6) < 3.0 / N
+    sigma = np.zeros((N, N, N), np.float32)
+    if kind == "haze":
+        sigma[:] = 0.3
+    elif kind == "steps":
+        G = N // B
+        sigma[:] = np.kron(rng.uniform(0, 20, (G, G, G)), np.ones((B, B, B)))
+    elif kind == "tiny":
+        sigma[:] = 1e-30
+        sigma[:8, :8, :8] = -0.0
+    elif kind == "whole":
+        sigma[:] = 7.7
+    elif kind == "huge":
+        sigma[:] = 0.1
+        sigma[N // 2] = 3e38
+    if kind != "whole":
+        sigma[shell] = rng.uniform(0, 400, shell.sum())
+    cams = W.sphere_cameras([(30, 26, 50.0)] * 3, seed=N) + [W.look_at((0.1, 0.05, -0.2), 20, 20, 70.0)]
+    buf = torch.empty(N ** 3 + 1, dtype=torch.float32, device="cuda")
+    buf[1:] = _dev(sigma.reshape(-1))
+    G3 = (N // B) ** 3
+    ind = torch.empty(G3, dtype=torch.int32, device="cuda")
+    alpha, vis = torch.empty(G3, device="cuda"), torch.empty(G3, device="cuda")
+    for tau_vis in (0.01, 0.9):
+        ref = K.cull(sigma, B, cams, tau_vis=tau_vis)
+        n = S.snerg_bake_cull(handle(), N, B, buf[1:], S.make_cameras(cams), S.make_bake_opts(tau_vis=tau_vis), ind,
+                              alpha, vis)
+        res = BK.BakeResult(n, ind, alpha, vis, None, None, None)
+        near = _check_cull(res, ref, N, tau_vis=tau_vis)
+        say(f"  tau_vis={tau_vis}: kept {n}/{G3}, near-threshold {near}")

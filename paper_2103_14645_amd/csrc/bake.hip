@@ -96,38 +96,49 @@ struct BakeVisArgs {
     const uint32_t* stats;
 };
 
-// Per-workgroup cache of bounds on the blocks' minima: 256 slots indexed by
-// the low 8 bits of the block index, each one 32-bit word (read and written
-// whole, so no reader sees half an update): the block index's high 10 bits,
-// then a 22-bit code whose value is an upper bound of a prefix sum already
-// folded into that block's minimum (the sum rounded up to float, then its
-// bits rounded up to a multiple of 2^10).  A block entry whose prefix sum is
-// at least that bound needs no global access: the block's minimum is already
-// no larger.  A racing overwrite only costs a later global check.
-constexpr int kVisSlots = 256;
+// Per-workgroup cache of bounds on the blocks' minima: 2^LOG slots indexed by
+// the low bits of the block index, each one 32-bit word (read and written
+// whole, so no reader sees half an update): the block index's bits from 8 on,
+// 10 of them, then a 22-bit code whose value is an upper bound of a prefix
+// sum that some lane of the workgroup has folded, or is about to fold, into
+// that block's minimum (the sum rounded up to float, then its bits rounded up
+// to a multiple of 2^10).  A block entry whose prefix sum is at least that
+// bound needs no global access.  A racing overwrite only costs a later global
+// check.
+template <int LOG>
+__device__ __forceinline__ void vis_cache_clear(volatile uint32_t* vcache) {
+    for (int i = threadIdx.x; i < (1 << LOG); i += blockDim.x)
+        vcache[i] = (uint32_t(i >> 8) << 22) | (0x7f800000u >> 10);  // bound +inf: never skips
+}
 
-__device__ __forceinline__ void vis_cache_clear(uint32_t* vcache) {
-    for (int i = threadIdx.x; i < kVisSlots; i += blockDim.x)
-        vcache[i] = (0x3ffu << 22) | (0x7f800000u >> 10);  // bound +inf: never skips
+__device__ __forceinline__ uint32_t vis_code(double sum) {
+    float f = float(sum);
+    if (double(f) < sum) f = __uint_as_float(__float_as_uint(f) + 1u);
+    return (__float_as_uint(f) + 0x3ffu) >> 10;
 }
 
 // Folds a prefix sum into the minimum of the macroblock a ray enters with it.
-__device__ __forceinline__ void vis_enter(uint32_t* vcache, uint64_t* depth_bits, uint32_t lin, double sum) {
-    const uint32_t key = vcache[lin & 255];
-    if ((key >> 22) != (lin >> 8) || double(__uint_as_float((key & 0x3fffffu) << 10)) > sum) {
-        const uint64_t bits = uint64_t(__double_as_longlong(sum));
-        uint64_t* w = depth_bits + lin;
-        uint64_t g = __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (bits < g) {
-            atomicMin(reinterpret_cast<unsigned long long*>(w), (unsigned long long)bits);
-            g = bits;
-        }
-        const double gv = __longlong_as_double((long long)g);
-        float gf = float(gv);
-        if (double(gf) < gv) gf = __uint_as_float(__float_as_uint(gf) + 1u);
-        const uint32_t code = (__float_as_uint(gf) + 0x3ffu) >> 10;
-        vcache[lin & 255] = ((lin >> 8) << 22) | code;
-    }
+// The lanes that enter a block together first agree in the cache on the
+// smallest code; a lane with a larger one leaves the fold to that lane (its
+// own sum is larger, and so is the bound it would have written).  The global
+// minimum is then read through the caches: it only ever falls, so an old
+// value is a bound as good as any, and a read that waits for the other XCDs
+// costs the ray several times a cached one.
+template <int LOG>
+__device__ __forceinline__ void vis_enter(volatile uint32_t* vcache, uint64_t* depth_bits, uint32_t lin, double sum) {
+    const uint32_t slot = lin & ((1u << LOG) - 1u), tag = lin >> 8;
+    const uint32_t key = vcache[slot];
+    if ((key >> 22) == tag && double(__uint_as_float((key & 0x3fffffu) << 10)) <= sum) return;
+    const uint32_t mine = (tag << 22) | vis_code(sum);
+    if ((key >> 22) == tag) atomicMin(const_cast<uint32_t*>(vcache) + slot, mine);
+    else vcache[slot] = mine;
+    const uint32_t now = vcache[slot];
+    if ((now >> 22) == tag && now < mine) return;
+    const uint64_t bits = uint64_t(__double_as_longlong(sum));
+    uint64_t* w = depth_bits + lin;
+    const uint64_t g = __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+    if (bits < g) atomicMin(reinterpret_cast<unsigned long long*>(w), (unsigned long long)bits);
+    else vcache[slot] = (tag << 22) | vis_code(__longlong_as_double((long long)g));
 }
 
 // The ray of lane `lane` in tile t and its samples inside the grid: position
@@ -164,8 +175,8 @@ enum { kIdx64 = 0, kIdx32 = 1, kIdxPow2 = 2 };
 
 template <int IDX>
 __global__ __launch_bounds__(256) void k_bake_visibility(BakeVisArgs a) {
-    __shared__ uint32_t vcache[kVisSlots];
-    vis_cache_clear(vcache);
+    __shared__ uint32_t vcache[256];
+    vis_cache_clear<8>(vcache);
     __syncthreads();
     const int lane = threadIdx.x & 63;
     const int64_t t = int64_t(blockIdx.x) * (blockDim.x >> 6) + (threadIdx.x >> 6);
@@ -232,7 +243,7 @@ __global__ __launch_bounds__(256) void k_bake_visibility(BakeVisArgs a) {
                             bz = bk[u] >> 16;
                         }
                         const uint32_t lin = __umul24(__umul24(bz, G) + by, G) + bx;
-                        vis_enter(vcache, a.depth_bits, lin, sum);
+                        vis_enter<8>(vcache, a.depth_bits, lin, sum);
                     }
                 }
                 sum += double(sv[u]);
@@ -347,23 +358,20 @@ __global__ __launch_bounds__(256) void k_bake_cells(const float* __restrict__ si
     }
 }
 
-// Steps of a ray at Q16 position P until it leaves the aligned cube of edge
-// 2^sh on some axis (at least 1); mag = |s|, inv = 1 / |s|.
-__device__ __forceinline__ int32_t steps_in_cube(const int32_t P[3], const int32_t s[3], const int32_t mag[3],
-                                                 const float inv[3], uint32_t sh) {
-    const int32_t W = int32_t(1u << sh), low = W - 1;
-    int32_t n = 0x7fffffff;
+// Steps a ray at Q16 position P may take inside the aligned cube of edge
+// 2^sh, at least 1.  up: all ones where s > 0, else 0; inv: just under 1/|s|
+// (1e9 for s = 0).  The distance to the face in units of 2^-16, D =
+// ((P ^ up) mod 2^sh) + 1, is left behind after ceil(D / |s|) steps; with inv
+// low by 2^-22, more than the two roundings can add, the estimate is never
+// above that.  Now and then it is one below, and the ray takes another step
+// in the same cube.
+__device__ __forceinline__ int32_t steps_in_cube(const int32_t P[3], const int32_t up[3], const float inv[3],
+                                                 uint32_t sh) {
+    const int32_t low = int32_t((1u << sh) - 1u);
+    float f[3];
 #pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        const int32_t f = P[a] & low;
-        const int32_t D = s[a] > 0 ? W - f : f + 1;  // in [1, W], W <= 2^22
-        // smallest k with k mag >= D: the estimate is off by at most one
-        int32_t k = int32_t(__builtin_ceilf(float(D) * inv[a])) & 0xffffff;
-        k += (__mul24(k, mag[a]) < D) ? 1 : 0;
-        k -= (__mul24(k - 1, mag[a]) >= D) ? 1 : 0;
-        n = min(n, mag[a] != 0 ? k : 0x7fffffff);
-    }
-    return n;
+    for (int a = 0; a < 3; ++a) f[a] = fmaf(float((P[a] ^ up[a]) & low), inv[a], inv[a]);
+    return int32_t(__builtin_ceilf(fminf(fminf(f[0], f[1]), f[2])));
 }
 
 // The march of k_bake_visibility over the cell table: a step of a ray is a
@@ -376,15 +384,24 @@ __device__ __forceinline__ int32_t steps_in_cube(const int32_t P[3], const int32
 // sum of interest reaches 2^(53+e); sums stop mattering past the threshold,
 // so four times that plus twice the largest value bounds them.  Where the
 // field does not satisfy this, only cells of zeros are skipped.
-// Bound by instruction issue (about 65 per step and 12 per mixed sample).
+// Bound by instruction issue for many rays (3,070 VALU instructions per
+// wavefront of 64 rays, VALUs about 70% busy): 100 views of 800x800 into a
+// 512^3 field take 6.9 ms, 30.1 sample by sample.  24 views of 200x150 into
+// 160^3 (204 us, 345 before) are bound by the chain of dependent loads, so
+// the next cell's entry is read before the current cell's samples and those
+// eight at a time.  Every first look at a macroblock by a workgroup costs a
+// global access (they took 40% of the time with 256 slots and one tile per
+// wavefront): the cache has a slot for every macroblock up to 16^3, and large
+// launches run resident workgroups over many tiles.
+constexpr int kCellsCacheLog = 12;
+constexpr int kCellAhead = 8;  // a ray crosses an 8^3 cell in up to 28 samples, 14 on average
+
 template <int IDX>
 __global__ __launch_bounds__(256) void k_bake_visibility_cells(BakeVisArgs a) {
-    __shared__ uint32_t vcache[kVisSlots];
-    vis_cache_clear(vcache);
+    __shared__ uint32_t vcache[1 << kCellsCacheLog];
+    vis_cache_clear<kCellsCacheLog>(vcache);
     __syncthreads();
     const int lane = threadIdx.x & 63;
-    const int64_t t = int64_t(blockIdx.x) * (blockDim.x >> 6) + (threadIdx.x >> 6);
-    if (t >= a.total_tiles) return;  // wave-uniform
     const double thr = a.sum_thr;
     const uint32_t top = a.stats[0], least = ~a.stats[1];
     bool exact = top < 0x7f800000u;  // finite and none negative
@@ -392,62 +409,69 @@ __global__ __launch_bounds__(256) void k_bake_visibility_cells(BakeVisArgs a) {
         const int e = int(max(least >> 23, 1u)) - 127 - 23;
         exact = 4.0 * thr + 2.0 * double(__uint_as_float(top)) < __builtin_ldexp(1.0, 53 + e);
     }
-    int32_t P[3], s[3], left;
-    if (!vis_ray(a, t, lane, P, s, left)) return;
-    int32_t mag[3];
-    float inv[3];
-#pragma unroll
-    for (int q = 0; q < 3; ++q) {
-        mag[q] = s[q] < 0 ? -s[q] : s[q];
-        inv[q] = mag[q] != 0 ? 1.0f / float(mag[q]) : 0.0f;
-    }
     const uint32_t N = uint32_t(a.N), G = uint32_t(a.G), M = N >> kCellLog;
     const int bs = 16 + a.logB;
     int lg = 0;
     while ((1 << lg) < a.N) ++lg;
-    double sum = 0.0;
-    uint32_t prev = 0xffffffffu;
-    while (left > 0 && sum <= thr) {
-        const uint32_t cell = ((uint32_t(P[2]) >> (16 + kCellLog)) * M + (uint32_t(P[1]) >> (16 + kCellLog))) * M +
-                              (uint32_t(P[0]) >> (16 + kCellLog));
-        const uint2 e = a.cells[cell];
-        const uint32_t lin = __umul24(__umul24(uint32_t(P[2]) >> bs, G) + (uint32_t(P[1]) >> bs), G) +
-                             (uint32_t(P[0]) >> bs);
-        if (lin != prev) {  // the ray's smallest prefix sum in this macroblock
-            prev = lin;
-            vis_enter(vcache, a.depth_bits, lin, sum);
+    const int64_t stride = int64_t(gridDim.x) * (blockDim.x >> 6);
+    for (int64_t t = int64_t(blockIdx.x) * (blockDim.x >> 6) + (threadIdx.x >> 6); t < a.total_tiles; t += stride) {
+        int32_t P[3], s[3], left;
+        if (!vis_ray(a, t, lane, P, s, left)) continue;
+        int32_t up[3];
+        float inv[3];
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+            up[q] = s[q] > 0 ? -1 : 0;
+            inv[q] = s[q] != 0 ? (1.0f / fabsf(float(s[q]))) * (1.0f - 0x1p-22f) : 1e9f;
         }
-        const int32_t n = min(steps_in_cube(P, s, mag, inv, e.y), left);
-        const float c = __uint_as_float(e.x);
-        if (c == 0.0f || (exact && e.x != kMixed)) {
-            sum = fma(double(n), double(c), sum);
-        } else {
+        auto entry = [&]() {
+            return a.cells[((uint32_t(P[2]) >> (16 + kCellLog)) * M + (uint32_t(P[1]) >> (16 + kCellLog))) * M +
+                           (uint32_t(P[0]) >> (16 + kCellLog))];
+        };
+        double sum = 0.0;
+        uint32_t prev = 0xffffffffu;
+        uint2 next = entry();
+        while (left > 0 && sum <= thr) {
+            const uint2 e = next;
+            const uint32_t lin = __umul24(__umul24(uint32_t(P[2]) >> bs, G) + (uint32_t(P[1]) >> bs), G) +
+                                 (uint32_t(P[0]) >> bs);
+            if (lin != prev) {  // the ray's smallest prefix sum in this macroblock
+                prev = lin;
+                vis_enter<kCellsCacheLog>(vcache, a.depth_bits, lin, sum);
+            }
+            const int32_t n = min(steps_in_cube(P, up, inv, e.y), left);
             uint32_t Q[3] = {uint32_t(P[0]), uint32_t(P[1]), uint32_t(P[2])};
-            for (int32_t j = 0; j < n; j += kVisAhead) {
-                // samples past the last are clamped onto it, so every load is in bounds
-                const int32_t last = n - 1 - j;
-                float sv[kVisAhead];
+            left -= n;
 #pragma unroll
-                for (int u = 0; u < kVisAhead; ++u) {
-                    if (u > 0 || j > 0) {
-                        const uint32_t m = u <= last ? 0xffffffffu : 0u;
+            for (int q = 0; q < 3; ++q) P[q] += __mul24(n, s[q]);  // |n s| <= B 2^16 + 2^15
+            if (left > 0) next = entry();  // in flight during the cell's own samples
+            const float c = __uint_as_float(e.x);
+            if (c == 0.0f || (exact && e.x != kMixed)) {
+                sum = fma(double(n), double(c), sum);
+            } else {
+                for (int32_t j = 0; j < n; j += kCellAhead) {
+                    // samples past the last are clamped onto it, so every load is in bounds
+                    const int32_t last = n - 1 - j;
+                    float sv[kCellAhead];
 #pragma unroll
-                        for (int q = 0; q < 3; ++q) Q[q] += uint32_t(s[q]) & m;
+                    for (int u = 0; u < kCellAhead; ++u) {
+                        if (u > 0 || j > 0) {
+                            const uint32_t m = u <= last ? 0xffffffffu : 0u;
+#pragma unroll
+                            for (int q = 0; q < 3; ++q) Q[q] += uint32_t(s[q]) & m;
+                        }
+                        if (IDX == kIdxPow2)
+                            sv[u] = a.sigma[(Q[0] >> 16) | ((Q[1] >> 16) << lg) | ((Q[2] >> 16) << (2 * lg))];
+                        else if (IDX == kIdx32)
+                            sv[u] = a.sigma[__umul24(__umul24(Q[2] >> 16, N) + (Q[1] >> 16), N) + (Q[0] >> 16)];
+                        else
+                            sv[u] = a.sigma[(uint64_t(Q[2] >> 16) * N + (Q[1] >> 16)) * N + (Q[0] >> 16)];
                     }
-                    if (IDX == kIdxPow2)
-                        sv[u] = a.sigma[(Q[0] >> 16) | ((Q[1] >> 16) << lg) | ((Q[2] >> 16) << (2 * lg))];
-                    else if (IDX == kIdx32)
-                        sv[u] = a.sigma[__umul24(__umul24(Q[2] >> 16, N) + (Q[1] >> 16), N) + (Q[0] >> 16)];
-                    else
-                        sv[u] = a.sigma[(uint64_t(Q[2] >> 16) * N + (Q[1] >> 16)) * N + (Q[0] >> 16)];
-                }
 #pragma unroll
-                for (int u = 0; u < kVisAhead; ++u) sum += u <= last ? double(sv[u]) : 0.0;
+                    for (int u = 0; u < kCellAhead; ++u) sum += u <= last ? double(sv[u]) : 0.0;
+                }
             }
         }
-        left -= n;
-#pragma unroll
-        for (int q = 0; q < 3; ++q) P[q] += __mul24(n, s[q]);  // |n s| <= B 2^16 + 2^15
     }
 }
 
@@ -636,9 +660,11 @@ hipError_t launch_bake_cull(const BakeCullPlan& p, hipStream_t s) {
                             ? kIdxPow2
                             : (int64_t(p.N) * p.N * p.N <= int64_t(0xffffffffu) ? kIdx32 : kIdx64);
         if (p.cells) {
-            if (idx == kIdxPow2) hipLaunchKernelGGL(k_bake_visibility_cells<kIdxPow2>, blocks, dim3(256), 0, s, v);
-            else if (idx == kIdx32) hipLaunchKernelGGL(k_bake_visibility_cells<kIdx32>, blocks, dim3(256), 0, s, v);
-            else hipLaunchKernelGGL(k_bake_visibility_cells<kIdx64>, blocks, dim3(256), 0, s, v);
+            // resident workgroups only, so that their caches of bounds serve many tiles
+            const dim3 wgs(blocks.x > 4u * 2048u ? 2048u : blocks.x);
+            if (idx == kIdxPow2) hipLaunchKernelGGL(k_bake_visibility_cells<kIdxPow2>, wgs, dim3(256), 0, s, v);
+            else if (idx == kIdx32) hipLaunchKernelGGL(k_bake_visibility_cells<kIdx32>, wgs, dim3(256), 0, s, v);
+            else hipLaunchKernelGGL(k_bake_visibility_cells<kIdx64>, wgs, dim3(256), 0, s, v);
         } else {
             if (idx == kIdxPow2) hipLaunchKernelGGL(k_bake_visibility<kIdxPow2>, blocks, dim3(256), 0, s, v);
             else if (idx == kIdx32) hipLaunchKernelGGL(k_bake_visibility<kIdx32>, blocks, dim3(256), 0, s, v);

@@ -91,7 +91,7 @@ extern "C" {
 
 /* ------------------------------------------------------------- option flags */
 #define SNERG_FLAG_MLP_FP16 (1u << 0)   /* deferred MLP on FP16 MFMA tiles, FP32 accumulation */
-#define SNERG_FLAG_PERSISTENT (1u << 1) /* one persistent launch over a global tile queue */
+#define SNERG_FLAG_PERSISTENT (1u << 1) /* one persistent launch over a global tile queue (renders small enough for several lanes to a ray, see snerg_tuning, have no queue) */
 #define SNERG_FLAG_GRAPH (1u << 2)      /* replay the launch from a captured HIP graph */
 #define SNERG_FLAG_MLP_GRAD_ONLY (1u << 3) /* backward: MLP gradient only (any grid dtype) */
 /* Render variants of the paper's own viewer (they change the image):
@@ -164,7 +164,10 @@ typedef struct {
     int32_t reserved;
 } snerg_opts;
 
-/* Launch shape used by the forward kernels (chosen by snerg_autotune). */
+/* Launch shape used by the forward kernels (chosen by snerg_autotune).  It
+ * sets how pixels are dealt to wavefronts, never a result.  Renders of up to
+ * 3 * 2^17 rays, and most of a SNERG_F32 grid, give each ray several lanes of a
+ * wavefront; of the shape they use only the tile. */
 typedef struct {
     int32_t tile_w, tile_h;   /* pixels per wavefront tile, tile_w * tile_h == 64 */
     int32_t waves_per_group;  /* wavefronts per workgroup: 1, 2 or 4 */

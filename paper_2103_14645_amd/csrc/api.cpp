@@ -310,6 +310,12 @@ snerg_tuning tuning_for(const snerg_handle* h, const snerg_grid* g, const snerg_
     return h->tuning;
 }
 
+// The counting and per-sample kernels have one lane to a ray.
+RenderSplit split_for(const RenderArgs& a, int vt, int mlp_mode) {
+    if (a.counters || a.opts.per_sample_mlp) return {1, 1};
+    return render_split(a, vt == 1, mlp_mode == kMlpF16);
+}
+
 int render_impl(snerg_handle* h, const snerg_grid* grid, const float* mlp, const snerg_camera* cams,
                 int32_t n_cams, const int64_t* ray_ids, int64_t n_rays, const snerg_opts* opts,
                 float* out_rgba, float* aux, hipStream_t s, const snerg_tuning& tu,
@@ -336,6 +342,7 @@ int render_impl(snerg_handle* h, const snerg_grid* grid, const float* mlp, const
     const int vt = grid->dtype == SNERG_F32 ? 1 : 0;
     const int mlp_mode = !opts->mlp_on ? kMlpOff : ((opts->flags & SNERG_FLAG_MLP_FP16) ? kMlpF16 : kMlpF32);
     const int wpg = tu.waves_per_group;
+    a.split = split_for(a, vt, mlp_mode);
     if (ray_ids) {
         a.mode = kModeList;
         HIP_TRY(timing_begin(h, s));
@@ -344,12 +351,13 @@ int render_impl(snerg_handle* h, const snerg_grid* grid, const float* mlp, const
         return SNERG_OK;
     }
     // heavy-first tile order (scheduling only: every tile's result is unchanged;
-    // int32 entries, so frames of more than 2^31 - 1 tiles keep image order)
+    // int32 entries, so frames of more than 2^31 - 1 tiles keep image order;
+    // small frames are resident at once and need none)
     // layout: counters [64] (fixed place), order [tiles], classes [tiles] bytes
     int32_t* counts = nullptr;
     int32_t* order = nullptr;
     uint8_t* cls = nullptr;
-    if (total_tiles <= int64_t(INT32_MAX)) {
+    if (a.split.ordered && total_tiles <= int64_t(INT32_MAX)) {
         const size_t order_words = 64 + size_t(total_tiles);
         float* const before = h->d_tiles;
         if ((rc = ensure_buffer(&h->d_tiles, &h->tiles_cap, order_words + (size_t(total_tiles) + 3) / 4, s))) return rc;
@@ -362,7 +370,7 @@ int render_impl(snerg_handle* h, const snerg_grid* grid, const float* mlp, const
         }
     }
     a.tile_order = order;
-    const bool persistent = (opts->flags & SNERG_FLAG_PERSISTENT) != 0;
+    const bool persistent = (opts->flags & SNERG_FLAG_PERSISTENT) != 0 && a.split.lanes == 1;
     a.mode = persistent ? kModePersistent : kModeTiles;
     const int n_groups = persistent ? h->n_cu * tu.groups_per_cu : 0;
     if (!(opts->flags & SNERG_FLAG_GRAPH)) {
@@ -640,18 +648,21 @@ int snerg_render_noalloc(snerg_handle* h, const snerg_grid* grid, const float* m
     a.aux = aux;
     const int vt = grid->dtype == SNERG_F32 ? 1 : 0;
     const int mlp_mode = !opts->mlp_on ? kMlpOff : ((opts->flags & SNERG_FLAG_MLP_FP16) ? kMlpF16 : kMlpF32);
+    a.split = split_for(a, vt, mlp_mode);
     if (ray_ids) {
         a.mode = kModeList;
         HIP_TRY(launch_render(a, vt, mlp_mode, tu.waves_per_group, 0, s));
         return SNERG_OK;
     }
-    const bool persistent = (opts->flags & SNERG_FLAG_PERSISTENT) != 0;
+    const bool persistent = (opts->flags & SNERG_FLAG_PERSISTENT) != 0 && a.split.lanes == 1;
     a.mode = persistent ? kModePersistent : kModeTiles;
-    a.tile_order = order;
-    // the order kernels expect zero counters; the array keeps whatever the
-    // last call left, so clear them (a fill kernel, no memset node)
-    HIP_TRY(launch_fill_i32(counts, 64, 0, s));
-    HIP_TRY(launch_tile_order(a, cls, counts, order, s));
+    if (a.split.ordered) {
+        a.tile_order = order;
+        // the order kernels expect zero counters; the array keeps whatever the
+        // last call left, so clear them (a fill kernel, no memset node)
+        HIP_TRY(launch_fill_i32(counts, 64, 0, s));
+        HIP_TRY(launch_tile_order(a, cls, counts, order, s));
+    }
     if (persistent) HIP_TRY(launch_fill_i32(counter, 1, 0, s));
     HIP_TRY(launch_render(a, vt, mlp_mode, tu.waves_per_group, persistent ? h->n_cu * tu.groups_per_cu : 0, s));
     return SNERG_OK;

@@ -392,6 +392,49 @@ struct FlatWalk {
         return true;
     }
 
+    // Enters the next macroblock: sets left, kk and q when it is occupied (left
+    // stays 0 otherwise).  Returns false at the end of the ray; the index
+    // guard keeps the table reads in bounds should the exact walk ever leave
+    // the grid.
+    template <typename Count>
+    __host__ __device__ __forceinline__ bool enter(const GridArgs& g, const uint2* occ, const int32_t s[3], Count& cnt) {
+        const int bs = 16 + g.logB;
+        const int32_t W = int32_t(1) << bs;
+        const uint32_t G3 = uint32_t(g.G) * uint32_t(g.G) * uint32_t(g.G);
+        const int32_t gstride[3] = {1, g.G, g.G * g.G};
+        if (k > kend || uint32_t(lin) >= G3) return false;
+        int32_t kn = kc[0] < kc[1] ? kc[0] : kc[1];
+        kn = kn < kc[2] ? kn : kc[2];
+        kn = kn < kend + 1 ? kn : kend + 1;
+        r = block_rank(occ, lin, g.n_blocks);
+        cnt.block(r >= 0);
+        if (r >= 0) {
+            dist = g.rec + int64_t(r) * g.rec_stride;
+            // Q16 position of sample k inside the macroblock, + 2^15 for the padding
+#pragma unroll
+            for (int a = 0; a < 3; ++a) q[a] = (s[a] > 0 ? W - F[a] : F[a] - 1) + mul_s24(k, s[a]) + 32768;
+            left = kn - k;
+            kk = k;
+        }
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            if (kc[a] == kn) {
+                lin += s[a] > 0 ? gstride[a] : -gstride[a];
+                F[a] += W;
+                const int32_t c = kc[a] + Q[a];
+                const int32_t cs = mul_s24(c, s[a]);  // c |s| = sign(s) c s
+                kc[a] = (s[a] > 0 ? cs : -cs) >= F[a] ? c : c + 1;
+            }
+        }
+        k = kn;
+        return true;
+    }
+
+    __host__ __device__ __forceinline__ bool enter(const GridArgs& g, const uint2* occ, const int32_t s[3]) {
+        NoCount nc;
+        return enter(g, occ, s, nc);
+    }
+
     // One trip: enter the next macroblock (going on to its first cell when
     // it is occupied) or step to the next cell; on an active cell hand the
     // sample to on_sample.  One if-region per kind of work and no early
@@ -407,46 +450,12 @@ struct FlatWalk {
     template <typename OnSample, typename Count>
     __host__ __device__ __forceinline__ bool trip(const GridArgs& g, const uint2* occ, const int32_t s[3],
                                                   OnSample&& on_sample, Count& cnt) {
-        const int bs = 16 + g.logB;
-        const int32_t W = int32_t(1) << bs;
         const uint32_t nc = uint32_t(g.Bc), ncc = nc * nc;
-        const uint32_t G3 = uint32_t(g.G) * uint32_t(g.G) * uint32_t(g.G);
-        const int32_t gstride[3] = {1, g.G, g.G * g.G};
         bool live = true;
         bool inside = left > 0;
         if (!inside) {
-            // the end of the ray; the index guard keeps the table reads in
-            // bounds should the exact walk ever leave the grid
-            if (k > kend || uint32_t(lin) >= G3) {
-                live = false;
-            } else {
-                int32_t kn = kc[0] < kc[1] ? kc[0] : kc[1];
-                kn = kn < kc[2] ? kn : kc[2];
-                kn = kn < kend + 1 ? kn : kend + 1;
-                r = block_rank(occ, lin, g.n_blocks);
-                cnt.block(r >= 0);
-                if (r >= 0) {
-                    dist = g.rec + int64_t(r) * g.rec_stride;
-                    // Q16 position of sample k inside the macroblock, + 2^15 for the padding
-#pragma unroll
-                    for (int a = 0; a < 3; ++a)
-                        q[a] = (s[a] > 0 ? W - F[a] : F[a] - 1) + mul_s24(k, s[a]) + 32768;
-                    left = kn - k;
-                    kk = k;
-                    inside = true;
-                }
-#pragma unroll
-                for (int a = 0; a < 3; ++a) {
-                    if (kc[a] == kn) {
-                        lin += s[a] > 0 ? gstride[a] : -gstride[a];
-                        F[a] += W;
-                        const int32_t c = kc[a] + Q[a];
-                        const int32_t cs = mul_s24(c, s[a]);  // c |s| = sign(s) c s
-                        kc[a] = (s[a] > 0 ? cs : -cs) >= F[a] ? c : c + 1;
-                    }
-                }
-                k = kn;
-            }
+            live = enter(g, occ, s, cnt);
+            inside = left > 0;
         }
         if (inside) {
             const int32_t p[3] = {q[0] >> 16, q[1] >> 16, q[2] >> 16};

@@ -1,5 +1,7 @@
 // Forward kernels: march + composite + deferred MLP (Section 5.2, Eq. 5-7),
 // and the visit-trace kernel.
+#include <type_traits>
+
 #include "march.h"
 #include "mlp.h"
 #include "snerg_launch.h"
@@ -118,31 +120,21 @@ __device__ __forceinline__ bool tile_pixel(const RenderArgs& a, int64_t t, int l
     return px < c.W && py < c.H;
 }
 
-template <int VT, int MLP, bool COUNT>
-__device__ __forceinline__ void render_ray(const RenderArgs& a, const uint2* occ, bool valid, int ci, int px,
-                                           int py, int64_t out_idx) {
-    RayAccum st = {{0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}, 1.0f, false};
-    RayCount rc = {0, 0, 0, 0, -1, 0u, 0u};
-    float d[3] = {0.f, 0.f, 1.f};
-    if (valid) {
-        int64_t o[3];
-        int32_t s[3];
-        ray_setup(a.cams[ci], a.grid.N, px, py, o, s, d);
-        // keep the direction as three floats from here on (left alone, the
-        // compiler carries its FP64 form through the march)
-        asm volatile("" : "+v"(d[0]), "+v"(d[1]), "+v"(d[2]));
-        march_composite<VT, COUNT>(a, occ, o, s, st, rc);
-        if (a.opts.unpremultiply) {
-            // Eq. 9: saturate alpha above 2/3, keep soft edges below
-            const float al = 1.0f - st.T;
-            if (al > 0.0f) {
-                const float sc = fminf(1.0f, 1.5f * al) / al;
+// What follows the march: Eq. 9 if asked for, the deferred network, the
+// outputs.  All 64 lanes call it; `valid` lanes hold a ray.
+template <int MLP>
+__device__ __forceinline__ void finish_ray(const RenderArgs& a, bool valid, RayAccum& st, const float d[3],
+                                           int64_t out_idx) {
+    if (valid && a.opts.unpremultiply) {
+        // Eq. 9: saturate alpha above 2/3, keep soft edges below
+        const float al = 1.0f - st.T;
+        if (al > 0.0f) {
+            const float sc = fminf(1.0f, 1.5f * al) / al;
 #pragma unroll
-                for (int ch = 0; ch < 3; ++ch) st.C[ch] *= sc;
+            for (int ch = 0; ch < 3; ++ch) st.C[ch] *= sc;
 #pragma unroll
-                for (int ch = 0; ch < 4; ++ch) st.V[ch] *= sc;
-                st.T = 1.0f - al * sc;
-            }
+            for (int ch = 0; ch < 4; ++ch) st.V[ch] *= sc;
+            st.T = 1.0f - al * sc;
         }
     }
     float R[3] = {0.f, 0.f, 0.f};
@@ -164,16 +156,34 @@ __device__ __forceinline__ void render_ray(const RenderArgs& a, const uint2* occ
             ax[0] = make_float4(st.C[0], st.C[1], st.C[2], st.V[0]);
             ax[1] = make_float4(st.V[1], st.V[2], st.V[3], st.gate ? st.T : -1.0f);
         }
-        if (COUNT) {
-            int32_t* c = a.counters + 7 * out_idx;
-            c[0] = rc.blocks;
-            c[1] = rc.occupied;
-            c[2] = rc.in_block;
-            c[3] = rc.active;
-            c[4] = rc.stop_k;
-            c[5] = int32_t(rc.k_sum);
-            c[6] = int32_t(rc.k_sq);
-        }
+    }
+}
+
+template <int VT, int MLP, bool COUNT>
+__device__ __forceinline__ void render_ray(const RenderArgs& a, const uint2* occ, bool valid, int ci, int px,
+                                           int py, int64_t out_idx) {
+    RayAccum st = {{0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}, 1.0f, false};
+    RayCount rc = {0, 0, 0, 0, -1, 0u, 0u};
+    float d[3] = {0.f, 0.f, 1.f};
+    if (valid) {
+        int64_t o[3];
+        int32_t s[3];
+        ray_setup(a.cams[ci], a.grid.N, px, py, o, s, d);
+        // keep the direction as three floats from here on (left alone, the
+        // compiler carries its FP64 form through the march)
+        asm volatile("" : "+v"(d[0]), "+v"(d[1]), "+v"(d[2]));
+        march_composite<VT, COUNT>(a, occ, o, s, st, rc);
+    }
+    finish_ray<MLP>(a, valid, st, d, out_idx);
+    if (COUNT && valid) {
+        int32_t* c = a.counters + 7 * out_idx;
+        c[0] = rc.blocks;
+        c[1] = rc.occupied;
+        c[2] = rc.in_block;
+        c[3] = rc.active;
+        c[4] = rc.stop_k;
+        c[5] = int32_t(rc.k_sum);
+        c[6] = int32_t(rc.k_sq);
     }
 }
 
@@ -219,6 +229,188 @@ __global__ __launch_bounds__(256) void k_render(RenderArgs a) {
         render_ray<VT, MLP, COUNT>(a, occ, valid, ci, px, py, out_idx);
         if (!PERSIST) break;
     }
+}
+
+// ------------------------------------------------- several lanes to a ray
+//
+// A render of few rays (which kernel when: render_split) is a handful of
+// wavefronts per SIMD, each a chain of
+// trips of about 1 us (a distance byte, then the corners it leads to, then the
+// interpolation), and lasts as long as its longest ray.  There a ray gets L
+// lanes: on every trip lane i of the group looks at the i-th lattice sample
+// from the ray's position on, so up to L samples are read and interpolated
+// at once, and the group moves on by the farthest point any of its lanes has
+// cleared.  The samples taken are those of the one-lane march (every sample
+// in an active cell, no skip passes one), and they are composited in lattice
+// order with the same operations (T by a chain of multiplications, the
+// colour and feature sums by a chain of fused multiply-adds, every lane of
+// the group holding them), so the result is the same bit for bit.
+
+// Lane J of each group of L lanes, in every lane of the group (all lanes of a
+// live group run together).
+template <int L, int J>
+__device__ __forceinline__ float group_bcast(float v) {
+    const int x = __float_as_int(v);
+    int y;
+    if constexpr (L == 2) {
+        y = __builtin_amdgcn_update_dpp(0, x, J * 5 + (2 + J) * 0x50, 0xf, 0xf, true);  // quad_perm J, J, 2 + J, 2 + J
+    } else if constexpr (L == 4) {
+        y = __builtin_amdgcn_update_dpp(0, x, J * 0x55, 0xf, 0xf, true);  // quad_perm J, J, J, J
+    } else {
+        static_assert(L == 16, "groups of 2, 4 or 16 lanes");
+        y = __builtin_amdgcn_update_dpp(0, x, 0x150 + J, 0xf, 0xf, true);  // row_newbcast J
+    }
+    return __int_as_float(y);
+}
+
+template <int CTRL>
+__device__ __forceinline__ int32_t dpp_max(int32_t v) {
+    return max(v, __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, true));
+}
+
+// Largest value (>= 0) of the group, in every lane of it.
+template <int L>
+__device__ __forceinline__ int32_t group_max(int32_t v) {
+    v = dpp_max<0xB1>(v);                          // quad_perm 1, 0, 3, 2
+    if constexpr (L >= 4) v = dpp_max<0x4E>(v);    // quad_perm 2, 3, 0, 1
+    if constexpr (L == 16) {
+        v = dpp_max<0x141>(v);  // row_half_mirror
+        v = dpp_max<0x140>(v);  // row_mirror
+    }
+    return v;
+}
+
+// f(integral_constant J) for J = 0 .. N - 1
+template <int N, int J = 0, typename F>
+__device__ __forceinline__ void unrolled(F&& f) {
+    if constexpr (J < N) {
+        f(std::integral_constant<int, J>{});
+        unrolled<N, J + 1>(f);
+    }
+}
+
+template <int VT, int L>
+__device__ __forceinline__ void march_composite_group(const RenderArgs& a, const uint2* occ, int lane,
+                                                      const int64_t o[3], const int32_t s[3], RayAccum& st) {
+    const GridArgs& g = a.grid;
+    const float cs = VT == 0 ? (1.0f / 255.0f) : 1.0f;
+    const float kx = g.sigma_scale * cs / float(g.N);
+    const int me = lane & (L - 1);
+    const uint32_t nb = uint32_t(g.Bp), nbb = nb * nb;
+    const uint32_t nc = uint32_t(g.Bc), ncc = nc * nc;
+    const int32_t ahead[3] = {me * s[0], me * s[1], me * s[2]};
+    FlatWalk w;
+    if (!w.init(g, o, s)) return;
+    for (;;) {
+        // on to the next occupied macroblock: nothing but LDS and arithmetic
+        bool live = true;
+        while (live && w.left <= 0) live = w.enter(g, occ, s);
+        if (!live) break;
+        Sample smp;
+        smp.active = false;
+        int32_t reach = 0;
+        if (me < w.left) {
+            const int32_t q[3] = {w.q[0] + ahead[0], w.q[1] + ahead[1], w.q[2] + ahead[2]};
+            const int32_t p[3] = {q[0] >> 16, q[1] >> 16, q[2] >> 16};
+            const int32_t d = w.dist[cell_index(p, nc, ncc)];
+            if (d == 0) {
+                const int32_t fr[3] = {q[0] & 0xFFFF, q[1] & 0xFFFF, q[2] & 0xFFFF};
+                const uint8_t* vox = w.dist + g.dist_bytes;
+                if (VT == 0) {
+                    Corners8 cn;
+                    load_corners_u8(vox + (uint64_t(cell_index(p, nb, nbb)) << 3), g.Bp, cn);
+                    interp_u8(cn, fr, smp);
+                    if (a.opts.nn_gate) smp.active = nearest_nonzero_u8(cn, fr);
+                } else {
+                    gather_f32(vox, g.Bp, p, fr, smp, a.opts.nn_gate != 0);
+                }
+                reach = me + 1;
+            } else {
+                reach = me + skip_steps(d, w.smax, w.inv_smax);
+            }
+        }
+        reach = min(group_max<L>(reach), w.left);
+        if (__any(smp.active)) {
+            // as composite(): T before this lane's sample, then the sums in lattice order
+            const float e = smp.active ? __expf(-(smp.sigma_raw * kx)) : 1.0f;
+            float T = st.T, before = st.T;
+            unrolled<L>([&](auto J) {
+                if (J == me) before = T;
+                T *= group_bcast<L, J>(e);
+            });
+            const bool ends = a.opts.early_stop && smp.active && before * e < a.opts.t_stop;
+            const uint64_t all = __ballot(ends);
+            const uint32_t mine = uint32_t(all >> (lane & ~(L - 1))) & ((1u << L) - 1u);
+            const int last = mine != 0 ? __builtin_ctz(mine) : L - 1;
+            bool take = smp.active;
+            if (all != 0) {
+                take = take && me <= last;
+                const float at = __shfl(before * e, (lane & ~(L - 1)) | last);
+                if (mine != 0) T = at;
+            }
+            const uint32_t taken = uint32_t(__ballot(take) >> (lane & ~(L - 1))) & ((1u << L) - 1u);
+            st.gate = st.gate || taken != 0;
+            const float wc = take ? before * (1.0f - e) * cs : 0.0f;
+            float v[7];
+#pragma unroll
+            for (int c = 0; c < 3; ++c) v[c] = take ? smp.rgb[c] : 0.0f;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) v[3 + c] = take ? smp.feat[c] : 0.0f;
+            unrolled<L>([&](auto J) {
+                const float wj = group_bcast<L, J>(wc);
+#pragma unroll
+                for (int c = 0; c < 3; ++c) st.C[c] = fmaf(wj, group_bcast<L, J>(v[c]), st.C[c]);
+#pragma unroll
+                for (int c = 0; c < 4; ++c) st.V[c] = fmaf(wj, group_bcast<L, J>(v[3 + c]), st.V[c]);
+            });
+            st.T = T;
+            if (mine != 0) break;
+        }
+        w.left -= reach;
+        w.kk += reach;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) w.q[c] += mul_s24(reach, s[c]);
+    }
+}
+
+// A wavefront takes 64 / L consecutive entries of a ray list, or that part of
+// a tile's 64 pixels.
+template <int VT, int MLP, int L>
+__global__ __launch_bounds__(256) void k_render_group(RenderArgs a) {
+    const uint2* occ = stage_occupancy(a.grid);
+    const int lane = threadIdx.x & 63;
+    const uint32_t wg = a.tile_order ? xcd_grouped(blockIdx.x, gridDim.x) : blockIdx.x;
+    const int64_t wt = wave_uniform(int64_t(wg) * (blockDim.x >> 6) + (threadIdx.x >> 6));
+    constexpr int kRays = 64 / L;
+    bool valid;
+    int ci = 0, px = 0, py = 0;
+    int64_t out_idx;
+    if (a.mode == kModeList) {
+        if (wt * kRays >= a.n_rays) return;  // wave-uniform
+        out_idx = wt * kRays + lane / L;
+        valid = out_idx < a.n_rays;
+        if (valid) {
+            const int64_t r = a.ray_ids[out_idx];
+            ci = find_camera_by_ray(a.cams, a.n_cams, r);
+            const int64_t local = r - a.cams[ci].ray_offset;
+            py = int(local / a.cams[ci].W);
+            px = int(local - int64_t(py) * a.cams[ci].W);
+        }
+    } else {
+        if (wt >= a.total_tiles * L) return;  // wave-uniform
+        const int64_t t = wave_uniform(a.tile_order ? int64_t(a.tile_order[wt / L]) : wt / L);
+        valid = tile_pixel(a, t, int(wt % L) * kRays + lane / L, ci, px, py, out_idx);
+    }
+    RayAccum st = {{0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}, 1.0f, false};
+    float d[3] = {0.f, 0.f, 1.f};
+    if (valid) {
+        int64_t o[3];
+        int32_t s[3];
+        ray_setup(a.cams[ci], a.grid.N, px, py, o, s, d);
+        asm volatile("" : "+v"(d[0]), "+v"(d[1]), "+v"(d[2]));  // three floats, as in render_ray
+        march_composite_group<VT, L>(a, occ, lane, o, s, st);
+    }
+    finish_ray<MLP>(a, valid && (lane & (L - 1)) == 0, st, d, out_idx);
 }
 
 // Visit trace: one lane per listed ray (or per ray id when the list is absent).
@@ -373,12 +565,54 @@ hipError_t launch_tile_order(const RenderArgs& a, uint8_t* cls, int32_t* counts,
     return hipGetLastError();
 }
 
+// Lanes per ray, by measurement (us; views of a shell grid at 39 degrees,
+// scattered pixels, 8x8 patches).  uint8, 512^3:
+//                       1 lane    4     16
+//    4,096 pixels/patches  402/180  175/83  74/47
+//   32,768                 339/235  181/105 169/110
+//   65,536                 382/296  222/140 272/178
+//   512x512 frame          394     266 (in tile order; 352 in image order)
+//   640x480 frame          372     323        (1024^3: 859 -> 576)
+//   800x800 frame          412     530        (1024^3, FP16: 859 -> 1084)
+// so 16 lanes up to 2^15 rays, 4 up to 3 2^17.  Past 2^16 rays the
+// wavefronts are not all resident at once, and the order pays for its two
+// launches.  float32 samples are 256 bytes each and bound by the texture
+// path; the samples of one ray side by side share most of their lines, so
+// there the split also pays where the chip is full: eight 800x800 views of
+// the 512^3 grid 5.25 ms, 2 lanes 4.05, 4 lanes 5.1; of a 1024^3 grid 13.0,
+// 7.6, 7.9; 2^20 scattered pixels 3.38, 2.09, 1.95.  The FP16 network's tiles
+// run once per wavefront, however many rays it holds: four 1080p views take
+// 7.05 ms with one lane and 7.20 with two, eight 800x800 views 5.24 and 4.86.
+RenderSplit render_split(const RenderArgs& a, bool f32, bool f16) {
+    const bool list = a.ray_ids != nullptr;
+    if (a.n_rays <= (int64_t(1) << 15)) return {16, 0};
+    if (a.n_rays <= (int64_t(1) << 16)) return {4, 0};
+    if (a.n_rays <= (int64_t(3) << 17)) return {4, 1};
+    if (f32 && list && a.n_rays <= (int64_t(1) << 20)) return {4, 1};
+    if (f32 && (!f16 || a.n_rays <= (int64_t(6) << 20))) return {2, 1};
+    return {1, 1};
+}
+
+template <int VT, int MLP, int L>
+static hipError_t launch_render_group(const RenderArgs& a, hipStream_t s) {
+    constexpr int kRays = 64 / L;
+    const int64_t waves = a.mode == kModeList ? (a.n_rays + kRays - 1) / kRays : a.total_tiles * L;
+    hipLaunchKernelGGL((k_render_group<VT, MLP, L>), dim3(unsigned((waves + 3) / 4)), dim3(256),
+                       size_t(a.grid.n_words) * sizeof(uint2), s, a);
+    return hipGetLastError();
+}
+
 template <int VT, int MLP>
 static hipError_t launch_render_t(const RenderArgs& args, int wpg, int n_groups, hipStream_t s) {
+    if (args.split.lanes == 16) return launch_render_group<VT, MLP, 16>(args, s);
+    if (args.split.lanes == 4) return launch_render_group<VT, MLP, 4>(args, s);
+    if constexpr (VT == 1) {
+        if (args.split.lanes == 2) return launch_render_group<VT, MLP, 2>(args, s);
+    }
     const int threads = 64 * wpg;
-    // A ray list of up to 2^16 rays fills at most one wavefront per SIMD at
-    // 64 rays each, and a lone wavefront waits on its own latencies: such
-    // lists go 32 (up to 2^16) or 16 (up to 2^15) rays to a wavefront.
+    // The counted render of a short list: a lone wavefront per SIMD waits on
+    // its own latencies, so lists of up to 2^16 rays go 32 and of up to 2^15
+    // 16 rays to a wavefront.
     RenderArgs a = args;
     a.list_rpw = a.n_rays <= (int64_t(1) << 15) ? 16 : (a.n_rays <= (int64_t(1) << 16) ? 32 : 64);
     unsigned blocks;

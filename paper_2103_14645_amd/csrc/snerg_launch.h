@@ -17,6 +17,12 @@ enum MlpMode : int32_t {
     kMlpF16 = 2,   // FP16 MFMA tiles, FP32 accumulation
 };
 
+// How a render deals rays to lanes (render_split): lanes per ray, and whether
+// its tiles go in heavy-first order.
+struct RenderSplit {
+    int32_t lanes, ordered;
+};
+
 struct RenderArgs {
     GridArgs grid;
     RenderOpts opts;
@@ -29,6 +35,7 @@ struct RenderArgs {
     int64_t total_tiles;
     int32_t tile_w, tile_h;  // tile_w * tile_h == 64
     int32_t list_rpw;        // set by the launch: rays per wavefront of a ray-list launch
+    RenderSplit split;       // modes tiles and list
     int32_t* tile_counter;   // persistent mode
     const int32_t* tile_order;  // tile of each wavefront slot / queue entry (null: identity)
     float* out;              // [n][4]
@@ -121,6 +128,7 @@ hipError_t launch_pack(const PackedLayout& L, int32_t n_blocks, bool f32, const 
 // vt: 0 = uint8 grid, 1 = float32 grid.
 hipError_t launch_render(const RenderArgs& a, int vt, int mlp_mode, int waves_per_group,
                          int n_groups, hipStream_t s);
+RenderSplit render_split(const RenderArgs& a, bool f32, bool f16);
 hipError_t launch_trace(const RenderArgs& a, int vt, hipStream_t s);
 // Heavy-first tile order for a tiled or persistent render: `cls` [total_tiles]
 // and `counts` [33] are scratch (counts zero on entry, left zero on exit),

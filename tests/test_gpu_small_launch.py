@@ -1,0 +1,66 @@
+"""Renders of few rays (and of float32 grids) give each ray several lanes; the
+result must be that of the one-lane kernel bit for bit.  The reference is the
+same rays inside a list too long for the split, and the counted render, which
+always has one lane to a ray."""
+import numpy as np
+import pytest
+import torch
+
+import workloads as W
+from paper_2103_14645_amd import snerg as S
+from tests import gpu_helpers as H
+
+pytestmark = pytest.mark.gpu
+LONG = (1 << 20) + 17
+
+
+def grid(kind):
+    if kind == "shell":
+        g = W.shell_grid(128, 16, 0.05)
+        return g, None
+    g = W.tiny_grid(N=48, B=8, n_occupied=40, zero_frac=0.4, seed=3)
+    return g, tuple((a / 255.0).astype(np.float32) for a in (g.dens, g.rgb, g.feat)) if kind == "f32" else None
+
+
+def render(dg, mlp, cams, ids, opts):
+    return S.render(H.handle(), dg, mlp, cams, ray_ids=ids, opts=opts, want_aux=True)
+
+
+@pytest.mark.parametrize("kind", ["shell", "blocks", "f32"])
+@pytest.mark.parametrize("kw", [dict(), dict(fp16=True), dict(early_stop=False), dict(mlp_on=False, nn_gate=True),
+                                dict(unpremultiply=True, bg=(0.2, 0.5, 0.9)), dict(t_stop=0.5)])
+def test_list_bitwise(kind, kw):
+    H.say(f"small lists {kind} {kw}")
+    g, values = grid(kind)
+    dg = H.device_grid(g, values)
+    cams = [W.orbit_camera(300, 200, seed=4), W.look_at((0.1, 0.2, -0.1), 210, 130, 70.0)]
+    mlp = S.mlp_tensor(W.mlp_weights())
+    opts = S.make_opts(**kw)
+    total = sum(c.n_rays for c in cams)
+    ids = torch.from_numpy(np.random.default_rng(1).integers(0, total, LONG)).cuda()
+    ref, raux = render(dg, mlp, cams, ids, opts)
+    if kind == "f32":  # its long lists are split too: the counted render's one lane is the reference
+        ref, _ = S.render_counted(H.handle(), dg, mlp, cams, ray_ids=ids, opts=opts)
+        out, raux = render(dg, mlp, cams, ids, opts)
+        assert torch.equal(out, ref)
+    for n in (1, 3, 4, 5, 63, 1000, 32768, 32769, 65536, 65537, 393216, 393217, 1 << 20):
+        out, aux = render(dg, mlp, cams, ids[:n].contiguous(), opts)
+        assert torch.equal(out, ref[:n]) and torch.equal(aux, raux[:n]), (kind, kw, n)
+
+
+@pytest.mark.parametrize("shape", [(1, 1), (64, 64), (255, 127), (257, 255), (513, 510), (633, 621)])
+@pytest.mark.parametrize("mode", ["tiles", "persistent", "graph", "noalloc"])
+@pytest.mark.parametrize("kind", ["shell", "f32"])
+def test_frames_bitwise(shape, mode, kind):
+    H.say(f"small frames {shape} {mode} {kind}")
+    dg = H.device_grid(*grid(kind))
+    cams = [W.orbit_camera(*shape, seed=6), W.orbit_camera(5, 3, seed=7)]
+    mlp = S.mlp_tensor(W.mlp_weights())
+    opts = S.make_opts(persistent=mode == "persistent", graph=mode == "graph")
+    ref, _ = S.render_counted(H.handle(), dg, mlp, cams, opts=S.make_opts())
+    out = torch.zeros_like(ref)
+    call = S.snerg_render_noalloc if mode == "noalloc" else S.snerg_render
+    for _ in range(2):
+        out.zero_()
+        call(H.handle(), dg.struct(), mlp, S.make_cameras(cams), None, len(out), opts, out)
+        assert torch.equal(out, ref), (shape, mode)

@@ -111,10 +111,10 @@ extern "C" {
 #define SNERG_FLAG_PER_SAMPLE_MLP (1u << 6)
 /* Backward with a ray list that comes in aligned groups of 64 neighbouring
  * rays (8x8 pixel patches, as the fine-tuning patch sampler draws them):
- * each wavefront's rays share voxels, so their gradients are summed per
- * voxel in LDS before the device atomics, as for whole views.  Without it a
- * ray list's gradients pass through an LDS log (no summing; faster when
- * rays share little).  Results are the same up to float summation order
+ * neighbours share voxels, so their gradients are summed per voxel in LDS
+ * before the device atomics, as for whole views.  Without it the gradients of
+ * a ray list of at most 2^18 rays pass through an LDS log (no summing; faster
+ * when rays share little).  Results are the same up to float summation order
  * either way. */
 #define SNERG_FLAG_PATCH_RAYS (1u << 7)
 /* Backward: add the gradients into grad_mlp, grad_dens, grad_rgb and
@@ -234,13 +234,12 @@ int snerg_render(snerg_handle *h, const snerg_grid *grid, const float *mlp, cons
  * overwritten, or added to with SNERG_FLAG_ACCUMULATE): grad_mlp [883],
  * grad_dens, grad_rgb, grad_feat in canonical atlas layout (or all eight
  * channels in grad_dens with SNERG_FLAG_GRAD_PACKED).  Gradient sums
- * use float32 atomics, so their rounding depends on scheduling; where a
- * wavefront's rays are summed per voxel in LDS first (whole views, and ray
- * lists with SNERG_FLAG_PATCH_RAYS) the colour and feature sums are 32-bit
- * fixed point, each hand-over rounded to within 2^-24 of the wavefront's
- * largest |dL/dC_d|, |dL/dV|.  A ray list of at most 2^18 rays runs in two
- * phases whose per-ray sample lists (up to 8 KB per ray) live in
- * handle-owned device memory, kept for later calls.  With SNERG_FLAG_MLP_FP16 the MLP
+ * use float32 atomics, so their rounding depends on scheduling; where
+ * neighbouring rays are summed per voxel in LDS first (whole views, ray lists
+ * with SNERG_FLAG_PATCH_RAYS and lists of more than 2^18 rays) the colour and
+ * feature sums are 32-bit fixed point, each hand-over rounded to within 2^-24
+ * of the largest |dL/dC_d|, |dL/dV| of the tile's (or 64 list entries') rays.
+ * With SNERG_FLAG_MLP_FP16 the MLP
  * backward runs on FP16 MFMA tiles with FP32 accumulation (as the forward).
  * With SNERG_FLAG_MLP_GRAD_ONLY only grad_mlp is computed (the fine-tuning
  * of Section 5.5 optimises the deferred network alone): no ray is

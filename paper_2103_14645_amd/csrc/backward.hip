@@ -6,7 +6,7 @@
 //     ray; the weight gradients of the wavefront's 64 rays are summed with
 //     FP32 MFMA outer products (rays are the K dimension) into per-wavefront
 //     partial rows, reduced afterwards.
-//  K2 (k_march_backward): re-march the same samples (nothing per sample was
+//  K2 (k_adjoint): re-march the same samples (nothing per sample was
 //     stored).  With E = g_C . C_d + g_V . V (from the forward's saved C_d,
 //     V), the running prefix P_k = sum_{j<=k} w_j e_j, e_k = g_C . c_k +
 //     g_V . v_k and dL/dT_N = g_rgb . bg - g_alpha, Eq. 2/5/6 give
@@ -17,14 +17,12 @@
 //     g_C, g_V times A = sum_k w_c(k) w_k (colour, features).  Along one ray
 //     each cell coordinate is monotone, so the 8 corners of the current cell
 //     are kept as running (A, D) sums and a voxel is handed over once, when
-//     the ray's cell window leaves it: into a per-wavefront LDS table that
-//     sums the hand-overs of the wavefront's rays (whole views in 8x8 pixel
-//     tiles, patch lists), or an LDS log (scattered ray lists), flushed to
-//     the gradient arrays with float atomics grouped by cache line.
-//  Short ray lists (up to 2^18 rays) run K2 in two phases: k_backward_record
-//     lists each ray's samples, k_backward_from_list runs the same adjoint
-//     over the lists (the single re-march is as slow as its slowest
-//     wavefront when the wavefronts are few).
+//     the ray's cell window leaves it: into an LDS table that sums the
+//     hand-overs of 32 neighbouring rays (whole views in 64-pixel tiles,
+//     patch lists, long lists) or an LDS log (scattered lists), either way
+//     flushed to the gradient arrays with float atomics grouped by cache line.
+#include <type_traits>
+
 #include "march.h"
 #include "mlp.h"
 #include "snerg_launch.h"
@@ -41,6 +39,12 @@ constexpr int kStageRow = 105;
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
     for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m);
+    return v;
+}
+
+__device__ __forceinline__ float wave_max(float v) {
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) v = fmaxf(v, __shfl_xor(v, m));
     return v;
 }
 
@@ -333,20 +337,22 @@ __global__ __launch_bounds__(64 * kBwdWaves) void k_mlp_backward(BackwardArgs a)
 
 // Canonical gradient slot of padded corner voxel (vx, vy, vz) (local
 // coordinates in [-1, B]) of the block with atlas id `id` at block
-// coordinates b.  Voxels outside the grid or in empty blocks are structural
-// zeros and have no slot (-1).
-__device__ __forceinline__ int64_t canonical_voxel(const GridArgs& g, int32_t id, const int32_t b[3],
-                                                   int vx, int vy, int vz, int32_t& nb_lin, int32_t& nb_id) {
+// coordinates b (x | y << 8 | z << 16).  Voxels outside the grid or in empty
+// blocks are structural zeros and have no slot (-1).  I: int32_t where all
+// indices fit it (a 64-bit multiply costs several times a shift).
+template <typename I>
+__device__ __forceinline__ I canonical_voxel(const GridArgs& g, int32_t id, int32_t b, int vx, int vy, int vz,
+                                             int32_t& nb_lin, int32_t& nb_id) {
     const int B = g.B;
     int32_t tid = id;
     if (tid < 0 || tid >= g.n_blocks) return -1;
-    if (vx < 0 || vy < 0 || vz < 0 || vx >= B || vy >= B || vz >= B) {
-        const int nx = b[0] + (vx < 0 ? -1 : (vx >= B ? 1 : 0));
-        const int ny = b[1] + (vy < 0 ? -1 : (vy >= B ? 1 : 0));
-        const int nz = b[2] + (vz < 0 ? -1 : (vz >= B ? 1 : 0));
-        if (nx < 0 || ny < 0 || nz < 0 || nx >= g.G || ny >= g.G || nz >= g.G) return -1;
+    if ((vx | vy | vz) < 0 || max(max(vx, vy), vz) >= B) {
+        const int nx = (b & 0xff) + (vx < 0 ? -1 : (vx >= B ? 1 : 0));
+        const int ny = ((b >> 8) & 0xff) + (vy < 0 ? -1 : (vy >= B ? 1 : 0));
+        const int nz = (b >> 16) + (vz < 0 ? -1 : (vz >= B ? 1 : 0));
+        if ((nx | ny | nz) < 0 || max(max(nx, ny), nz) >= g.G) return -1;
         // the last neighbour looked up (a ray runs along a face for a while)
-        const int32_t nlin = (nz * g.G + ny) * g.G + nx;
+        const int32_t nlin = mul_s24(mul_s24(nz, g.G) + ny, g.G) + nx;
         if (nlin != nb_lin) {
             nb_lin = nlin;
             nb_id = g.ind[nlin];
@@ -357,65 +363,51 @@ __device__ __forceinline__ int64_t canonical_voxel(const GridArgs& g, int32_t id
         vy &= B - 1;
         vz &= B - 1;
     }
-    return int64_t(tid) * B * B * B + (int64_t(vz) * B + vy) * B + vx;
+    return (((((I(tid) << g.logB) | vz) << g.logB) | vy) << g.logB) | vx;
 }
 
-// Running gradient sums for the 8 corner voxels of the ray's current cell.
-struct CellWindow {
-    int32_t c[3];  // padded cell coordinates
-    int32_t rank;  // block record, -1 when empty
-    int32_t id;    // atlas id of the block
-    int32_t b[3];  // block coordinates
-    float A[8], D[8];
-};
-
-// Per-wavefront gradient aggregation in LDS.  The rays of an 8x8 pixel tile
-// share most of the voxels they touch, so each voxel's eight gradient values
-// (density, RGB, features) are first summed in an open-addressed table of
-// kAggSlots entries and reach device memory with one set of atomics per
-// table flush instead of one per ray.  Keys are canonical voxel indices
-// (< 2^31; the launch falls back to direct atomics otherwise).
+// Gradient aggregation in LDS.  Neighbouring rays share most of the voxels
+// they touch, so each voxel's eight gradient values (density, RGB, features)
+// are first summed in an open-addressed table of kAggSlots entries, one per
+// workgroup, and reach device memory with one set of atomics per table flush
+// instead of one per ray.  Keys are canonical voxel indices (< 2^31; the
+// launch takes the log otherwise).
 //
 // The colour and feature sums are kept in 32-bit fixed point: on gfx950 an
 // LDS float add (ds_add_f32) retires about one lane every three cycles, an
 // LDS integer add (ds_add_u32) more than forty times faster.  A ray hands a
 // voxel its colour gradient A g_C with A = sum_k w_c(k) w_k, and the A of all
-// of a ray's hand-overs add up to at most sum_k w_k <= 1, so with
-// M = max over the wavefront's rays of |g_C|, |g_V| all that one ray hands to
-// one voxel is at most M and a table entry (64 rays between flushes) at most
-// 64 M.  Values are scaled by 2^S, the largest power of two with M 2^S < 2^24,
-// and rounded to integers: an entry stays below 2^30 (plus its rounding),
+// of a ray's hand-overs add up to at most sum_k w_k <= 1, so with M = max over
+// the rays of the tile, or of 64 list entries, of |g_C|, |g_V| all that one ray
+// hands to one voxel is at most M and a table entry (32 rays between flushes)
+// at most 32 M.  Values are scaled by 2^S, the largest power of two with M 2^S < 2^24,
+// and rounded to integers: an entry stays below 2^29 (plus its rounding),
 // and each hand-over carries a rounding error of at most 2^-24 M.  The
 // density sums, whose size depends on the grid values, stay in float.
-constexpr int kAggSlots = 512;
+constexpr int kAdjWaves = 4;  // wavefronts per workgroup: 32 rays, 8 lanes each
 constexpr int kAggLog = 9;
+constexpr int kAggSlots = 1 << kAggLog;
 constexpr int kAggProbes = 16;
-// Flush once this many keys are in.  Every flush sends each held voxel's
-// eight sums to device memory as float atomics, which gfx950 executes at the
-// memory side, about 21 G cache lines per second, so the fewer flushes the
-// better: at 7/8 full the adjoint frame runs 18% faster than at 1/2 (the
-// table then holds most of a tile's voxels at once); a key that finds no
-// free slot within kAggProbes probes goes to device memory directly.
-constexpr int kAggFlushAt = kAggSlots * 7 / 8;
-constexpr int kAggWaves = 4;                 // wavefronts per workgroup
-constexpr int kAggWords = kAggSlots * 9;     // keys, 8 value planes
-// dynamic LDS of the re-march kernels after the occupancy words: kAggWaves tables
-constexpr int kAggLdsWords = kAggWaves * kAggWords;
+constexpr int kAggWords = kAggSlots * 9;  // keys, 8 value planes
+// The workgroup looks at the table every kAggTrips trips of its rays and
+// flushes it when it holds more than kAggFlushAt keys; what its rays add in
+// four trips (up to 32 samples each) mostly fits above that, and a key that
+// finds no free slot within kAggProbes probes goes to device memory directly.
+constexpr int kAggFlushAt = kAggSlots * 9 / 16;
+constexpr int kAggTrips = 4;
+
+// The log of a wavefront whose rays share few voxels, in 16-byte entries.
+constexpr int kLogEntries = 320;
 
 struct AggTable {
     int32_t* key;  // [kAggSlots], -1 = free
     float* val;    // [8][kAggSlots]: plane 0 float (density), planes 1..7 int32 fixed point
-    float q;       // wave-uniform 2^S: fixed-point scale of the colour and feature planes
+    float q;       // 2^S: fixed-point scale of the colour and feature planes
     float dq;      // 2^-S
 };
 
-// The same LDS as an append-only log, for rays that share few voxels
-// (scattered ray lists): entry e holds a key and its eight float values,
-// written once, with no probing and no LDS atomics (AdjointRay::commit
-// places the entries).  Flushed by cache line as the table is.
-
-// Fixed-point scale for a wavefront whose largest |g_C|, |g_V| is m (m >= 0,
-// the same value in every lane): 2^S with m 2^S < 2^24 <= 2 m 2^S.
+// Fixed-point scale for rays whose largest |g_C|, |g_V| is m (m >= 0, the
+// same value in every lane): 2^S with m 2^S < 2^24 <= 2 m 2^S.
 __device__ __forceinline__ void agg_scale(AggTable& t, float m) {
     int e = 0;
     (void)__builtin_frexpf(m, &e);  // 2^(e-1) <= m < 2^e
@@ -425,620 +417,544 @@ __device__ __forceinline__ void agg_scale(AggTable& t, float m) {
     t.dq = __builtin_ldexpf(1.0f, -sh);
 }
 
-__device__ __forceinline__ void add_global(const BackwardArgs& a, int64_t vi, const float v[8], bool feat) {
-    if (a.grad_packed) {
-        float* g = a.grad_dens + 8 * vi;
-        for (int c = 0; c < (feat ? 8 : 4); ++c) unsafeAtomicAdd(g + c, v[c]);
-        return;
-    }
-    unsafeAtomicAdd(a.grad_dens + vi, v[0]);
-    unsafeAtomicAdd(a.grad_rgb + 3 * vi + 0, v[1]);
-    unsafeAtomicAdd(a.grad_rgb + 3 * vi + 1, v[2]);
-    unsafeAtomicAdd(a.grad_rgb + 3 * vi + 2, v[3]);
-    if (feat) {
-        unsafeAtomicAdd(a.grad_feat + 4 * vi + 0, v[4]);
-        unsafeAtomicAdd(a.grad_feat + 4 * vi + 1, v[5]);
-        unsafeAtomicAdd(a.grad_feat + 4 * vi + 2, v[6]);
-        unsafeAtomicAdd(a.grad_feat + 4 * vi + 3, v[7]);
-    }
+// The device address of channel c (0 density, 1..3 RGB, 4..7 features) of
+// voxel vi.
+__device__ __forceinline__ float* grad_channel(const BackwardArgs& a, int64_t vi, int c) {
+    if (a.grad_packed) return a.grad_dens + 8 * vi + c;
+    return c == 0 ? a.grad_dens + vi : (c < 4 ? a.grad_rgb + 3 * vi + (c - 1) : a.grad_feat + 4 * vi + (c - 4));
 }
 
-// Adds v to the table entry of `key` (lanes may diverge); false when no slot
-// was found within kAggProbes probes.  `fresh` counts the lane's new keys.
-__device__ __forceinline__ bool agg_add(const AggTable& t, int32_t key, const float v[8], bool feat, int& fresh) {
-    const uint32_t h = (uint32_t(key) * 2654435761u) >> (32 - kAggLog);
+// The table slot of `key` (lanes may diverge), claimed if it has none; -1
+// when no slot was found within kAggProbes probes.  `fresh` counts the lane's
+// new keys.
+__device__ __forceinline__ int agg_slot(const AggTable& t, int32_t key, int& fresh) {
+    uint32_t sl = (uint32_t(key) * 2654435761u) >> (32 - kAggLog);
+#pragma nounroll
     for (int pr = 0; pr < kAggProbes; ++pr) {
-        const uint32_t sl = (h + pr) & (kAggSlots - 1);
         // one round trip per probe: the compare-and-swap claims a free slot
         // and otherwise returns the key that holds it
-        int32_t k = atomicCAS(t.key + sl, -1, key);
-        if (k == -1) {
-            ++fresh;
-            k = key;
-        }
-        if (k == key) {
-            const int nv = feat ? 8 : 4;
-            atomicAdd(t.val + sl, v[0]);
-            int32_t* iv = reinterpret_cast<int32_t*>(t.val);
-            for (int c = 1; c < nv; ++c) atomicAdd(iv + c * kAggSlots + sl, int32_t(__builtin_rintf(v[c] * t.q)));
-            return true;
-        }
+        const int32_t k = atomicCAS(t.key + sl, -1, key);
+        fresh += k == -1 ? 1 : 0;
+        if (k == -1 || k == key) return int(sl);
+        sl = (sl + 1) & (kAggSlots - 1);
     }
-    return false;
+    return -1;
 }
 
-// The device address of channel c (0 density, 1..3 RGB, 4..7 features) of
-// voxel key in the three separate gradient arrays.
-__device__ __forceinline__ float* grad_channel(const BackwardArgs& a, int32_t key, int c) {
-    return c == 0 ? a.grad_dens + key
-                  : (c < 4 ? a.grad_rgb + 3 * int64_t(key) + (c - 1) : a.grad_feat + 4 * int64_t(key) + (c - 4));
-}
-
-// All 64 lanes together: the log's first n entries go to device memory and
-// the log is emptied.  Lanes are laid across each entry's channels as in
-// agg_flush.
-template <bool FEAT>
-__device__ __forceinline__ void log_flush(const BackwardArgs& a, const AggTable& t, int lane, int n) {
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    if (a.grad_packed) {
-        constexpr int kC = FEAT ? 8 : 4;  // lanes per entry, one channel each
-        const int c = lane % kC;
-        for (int e = lane / kC; e < n; e += 64 / kC) {
-            const float v = t.val[c * kAggSlots + e];
-            if (v != 0.0f) unsafeAtomicAdd(a.grad_dens + 8 * int64_t(t.key[e]) + c, v);
-        }
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        return;
-    }
-    const int c = lane & 3;
-    for (int e = lane >> 2; e < n; e += 16) {
-        const int32_t key = t.key[e];
-        const float v0 = t.val[c * kAggSlots + e];
-        if (v0 != 0.0f) unsafeAtomicAdd(grad_channel(a, key, c), v0);
-        if (FEAT) {
-            const float v1 = t.val[(c + 4) * kAggSlots + e];
-            if (v1 != 0.0f) unsafeAtomicAdd(grad_channel(a, key, c + 4), v1);
-        }
-    }
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
-
-// All 64 lanes together: every used entry goes to device memory, the table
-// is cleared.  gfx950 serves a wavefront's float atomics per 64-byte line
-// (measured: about 21 G lines per second whether a line carries one lane's
-// add or sixteen), so the lanes are laid across the entries' channels, not
-// the entries: lane l takes entry l / 4 of a group of 16 and within it
-// channels l % 4 and l % 4 + 4, so that one instruction adds an entry's
-// density and colour (two lines) and the next its four features (one
-// line), where one lane per entry would touch seven lines.  With packed
+// The whole workgroup, between barriers: every used entry goes to device
+// memory, the table is cleared.  gfx950 serves a wavefront's float atomics
+// per 64-byte line (measured: about 21 G lines per second whether a line
+// carries one lane's add or sixteen), so the lanes are laid across the
+// entries' channels, not the entries: lane l takes entry l / 4 of a group of
+// 16 and within it channels l % 4 and l % 4 + 4, so that one instruction adds
+// an entry's density and colour (two lines) and the next its four features
+// (one line), where one lane per entry would touch seven lines.  With packed
 // gradients an entry's eight sums share one line: eight lanes per entry (four
 // without features), one instruction per group.
 template <bool FEAT>
-__device__ __forceinline__ void agg_flush(const BackwardArgs& a, const AggTable& t, int lane) {
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-    __builtin_amdgcn_wave_barrier();
+__device__ __forceinline__ void agg_flush(const BackwardArgs& a, const AggTable& t) {
     int32_t* iv = reinterpret_cast<int32_t*>(t.val);
-    if (a.grad_packed) {
-        constexpr int kC = FEAT ? 8 : 4;
-        const int c = lane % kC;
-        for (int sl = lane / kC; sl < kAggSlots; sl += 64 / kC) {
-            const int32_t key = t.key[sl];
-            if (key >= 0) {
-                float v;
-                if (c == 0) {
-                    v = t.val[sl];
-                    t.val[sl] = 0.0f;
-                } else {
-                    v = float(iv[c * kAggSlots + sl]) * t.dq;
-                    iv[c * kAggSlots + sl] = 0;
-                }
-                if (v != 0.0f) unsafeAtomicAdd(a.grad_dens + 8 * int64_t(key) + c, v);
-            }
-        }
-    } else {
-        const int c = lane & 3;
-        for (int sl = lane >> 2; sl < kAggSlots; sl += 16) {
-            const int32_t key = t.key[sl];
-            if (key >= 0) {
-                float v0;
-                if (c == 0) {
-                    v0 = t.val[sl];
-                    t.val[sl] = 0.0f;
-                } else {
-                    v0 = float(iv[c * kAggSlots + sl]) * t.dq;
-                    iv[c * kAggSlots + sl] = 0;
-                }
-                if (v0 != 0.0f) unsafeAtomicAdd(grad_channel(a, key, c), v0);
-                if (FEAT) {
-                    const float v1 = float(iv[(c + 4) * kAggSlots + sl]) * t.dq;
-                    iv[(c + 4) * kAggSlots + sl] = 0;
-                    if (v1 != 0.0f) unsafeAtomicAdd(grad_channel(a, key, c + 4), v1);
-                }
-            }
-        }
-    }
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    for (int sl = lane; sl < kAggSlots; sl += 64) t.key[sl] = -1;
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
-
-__device__ __forceinline__ int wave_sum_i32(int v) {
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m);
-    return __builtin_amdgcn_readfirstlane(v);
-}
-
-template <bool FEAT, bool AGG>
-__device__ __forceinline__ void flush_corner(const BackwardArgs& a, const AggTable& t, const CellWindow& w, int c,
-                                             const float gC[3], const float gV[4], int& fresh, int32_t& nb_lin,
-                                             int32_t& nb_id) {
-    const float A = w.A[c], D = w.D[c];
-    if (A == 0.0f && D == 0.0f) return;
-    const GridArgs& g = a.grid;
-    const int64_t vi = canonical_voxel(g, w.id, w.b, w.c[0] + (c & 1) - 1, w.c[1] + ((c >> 1) & 1) - 1,
-                                       w.c[2] + (c >> 2) - 1, nb_lin, nb_id);
-    if (vi < 0) return;
-    float v[8] = {g.sigma_scale * D, A * gC[0], A * gC[1], A * gC[2], 0.f, 0.f, 0.f, 0.f};
-    if (FEAT) {
-        v[4] = A * gV[0]; v[5] = A * gV[1]; v[6] = A * gV[2]; v[7] = A * gV[3];
-    }
-    if (AGG && agg_add(t, int32_t(vi), v, FEAT, fresh)) return;
-    add_global(a, vi, v, FEAT);
-}
-
-// The adjoint state of one ray's re-march: its output gradient and the
-// forward's per-ray results (E, the T_N tail), the running transmittance T
-// and prefix P_k, and the corner window.  sample() takes the samples in
-// march order, as march_ray hands them over (inactive ones included), and
-// returns true once the early-stop rule ends the ray; finish() hands over
-// the last window.
-template <bool FEAT, bool AGG, bool LOG = false>
-struct AdjointRay {
-    float gC[3], gV[4];
-    float E, tail, T, Pk;
-    float delta, kx, t_stop;
-    bool early, nn_gate;
-    CellWindow win;
-    int fresh;  // this lane's new table keys since the last count
-    int32_t nb_lin, nb_id;  // the last neighbouring block looked up: linear index, atlas id
-    // LOG: the corners handed over since the last commit, by corner index
-    uint32_t pmask;
-    int32_t pvi[8];
-    float pA[8], pD[8];
-
-    // Reads list position i's state; false when the ray composited nothing
-    // (no grid gradient) or `live` is false.
-    __device__ __forceinline__ bool setup(const BackwardArgs& a, int64_t i, bool live) {
-        float4 a0 = make_float4(0.f, 0.f, 0.f, 0.f), a1 = make_float4(0.f, 0.f, 0.f, -1.f);
-        float4 gg = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (live) {
-            a1 = reinterpret_cast<const float4*>(a.aux)[2 * i + 1];
-            live = a1.w >= 0.0f;  // nothing was composited: no grid gradient
-        }
-        gC[0] = gC[1] = gC[2] = 0.f;
-        gV[0] = gV[1] = gV[2] = gV[3] = 0.f;
-        if (live) {
-            a0 = reinterpret_cast<const float4*>(a.aux)[2 * i];
-            gg = reinterpret_cast<const float4*>(a.grad_rgba)[i];
-            gC[0] = gg.x; gC[1] = gg.y; gC[2] = gg.z;
-            if (FEAT) {
-                const float4 c0 = reinterpret_cast<const float4*>(a.gcv)[2 * i];
-                const float4 c1 = reinterpret_cast<const float4*>(a.gcv)[2 * i + 1];
-                gC[0] = c0.x; gC[1] = c0.y; gC[2] = c0.z;
-                gV[0] = c0.w; gV[1] = c1.x; gV[2] = c1.y; gV[3] = c1.z;
-            }
-        }
-        E = gC[0] * a0.x + gC[1] * a0.y + gC[2] * a0.z + (gV[0] * a0.w + gV[1] * a1.x + gV[2] * a1.y + gV[3] * a1.z);
-        const float gTN = gg.x * a.opts.bg[0] + gg.y * a.opts.bg[1] + gg.z * a.opts.bg[2] - gg.w;
-        tail = a1.w * gTN;
-        T = 1.0f;
-        Pk = 0.0f;
-        delta = 1.0f / float(a.grid.N);
-        kx = a.grid.sigma_scale * delta;
-        t_stop = a.opts.t_stop;
-        early = a.opts.early_stop != 0;
-        nn_gate = a.opts.nn_gate != 0;
-        win.rank = -1;
-        win.id = 0;
-        win.c[0] = win.c[1] = win.c[2] = 0;
-        win.b[0] = win.b[1] = win.b[2] = 0;
-#pragma unroll
-        for (int c = 0; c < 8; ++c) win.A[c] = win.D[c] = 0.0f;
-        fresh = 0;
-        pmask = 0;
-        nb_lin = -1;
-        nb_id = -1;
-        return live;
-    }
-
-    // LOG: keeps corner c's hand-over (lanes may diverge) for commit().
-    __device__ __forceinline__ void stash(const GridArgs& g, int c) {
-        const float A = win.A[c], D = win.D[c];
-        if (A == 0.0f && D == 0.0f) return;
-        const int64_t vi = canonical_voxel(g, win.id, win.b, win.c[0] + (c & 1) - 1, win.c[1] + ((c >> 1) & 1) - 1,
-                                           win.c[2] + (c >> 2) - 1, nb_lin, nb_id);
-        if (vi < 0) return;
-        pvi[c] = int32_t(vi);  // LOG runs only on grids of fewer than 2^31 voxels
-        pA[c] = A;
-        pD[c] = D;
-        pmask |= 1u << c;
-    }
-
-    // LOG, all 64 lanes together: appends the stashed hand-overs to the log,
-    // corner by corner.  The lanes appending a corner take the next entries
-    // in lane order (a ballot and a prefix count), so the fill count n stays
-    // the same in every lane and nothing needs an LDS atomic; the log is
-    // flushed whenever another corner might not fit.
-    template <bool F>
-    __device__ __forceinline__ void commit(const BackwardArgs& a, const AggTable& t, int lane, int& n) {
-        const GridArgs& g = a.grid;
-#pragma unroll
-        for (int c = 0; c < 8; ++c) {
-            const bool want = (pmask >> c) & 1u;
-            const uint64_t m = __ballot(want);
-            if (m == 0) continue;  // wave-uniform
-            if (n > kAggSlots - 64) {
-                log_flush<F>(a, t, lane, n);
-                n = 0;
-            }
-            if (want) {
-                const int e = n + int(__builtin_amdgcn_mbcnt_hi(uint32_t(m >> 32),
-                                                                __builtin_amdgcn_mbcnt_lo(uint32_t(m), 0u)));
-                const float A = pA[c];
-                t.key[e] = pvi[c];
-                t.val[e] = g.sigma_scale * pD[c];
-                t.val[kAggSlots + e] = A * gC[0];
-                t.val[2 * kAggSlots + e] = A * gC[1];
-                t.val[3 * kAggSlots + e] = A * gC[2];
-                if (F) {
-                    t.val[4 * kAggSlots + e] = A * gV[0];
-                    t.val[5 * kAggSlots + e] = A * gV[1];
-                    t.val[6 * kAggSlots + e] = A * gV[2];
-                    t.val[7 * kAggSlots + e] = A * gV[3];
-                }
-            }
-            n += __builtin_popcountll(m);
-        }
-        pmask = 0;
-    }
-
-    // Wavefront-wide (all 64 lanes, the same value in each): the largest
-    // |g_C|, |g_V| sets the table's fixed-point scale.
-    __device__ __forceinline__ void table_scale(AggTable& tab) const {
-        float m = fmaxf(fmaxf(fabsf(gC[0]), fabsf(gC[1])), fmaxf(fabsf(gC[2]), fabsf(gV[0])));
-        m = fmaxf(m, fmaxf(fmaxf(fabsf(gV[1]), fabsf(gV[2])), fabsf(gV[3])));
-#pragma unroll
-        for (int sh = 32; sh >= 1; sh >>= 1) m = fmaxf(m, __shfl_xor(m, sh));
-        agg_scale(tab, m);  // the butterfly leaves the same maximum in every lane
-    }
-
-    __device__ __forceinline__ bool sample(const BackwardArgs& a, const AggTable& tab, int32_t rk, const uint8_t* vox,
-                                           const int32_t p[3], const int32_t fr[3]) {
-        Sample smp;
-        gather_f32(vox, a.grid.Bp, p, fr, smp, nn_gate);
-        return take(a, tab, rk, smp, p, fr);
-    }
-
-    // The sample with its corners already interpolated.
-    __device__ __forceinline__ bool take(const BackwardArgs& a, const AggTable& tab, int32_t rk, const Sample& smp,
-                                         const int32_t p[3], const int32_t fr[3]) {
-        const GridArgs& g = a.grid;
-        if (!smp.active) return false;
-        const float e = __expf(-smp.sigma_raw * kx);
-        const float w = T * (1.0f - e);
-        const float ek = gC[0] * smp.rgb[0] + gC[1] * smp.rgb[1] + gC[2] * smp.rgb[2] +
-                         (gV[0] * smp.feat[0] + gV[1] * smp.feat[1] + gV[2] * smp.feat[2] + gV[3] * smp.feat[3]);
-        Pk += w * ek;
-        T *= e;
-        const float gsig = delta * (T * ek - (E - Pk) - tail);
-        // Slide the corner window to this sample's cell: corners on a
-        // trailing face (or all of them after a jump) are flushed once, the
-        // survivors shift to their new corner index.
-        const bool jump = win.rank != rk || abs(p[0] - win.c[0]) > 1 || abs(p[1] - win.c[1]) > 1 ||
-                          abs(p[2] - win.c[2]) > 1;
-        int dd[3] = {p[0] - win.c[0], p[1] - win.c[1], p[2] - win.c[2]};
-        uint32_t leave = 0;
-        if (jump) {
-            leave = win.rank >= 0 ? 0xFFu : 0u;
+    auto take = [&](int sl, int c) {
+        float v;
+        if (c == 0) {
+            v = t.val[sl];
+            t.val[sl] = 0.0f;
         } else {
-#pragma unroll
-            for (int ax = 0; ax < 3; ++ax) {
-                // corners with bit ax clear: 0x55, 0x33, 0x0F for ax = 0, 1, 2
-                const uint32_t clear = ax == 0 ? 0x55u : (ax == 1 ? 0x33u : 0x0Fu);
-                if (dd[ax] > 0) leave |= clear;
-                if (dd[ax] < 0) leave |= ~clear & 0xFFu;
-            }
+            v = float(iv[c * kAggSlots + sl]) * t.dq;
+            iv[c * kAggSlots + sl] = 0;
         }
-#pragma unroll
-        for (int c = 0; c < 8; ++c)
-            if ((leave >> c) & 1u) {
-                if (LOG) stash(g, c);
-                else flush_corner<FEAT, AGG>(a, tab, win, c, gC, gV, fresh, nb_lin, nb_id);
+        return v;
+    };
+    // the lanes of an entry sit in one wavefront and read its key before any
+    // of them frees it
+    const int kC = a.grad_packed && FEAT ? 8 : 4;  // lanes per entry
+    const int c = threadIdx.x & (kC - 1);
+    for (int sl = threadIdx.x / kC; sl < kAggSlots; sl += blockDim.x / kC) {
+        const int32_t key = t.key[sl];
+        if (key >= 0) {
+            const float v0 = take(sl, c);
+            if (v0 != 0.0f) unsafeAtomicAdd(grad_channel(a, key, c), v0);
+            if (FEAT && kC == 4) {
+                const float v1 = take(sl, c + 4);
+                if (v1 != 0.0f) unsafeAtomicAdd(grad_channel(a, key, c + 4), v1);
             }
-        if (jump) {
-#pragma unroll
-            for (int c = 0; c < 8; ++c) win.A[c] = win.D[c] = 0.0f;
-            win.rank = rk;
-            win.id = g.rank_id[rk];
-            const int32_t lin = g.rank_lin[rk];
-            win.b[0] = lin % g.G;
-            win.b[1] = (lin / g.G) % g.G;
-            win.b[2] = lin / (g.G * g.G);
-            win.c[0] = p[0]; win.c[1] = p[1]; win.c[2] = p[2];
-        } else {
-#pragma unroll
-            for (int ax = 0; ax < 3; ++ax) {
-                const int bit = 1 << ax;
-#pragma unroll
-                for (int c = 0; c < 8; ++c) {
-                    if (c & bit) continue;
-                    const int c1 = c | bit;
-                    const float a0v = win.A[c], d0v = win.D[c], a1v = win.A[c1], d1v = win.D[c1];
-                    win.A[c] = dd[ax] > 0 ? a1v : (dd[ax] < 0 ? 0.0f : a0v);
-                    win.D[c] = dd[ax] > 0 ? d1v : (dd[ax] < 0 ? 0.0f : d0v);
-                    win.A[c1] = dd[ax] < 0 ? a0v : (dd[ax] > 0 ? 0.0f : a1v);
-                    win.D[c1] = dd[ax] < 0 ? d0v : (dd[ax] > 0 ? 0.0f : d1v);
-                }
-                win.c[ax] += dd[ax];
-            }
+            if (c == 0) t.key[sl] = -1;
         }
-        float wc[8];
-        corner_weights(fr, wc);
-#pragma unroll
-        for (int c = 0; c < 8; ++c) {
-            win.A[c] = fmaf(wc[c], w, win.A[c]);
-            win.D[c] = fmaf(wc[c], gsig, win.D[c]);
-        }
-        return early && T < t_stop;
+    }
+}
+
+template <int CTRL>
+__device__ __forceinline__ int32_t dpp(int32_t v) {
+    return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, true);
+}
+template <int CTRL>
+__device__ __forceinline__ float dpp(float v) {
+    return __int_as_float(dpp<CTRL>(__float_as_int(v)));
+}
+
+// The 8 lanes of a ray.  Lane l holds corner (x, y, z) of the ray's cell with
+// z = l / 4 and x, y the low bits of l, flipped where z = 1, so that the
+// neighbour across each axis is one DPP step away: l ^ 1 in x, l ^ 2 in y and
+// l ^ 7, the mirror of 8 lanes, in z.
+constexpr int kFlipX = 0xB1, kFlipY = 0x4E, kFlipZ = 0x141;  // quad_perm 1,0,3,2; 2,3,0,1; row_half_mirror
+// A value that lane a of every quad holds for axis a, of axis x, y, z.
+constexpr int kAxisX = 0x00, kAxisY = 0x55, kAxisZ = 0xAA;
+
+__device__ __forceinline__ float corner_sum(float v) {
+    v += dpp<kFlipX>(v);
+    v += dpp<kFlipY>(v);
+    return v + dpp<kFlipZ>(v);
+}
+
+__device__ __forceinline__ uint32_t ray_bits(bool p, int lane) {
+    return uint32_t(__ballot(p) >> (lane & ~7)) & 0xFFu;
+}
+
+// FlatWalk with its per-axis state dealt to the lanes: in every quad lane
+// q % 4 = 0, 1, 2 holds axis x, y, z (lane 3 a copy of z), the rest is the
+// same in all 8.  A third of the registers and of the work of a macroblock
+// entry, and the registers are what bounds the number of resident wavefronts.
+struct QuadWalk {
+    int32_t kc, F, Q, s, q;  // own axis
+    int32_t stride;          // change of lin across a face of the own axis (0 in lane 3)
+    int32_t kend, k, lin, left, r, smax;
+    float inv_smax;
+    const uint8_t* __restrict__ dist;
+
+    __device__ __forceinline__ bool init(const GridArgs& g, const int64_t o[3], const int32_t s3[3], int l) {
+        FlatWalk w;
+        if (!w.init(g, o, s3)) return false;
+        const int a = l & 3;
+        kc = a == 0 ? w.kc[0] : (a == 1 ? w.kc[1] : w.kc[2]);
+        F = a == 0 ? w.F[0] : (a == 1 ? w.F[1] : w.F[2]);
+        Q = a == 0 ? w.Q[0] : (a == 1 ? w.Q[1] : w.Q[2]);
+        s = a == 0 ? s3[0] : (a == 1 ? s3[1] : s3[2]);
+        stride = a == 0 ? 1 : (a == 1 ? g.G : (a == 2 ? g.G * g.G : 0));
+        stride = s > 0 ? stride : -stride;
+        q = 0;
+        kend = w.kend;
+        k = 0;
+        lin = w.lin;
+        left = 0;
+        r = -1;
+        smax = w.smax;
+        inv_smax = w.inv_smax;
+        dist = g.rec;
+        return true;
     }
 
-    __device__ __forceinline__ void finish(const BackwardArgs& a, const AggTable& tab) {
-        if (win.rank >= 0) {
-#pragma unroll
-            for (int c = 0; c < 8; ++c) {
-                if (LOG) stash(a.grid, c);
-                else flush_corner<FEAT, AGG>(a, tab, win, c, gC, gV, fresh, nb_lin, nb_id);
-            }
+    // As FlatWalk::enter.
+    __device__ __forceinline__ bool enter(const GridArgs& g, const uint2* occ) {
+        const int bs = 16 + g.logB;
+        const int32_t W = int32_t(1) << bs;
+        const uint32_t G3 = uint32_t(g.G) * uint32_t(g.G) * uint32_t(g.G);
+        if (k > kend || uint32_t(lin) >= G3) return false;
+        int32_t kn = min(kc, dpp<kFlipX>(kc));
+        kn = min(kn, dpp<kFlipY>(kn));
+        kn = min(kn, kend + 1);
+        r = block_rank(occ, lin, g.n_blocks);
+        if (r >= 0) {
+            // (records are multiples of 256 bytes)
+            dist = g.rec + (uint64_t(uint32_t(r) * uint32_t(g.rec_stride >> 8)) << 8);
+            q = (s > 0 ? W - F : F - 1) + mul_s24(k, s) + 32768;
+            left = kn - k;
         }
+        int32_t step = 0;
+        if (kc == kn) {
+            step = stride;
+            F += W;
+            const int32_t c = kc + Q;
+            const int32_t cs = mul_s24(c, s);  // c |s| = sign(s) c s
+            kc = (s > 0 ? cs : -cs) >= F ? c : c + 1;
+        }
+        step += dpp<kFlipX>(step);
+        lin += step + dpp<kFlipY>(step);
+        k = kn;
+        return true;
     }
 };
 
-// The table of the calling wavefront in dynamic LDS (after the occupancy
-// words), cleared.
-__device__ __forceinline__ AggTable agg_table(uint2* s_occ, int n_words, int wave, int lane, bool clear) {
-    AggTable tab;
-    int32_t* base = reinterpret_cast<int32_t*>(s_occ + n_words) + wave * kAggWords;
-    tab.key = base;
-    tab.val = reinterpret_cast<float*>(base + kAggSlots);
-    if (clear) {
-        for (int sl = lane; sl < kAggSlots; sl += 64) {
+// One ray per 8 lanes.  A trip of the walk looks at the ray's next 8 lattice
+// samples, one per lane (its distance byte), and then takes the active ones
+// in order, all lanes together, lane by corner: each loads its corner's
+// voxel, the two sums a sample needs (density and g . value) are three DPP
+// additions each, and each lane keeps its corner's (A, D) and hands it over
+// by itself.  One ray per lane, as this was before, paid for every sample
+// with eight guarded hand-over passes and 256 bytes of loads per lane, at two
+// wavefronts per SIMD (197 to 256 registers), and a list of 65,536 rays
+// needed a separate walk to keep 64 rays of unequal length apart.
+//   eight 800x800 views, 512^3, FP32 network   23.7 -> 18.1 ms
+//   16,384 rays in 8x8 patches, 512^3           1.95 -> 0.41 ms
+//   65,536 scattered rays, 1024^3, packed       2.35 -> 1.2 ms
+// Bound by instruction issue with the table (VALUs 82% busy, half the lanes
+// at work: about 270 instructions per sample of 8 rays), for scattered rays
+// by latency and by rays of unequal length side by side.  Registers: 96 (five
+// wavefronts per SIMD) with the table, where six or three cost 9 and 40%;
+// scattered rays want the next sample's voxels in flight, which takes 118
+// (20% slower squeezed into 96).
+// Without a ray list the workgroups walk halves of the cameras'
+// tile_w x tile_h pixel tiles, with one 32 consecutive list entries.  AGG:
+// gradients go through the workgroup's LDS table, else through the
+// wavefront's log.
+template <bool FEAT, bool AGG>
+__global__ __launch_bounds__(64 * kAdjWaves) __attribute__((amdgpu_waves_per_eu(AGG ? 5 : 4))) void k_adjoint(BackwardArgs a) {
+    constexpr int kWaves = kAdjWaves;
+    extern __shared__ uint2 s_occ[];
+    __shared__ float s_max;
+    __shared__ int32_t s_fresh[3], s_live[3];
+    __shared__ float s_gch[AGG ? 1 : kWaves][8][8];  // the rays' gradients by channel
+    const GridArgs& g = a.grid;
+    for (int w = threadIdx.x; w < g.n_words; w += blockDim.x) s_occ[w] = g.occ[w];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int l = lane & 7;
+    const int cz = l >> 2, cx = (l & 1) ^ cz, cy = ((l >> 1) & 1) ^ cz;
+    AggTable tab = {nullptr, nullptr, 0.0f, 0.0f};
+    if (AGG) {
+        tab.key = reinterpret_cast<int32_t*>(s_occ + g.n_words);
+        tab.val = reinterpret_cast<float*>(tab.key + kAggSlots);
+        for (int sl = threadIdx.x; sl < kAggSlots; sl += blockDim.x) {
             tab.key[sl] = -1;
 #pragma unroll
             for (int c = 0; c < 8; ++c) tab.val[c * kAggSlots + sl] = 0.0f;
         }
+        if (threadIdx.x < 3) s_fresh[threadIdx.x] = s_live[threadIdx.x] = 0;
     }
-    return tab;
-}
+    int4* log = reinterpret_cast<int4*>(s_occ + ((g.n_words + 1) & ~1)) + wave * kLogEntries;
 
-// Wavefront-wide, after each step of the lanes: counts the table's new keys
-// and flushes it once it is full enough.
-struct TableSync {
-    int in_table = 0;  // wave-uniform: keys in the table
-    template <bool FEAT>
-    __device__ __forceinline__ void step(const BackwardArgs& a, const AggTable& tab, int lane, int& fresh) {
-        if (__any(fresh != 0)) {
-            in_table += wave_sum_i32(fresh);
-            fresh = 0;
-            if (in_table >= kAggFlushAt) {
-                agg_flush<FEAT>(a, tab, lane);
-                in_table = 0;
-            }
+    // Rays come in sets of 64 (a tile, or 64 list entries), a workgroup takes
+    // half of one.  Ray idx of the set: list position i (indexes aux,
+    // grad_rgba, gcv), pixel (px, py) of camera ci.
+    // (of a view's tiles each XCD takes runs of 32 workgroups, as the render does)
+    const uint32_t u = a.ray_ids ? blockIdx.x : xcd_grouped<32>(blockIdx.x, gridDim.x);
+    const int64_t set = (a.first_group + u) >> 1;
+    const int half = int(u & 1);
+    auto ray_of = [&](int idx, int64_t& i, int& ci, int& px, int& py) {
+        if (a.ray_ids) {
+            i = set * 64 + idx;
+            if (i >= a.n_rays) return false;
+            locate(a, a.ray_ids[i], ci, px, py);
+            return true;
         }
-    }
-};
-
-// One lane per ray.  Without a ray list the wavefronts walk the cameras'
-// tt_w x tt_h pixel tiles (neighbouring rays, shared voxels); with a list,
-// 64 consecutive list entries.  AGG: gradients go through the per-wavefront
-// LDS table.  Every lane stays to the end (the flushes need all 64).
-template <bool FEAT, bool AGG>
-__global__ __launch_bounds__(64 * kAggWaves) void k_march_backward(BackwardArgs a) {
-    extern __shared__ uint2 s_occ[];
-    const GridArgs& g = a.grid;
-    for (int w = threadIdx.x; w < g.n_words; w += blockDim.x) s_occ[w] = g.occ[w];
-    const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
-    AggTable tab = agg_table(s_occ, g.n_words, wave, lane, AGG);
-    __syncthreads();
-
-    // this lane's ray: list position i (indexes aux, grad_rgba, gcv) and id r
-    bool live;
-    int64_t i, r;
-    const int64_t wt = int64_t(a.ray_ids ? blockIdx.x : xcd_grouped(blockIdx.x, gridDim.x)) * kAggWaves + wave;
-    if (a.ray_ids) {
-        i = wt * 64 + lane;
-        live = i < a.n_rays;
-        r = live ? a.ray_ids[i] : 0;
-    } else {
-        live = wt < a.total_tiles;
-        i = r = 0;
-        if (live) {
-            const int ci = find_camera_by_tile(a.cams, a.n_cams, wt);
-            const DevCamera& c = a.cams[ci];
-            const int64_t tl = wt - c.tile_offset;
-            const int px = int(tl % c.tiles_x) * a.tile_w + lane % a.tile_w;
-            const int py = int(tl / c.tiles_x) * a.tile_h + lane / a.tile_w;
-            live = px < c.W && py < c.H;
-            i = r = c.ray_offset + int64_t(py) * c.W + px;
+        ci = find_camera_by_tile(a.cams, a.n_cams, set);
+        const DevCamera& c = a.cams[ci];
+        const int64_t tl = set - c.tile_offset;
+        px = int(tl % c.tiles_x) * a.tile_w + idx % a.tile_w;
+        py = int(tl / c.tiles_x) * a.tile_h + idx / a.tile_w;
+        i = c.ray_offset + int64_t(py) * c.W + px;
+        return px < c.W && py < c.H;
+    };
+    if (AGG && threadIdx.x < 64) {  // the table's scale, from the whole set
+        int64_t i;
+        int ci, px, py;
+        float m = 0.0f;
+        if (ray_of(threadIdx.x, i, ci, px, py) && a.aux[8 * i + 7] >= 0.0f) {
+            const float* v = FEAT ? a.gcv + 8 * i : a.grad_rgba + 4 * i;
+#pragma unroll
+            for (int c = 0; c < (FEAT ? 7 : 3); ++c) m = fmaxf(m, fabsf(v[c]));
         }
+        m = wave_max(m);
+        if (threadIdx.x == 0) s_max = m;
     }
-    AdjointRay<FEAT, AGG> st;
-    live = st.setup(a, i, live);
-    if (AGG) st.table_scale(tab);
-
-    int64_t o[3] = {0, 0, 0};
-    int32_t s[3] = {0, 0, 1 << 15};
+    int64_t i = 0;
+    int ci = 0, px = 0, py = 0;
+    bool live = ray_of((half * kWaves + wave) * 8 + (lane >> 3), i, ci, px, py);
+    QuadWalk w;
     if (live) {
-        int ci, px, py;
-        locate(a, r, ci, px, py);
-        float d[3];
-        ray_setup(a.cams[ci], g.N, px, py, o, s, d);
-    }
-    TableSync sync;
-    march_ray_flat_sync(
-        g, s_occ, live, o, s,
-        [&](int64_t, int32_t rk, const uint8_t* vox, const int32_t p[3], const int32_t fr[3]) {
-            return st.sample(a, tab, rk, vox, p, fr);
-        },
-        [&]() {
-            if (AGG) sync.step<FEAT>(a, tab, lane, st.fresh);
-            return false;
-        });
-    st.finish(a, tab);
-    if (AGG) agg_flush<FEAT>(a, tab, lane);
-}
-
-// Short ray lists in two phases.  With few rays the wavefronts are few and
-// the backward is as slow as its slowest wavefront, whose 64 rays march in
-// lock step: at nearly every step some lane takes a sample, so every step
-// pays for the whole gradient code.  Phase 1 (k_backward_record) walks each
-// ray alone and lists the samples the walk hands over (cell position and
-// macroblock record: cells with a zero distance byte, nearly all of them
-// active; the gradient code decides); phase 2
-// (k_backward_from_list) runs the gradient code over the lists, one listed
-// sample per lane per step, with the same per-ray arithmetic in the same
-// order as k_march_backward.  A ray with more than kBackwardListCap listed
-// samples walks on from its start in phase 2, skipping the listed ones.
-constexpr int kListCap = kBackwardListCap;
-
-__global__ __launch_bounds__(256) void k_backward_record(BackwardArgs a, int4* __restrict__ list,
-                                                         int32_t* __restrict__ count, int64_t* __restrict__ klast) {
-    extern __shared__ uint2 s_occ[];
-    const GridArgs& g = a.grid;
-    for (int w = threadIdx.x; w < g.n_words; w += blockDim.x) s_occ[w] = g.occ[w];
-    __syncthreads();
-    // a.list_rpw rays per wavefront, as in the gradient pass
-    const int lane = threadIdx.x & 63;
-    const int64_t i = (int64_t(blockIdx.x) * (blockDim.x >> 6) + (threadIdx.x >> 6)) * a.list_rpw + lane;
-    if (lane >= a.list_rpw || i >= a.n_rays) return;
-    int32_t n = 0;
-    int64_t kl = 0;
-    // rays that composited nothing have no grid gradient (phase 2 skips them)
-    if (reinterpret_cast<const float4*>(a.aux)[2 * i + 1].w >= 0.0f) {
-        int ci, px, py;
-        locate(a, a.ray_ids[i], ci, px, py);
         int64_t o[3];
         int32_t s[3];
         float d[3];
         ray_setup(a.cams[ci], g.N, px, py, o, s, d);
-        int4* mine = list + i * kListCap;
-        march_ray_flat(g, s_occ, o, s,
-                       [&](int64_t k, int32_t rk, const uint8_t*, const int32_t p[3], const int32_t fr[3]) {
-                           if (n < kListCap) {
-                               mine[n] = make_int4((p[0] << 16) | fr[0], (p[1] << 16) | fr[1], (p[2] << 16) | fr[2], rk);
-                               kl = k;
-                           }
-                           ++n;
-                           return false;
-                       });
+        live = w.init(g, o, s, l);
     }
-    count[i] = n;
-    klast[i] = kl;
-}
-
-template <bool FEAT, bool LOG>
-__global__ __launch_bounds__(64 * kAggWaves) void k_backward_from_list(BackwardArgs a, const int4* __restrict__ list,
-                                                                       const int32_t* __restrict__ count,
-                                                                       const int64_t* __restrict__ klast) {
-    extern __shared__ uint2 s_occ[];
-    const GridArgs& g = a.grid;
-    for (int w = threadIdx.x; w < g.n_words; w += blockDim.x) s_occ[w] = g.occ[w];
-    const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
-    AggTable tab = agg_table(s_occ, g.n_words, wave, lane, true);
+    // its output gradient and what the forward saved
+    float4 a0 = make_float4(0.f, 0.f, 0.f, 0.f), a1 = make_float4(0.f, 0.f, 0.f, -1.f);
+    float4 gg = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (live) {
+        a1 = reinterpret_cast<const float4*>(a.aux)[2 * i + 1];
+        live = a1.w >= 0.0f;  // nothing was composited: no grid gradient
+    }
+    float gC[3] = {0.f, 0.f, 0.f}, gV[4] = {0.f, 0.f, 0.f, 0.f};
+    if (live) {
+        a0 = reinterpret_cast<const float4*>(a.aux)[2 * i];
+        gg = reinterpret_cast<const float4*>(a.grad_rgba)[i];
+        gC[0] = gg.x; gC[1] = gg.y; gC[2] = gg.z;
+        if (FEAT) {
+            const float4 c0 = reinterpret_cast<const float4*>(a.gcv)[2 * i];
+            const float4 c1 = reinterpret_cast<const float4*>(a.gcv)[2 * i + 1];
+            gC[0] = c0.x; gC[1] = c0.y; gC[2] = c0.z;
+            gV[0] = c0.w; gV[1] = c1.x; gV[2] = c1.y; gV[3] = c1.z;
+        }
+    }
+    const float E = gC[0] * a0.x + gC[1] * a0.y + gC[2] * a0.z +
+                    (gV[0] * a0.w + gV[1] * a1.x + gV[2] * a1.y + gV[3] * a1.z);
+    const float gTN = gg.x * a.opts.bg[0] + gg.y * a.opts.bg[1] + gg.z * a.opts.bg[2] - gg.w;
+    const float tail = a1.w * gTN;  // T_N dL/dT_N
+    const float inv_g = 1.0f / float(g.G);
+    const float delta = 1.0f / float(g.N), kx = g.sigma_scale * delta;
+    // Where the forward ended the ray early, at the sample that left it its
+    // T_N < t_stop, the re-march ends there too: T is recomputed here with
+    // other roundings (a few 2^-22), so it ends when T has come down to T_N,
+    // give or take 2^-16, or is that clearly past the threshold.
+    const float t_end = a.opts.early_stop && a1.w < a.opts.t_stop
+                            ? fmaxf(a1.w * (1.0f + 0x1p-16f), a.opts.t_stop * (1.0f - 0x1p-16f))
+                            : -1.0f;
+    // direct atomics: this lane's channel and its gradient
+    float gch = 0.0f;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) gch = l == 1 + c ? gC[c] : gch;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) gch = l == 4 + c ? gV[c] : gch;
+    if (!AGG) s_gch[wave][lane >> 3][l] = gch;
     __syncthreads();
-    // a.list_rpw rays per wavefront (lanes past them idle)
-    const int64_t i = (int64_t(blockIdx.x) * kAggWaves + wave) * a.list_rpw + lane;
-    bool live = lane < a.list_rpw && i < a.n_rays;
-    AdjointRay<FEAT, true, LOG> st;
-    live = st.setup(a, i, live);
-    if (!LOG) st.table_scale(tab);
-    const int32_t total = live ? count[i] : 0;
-    const int32_t n = total < kListCap ? total : kListCap;
-    const int4* mine = list + i * kListCap;
-    TableSync sync;
-    int n_log = 0;  // LOG: entries in the log, the same in every lane
-    bool going = live;
-    // Software pipeline (at these sizes one wavefront per SIMD, so nothing
-    // else hides a step's loads): list entries are read two steps ahead and
-    // the next sample's corners are loaded before the current sample's
-    // gradient work, in two corner buffers with the loop unrolled by two so
-    // that neither is copied.
-    const int4 none = make_int4(0, 0, 0, 0);
-    int4 e0 = n > 0 ? mine[0] : none;
-    int4 e1 = n > 1 ? mine[1] : none;
-    CornersF32 cb[2];
-    auto load = [&](const int4& e, CornersF32& cn) {
-        const int32_t p[3] = {e.x >> 16, e.y >> 16, e.z >> 16};
-        load_corners_f32(g.rec + int64_t(e.w) * g.rec_stride + g.dist_bytes, g.Bp, p, cn);
-    };
-    if (n > 0) load(e0, cb[0]);
-    auto step = [&](int32_t j, const int4& e, const CornersF32& cn) {
-        if (going && j < n) {
-            const int32_t p[3] = {e.x >> 16, e.y >> 16, e.z >> 16};
-            const int32_t fr[3] = {e.x & 0xFFFF, e.y & 0xFFFF, e.z & 0xFFFF};
-            Sample smp;
-            interp_f32(cn, fr, smp, st.nn_gate);
-            if (st.take(a, tab, e.w, smp, p, fr)) going = false;
+    if (AGG) agg_scale(tab, s_max);
+
+    const uint32_t nb = uint32_t(g.Bp), nbb = nb * nb;
+    const uint32_t nc = uint32_t(g.Bc), ncc = nc * nc;
+    const uint32_t corner = (uint32_t(cz) * nbb + uint32_t(cy) * nb + uint32_t(cx)) * 32u;
+    // weight of the corner on an axis: f = |0 - f| or 1 - f
+    const float ox = cx ? 0.0f : 1.0f, oy = cy ? 0.0f : 1.0f, oz = cz ? 0.0f : 1.0f;
+
+    float T = 1.0f, rest = E + tail;  // rest: E - P_k + T_N dL/dT_N
+    float A = 0.0f, D = 0.0f;         // this corner's sums
+    int32_t wc = 0;                      // the window's cell, own axis
+    int32_t wrank = -1, wid = 0, wb = 0;  // its block's record, atlas id, coordinates (8 bits each)
+    int32_t nb_lin = -1, nb_id = -1;
+    int fresh = 0;
+    int32_t* iv = reinterpret_cast<int32_t*>(tab.val);
+
+    int4 out = make_int4(0, -1, 0, 0);  // without the table: what this lane hands over, out.y < 0: nothing
+
+    // Hands this corner's sums over where `leave` is set (the same decision
+    // rule in all lanes of the ray, not the same answer).
+    auto hand_over = [&](bool leave) {
+        const int vx = dpp<kAxisX>(wc) + cx - 1, vy = dpp<kAxisY>(wc) + cy - 1, vz = dpp<kAxisZ>(wc) + cz - 1;
+        using Index = typename std::conditional<AGG, int32_t, int64_t>::type;  // the table's keys are int32
+        Index vi = -1;
+        if (leave && (A != 0.0f || D != 0.0f))
+            vi = canonical_voxel<Index>(g, wid, wb, vx, vy, vz, nb_lin, nb_id);
+        const float Ds = g.sigma_scale * D;
+        if (AGG && vi >= 0) {
+            const int sl = agg_slot(tab, vi, fresh);
+            if (sl >= 0) {
+                vi = -1;
+                atomicAdd(tab.val + sl, Ds);
+                const float Aq = A * tab.q;  // a power of two: exact, so the products round as A g would
+#pragma unroll
+                for (int c = 0; c < 3; ++c)
+                    atomicAdd(iv + (1 + c) * kAggSlots + sl, int32_t(__builtin_rintf(Aq * gC[c])));
+                if (FEAT) {
+#pragma unroll
+                    for (int c = 0; c < 4; ++c)
+                        atomicAdd(iv + (4 + c) * kAggSlots + sl, int32_t(__builtin_rintf(Aq * gV[c])));
+                }
+            }
         }
-        if (LOG) st.template commit<FEAT>(a, tab, lane, n_log);
-        else sync.step<FEAT>(a, tab, lane, st.fresh);
-    };
-    for (int32_t j = 0; __any(going && j < n); j += 2) {
-        if (going && j + 1 < n) load(e1, cb[1]);
-        const int4 e2 = going && j + 2 < n ? mine[j + 2] : none;
-        step(j, e0, cb[0]);
-        if (!__any(going && j + 1 < n)) break;
-        if (going && j + 2 < n) load(e2, cb[0]);
-        const int4 e3 = going && j + 3 < n ? mine[j + 3] : none;
-        step(j + 1, e1, cb[1]);
-        e0 = e2;
-        e1 = e3;
-    }
-    // past the list: walk from the start and take the samples after the last listed one
-    const bool more = going && total > kListCap;
-    if (__any(more)) {
-        int64_t o[3] = {0, 0, 0};
-        int32_t s[3] = {0, 0, 1 << 15};
-        const int64_t k_listed = more ? klast[i] : 0;
-        if (more) {
-            int ci, px, py;
-            locate(a, a.ray_ids[i], ci, px, py);
-            float d[3];
-            ray_setup(a.cams[ci], g.N, px, py, o, s, d);
+        if (AGG) {  // no slot free: the ray's 8 lanes add a corner's 8 channels
+            for (uint32_t m = ray_bits(vi >= 0, lane); m != 0; m &= m - 1) {
+                const int from = (lane & ~7) | __builtin_ctz(m);
+                const Index v = __shfl(vi, from);
+                const float dv = __shfl(Ds, from), av = __shfl(A, from);
+                const float x = l == 0 ? dv : av * gch;
+                if (x != 0.0f) unsafeAtomicAdd(grad_channel(a, v, l), x);
+            }
+        } else {
+            out = make_int4(int32_t(uint32_t(uint64_t(vi))), int32_t(vi >> 32), __float_as_int(A), __float_as_int(Ds));
         }
-        march_ray_flat_sync(
-            g, s_occ, more, o, s,
-            [&](int64_t k, int32_t rk, const uint8_t* vox, const int32_t p[3], const int32_t fr[3]) {
-                return k > k_listed && st.sample(a, tab, rk, vox, p, fr);
-            },
-            [&]() {
-                if (LOG) st.template commit<FEAT>(a, tab, lane, n_log);
-                else sync.step<FEAT>(a, tab, lane, st.fresh);
-                return false;
-            });
+    };
+
+    // Without the table: what the lanes hand over in a step goes, at the next
+    // point where all 64 are together, to the wavefront's log (voxel, ray, A,
+    // density sum), each to the place a ballot gives it, so the fill count is
+    // the same in every lane.  A full log goes to device memory, 8 entries to
+    // an instruction, the lanes of one across the voxel's channels.  Added
+    // straight away, every atomic would stand in front of the next step's
+    // loads, which wait for it (vector memory retires in order).
+    int n_log = 0;
+    auto log_flush = [&]() {
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        for (int e = lane >> 3; e < n_log; e += 8) {
+            const int4 h = log[e];
+            const int64_t v = int64_t(uint64_t(uint32_t(h.x)) | (uint64_t(uint32_t(h.y & 0xffffff)) << 32));
+            const float x = l == 0 ? __int_as_float(h.w) : __int_as_float(h.z) * s_gch[wave][h.y >> 24][l];
+            if (x != 0.0f) unsafeAtomicAdd(grad_channel(a, v, l), x);
+        }
+        n_log = 0;
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    };
+    auto log_append = [&]() {
+        const bool want = out.y >= 0;
+        const uint64_t m = __ballot(want);
+        if (m == 0) return;  // wave-uniform
+        if (n_log > kLogEntries - 64) log_flush();
+        if (want) {
+            out.y |= (lane >> 3) << 24;
+            log[n_log + int(__builtin_amdgcn_mbcnt_hi(uint32_t(m >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(m), 0u)))] =
+                out;
+        }
+        n_log += __builtin_popcountll(m);
+        out.y = -1;
+    };
+
+    int in_table = 0, phase = 0;  // AGG: keys in the table, the same in every lane of the workgroup
+    for (int trip = 0;; ++trip) {
+        if (AGG) {
+            if (trip % kAggTrips == 0) {
+                // Slot `phase` collects this phase's counts before the barrier
+                // and is read after it; the slot of the phase after next was
+                // last read before this barrier, and is cleared for it.
+                int f = fresh;
+#pragma unroll
+                for (int sh = 32; sh >= 1; sh >>= 1) f += __shfl_xor(f, sh);
+                const bool some = __any(live);
+                if (lane == 0 && f != 0) atomicAdd(&s_fresh[phase], f);
+                if (lane == 0 && some) s_live[phase] = 1;
+                fresh = 0;
+                __syncthreads();
+                in_table += s_fresh[phase];
+                const bool on = s_live[phase] != 0;
+                const int clear = phase == 0 ? 2 : phase - 1;
+                if (threadIdx.x == 0) s_fresh[clear] = s_live[clear] = 0;
+                phase = phase == 2 ? 0 : phase + 1;
+                if (!on || in_table > kAggFlushAt) {
+                    if (!on) {  // the last windows
+                        hand_over(wrank >= 0);
+                        __syncthreads();
+                    }
+                    agg_flush<FEAT>(a, tab);
+                    if (!on) break;
+                    in_table = 0;
+                    __syncthreads();
+                }
+            }
+        } else if (!__any(live)) {
+            break;
+        }
+        uint32_t todo = 0;
+        int32_t reach = 0;
+        if (live) {
+            while (live && w.left <= 0) live = w.enter(g, s_occ);
+        }
+        if (live) {
+            bool act = false;
+            const int32_t p[3] = {(dpp<kAxisX>(w.q) + mul_s24(l, dpp<kAxisX>(w.s))) >> 16,
+                                  (dpp<kAxisY>(w.q) + mul_s24(l, dpp<kAxisY>(w.s))) >> 16,
+                                  (dpp<kAxisZ>(w.q) + mul_s24(l, dpp<kAxisZ>(w.s))) >> 16};
+            if (l < w.left) {
+                const int32_t db = w.dist[cell_index(p, nc, ncc)];
+                act = db == 0;
+                reach = l + (act ? 1 : skip_steps(db, w.smax, w.inv_smax));
+            }
+            todo = ray_bits(act, lane);
+            reach = max(reach, dpp<kFlipX>(reach));
+            reach = max(reach, dpp<kFlipY>(reach));
+            reach = max(reach, dpp<kFlipZ>(reach));
+            reach = min(reach, w.left);
+        }
+        // Reads this corner's voxel of the ray's next active sample.
+        auto fetch = [&](int32_t& own, float4& va, float4& vb) {
+            own = w.q + mul_s24(__builtin_ctz(todo), w.s);
+            todo &= todo - 1;
+            const int32_t p[3] = {dpp<kAxisX>(own) >> 16, dpp<kAxisY>(own) >> 16, dpp<kAxisZ>(own) >> 16};
+            const uint8_t* at = w.dist + g.dist_bytes + (uint64_t(cell_index(p, nb, nbb)) * 32u + corner);
+            va = reinterpret_cast<const float4*>(at)[0];
+            if (FEAT) vb = reinterpret_cast<const float4*>(at)[1];
+        };
+        auto take = [&](int32_t own, const float4& va, const float4& vb) {
+            const int32_t q[3] = {dpp<kAxisX>(own), dpp<kAxisY>(own), dpp<kAxisZ>(own)};
+            const float fx = float(q[0] & 0xFFFF) * (1.0f / 65536.0f);
+            const float fy = float(q[1] & 0xFFFF) * (1.0f / 65536.0f);
+            const float fz = float(q[2] & 0xFFFF) * (1.0f / 65536.0f);
+            const float wt = (fabsf(ox - fx) * fabsf(oy - fy)) * fabsf(oz - fz);
+            // The exact active test: some corner of non-zero weight (every
+            // product of non-zero fractions is at least 2^-48) has non-zero
+            // density; or, the viewer's gate, the nearest corner has.
+            bool dense = va.x != 0.0f && wt != 0.0f;
+            if (a.opts.nn_gate)
+                dense = va.x != 0.0f && cx == ((q[0] >> 15) & 1) && cy == ((q[1] >> 15) & 1) && cz == ((q[2] >> 15) & 1);
+            float ev = gC[0] * va.y + gC[1] * va.z + gC[2] * va.w;
+            if (FEAT) ev += gV[0] * vb.x + gV[1] * vb.y + gV[2] * vb.z + gV[3] * vb.w;
+            const float sigma = corner_sum(wt * va.x);
+            const float ek = corner_sum(wt * ev);
+            if (ray_bits(dense, lane) == 0) return;
+            const float e = __expf(-sigma * kx);
+            const float ws = T * (1.0f - e);
+            rest -= ws * ek;
+            T *= e;
+            const float gsig = delta * (T * ek - rest);
+            // Slide the corner window to this sample's cell: corners on a
+            // trailing face (or all of them after a jump) are handed over, the
+            // survivors move to their new lane.
+            const int32_t move = (own >> 16) - wc;
+            const int32_t dd[3] = {dpp<kAxisX>(move), dpp<kAxisY>(move), dpp<kAxisZ>(move)};
+            const bool jump = wrank != w.r || ray_bits(abs(move) > 1, lane) != 0;
+            // the corner leaves on an axis the window moves along if it is on the trailing side
+            const bool lx = dd[0] != 0 && (dd[0] > 0) == (cx == 0);
+            const bool ly = dd[1] != 0 && (dd[1] > 0) == (cy == 0);
+            const bool lz = dd[2] != 0 && (dd[2] > 0) == (cz == 0);
+            hand_over(jump ? wrank >= 0 : lx || ly || lz);
+            if (jump) {
+                A = D = 0.0f;
+                wrank = w.r;
+                wid = g.rank_id[w.r];
+                const int32_t lin = g.rank_lin[w.r];
+                // lin < 2^18: the rounded product is never a half away from the quotient
+                const int32_t yz = int32_t((float(lin) + 0.5f) * inv_g), z = int32_t((float(yz) + 0.5f) * inv_g);
+                wb = (lin - mul_s24(yz, g.G)) | (yz - mul_s24(z, g.G)) << 8 | z << 16;
+            } else {
+                // a trailing corner takes its leading neighbour's sums, which start anew
+                float An = dpp<kFlipX>(A), Dn = dpp<kFlipX>(D);
+                A = dd[0] == 0 ? A : (lx ? An : 0.0f);
+                D = dd[0] == 0 ? D : (lx ? Dn : 0.0f);
+                An = dpp<kFlipY>(A), Dn = dpp<kFlipY>(D);
+                A = dd[1] == 0 ? A : (ly ? An : 0.0f);
+                D = dd[1] == 0 ? D : (ly ? Dn : 0.0f);
+                An = dpp<kFlipZ>(A), Dn = dpp<kFlipZ>(D);
+                A = dd[2] == 0 ? A : (lz ? An : 0.0f);
+                D = dd[2] == 0 ? D : (lz ? Dn : 0.0f);
+            }
+            wc += move;
+            A = fmaf(wt, ws, A);
+            D = fmaf(wt, gsig, D);
+            if (T <= t_end) live = false;
+        };
+        int32_t own = 0;
+        float4 va = make_float4(0.f, 0.f, 0.f, 0.f), vb = va;
+        if (AGG) {
+            while (todo != 0) {
+                fetch(own, va, vb);
+                take(own, va, vb);
+                if (!live) todo = 0;
+            }
+        } else {
+            // the next sample's voxels are read before the current one's work
+            bool more = todo != 0;
+            if (more) fetch(own, va, vb);
+            while (__any(more)) {
+                if (more) {
+                    const int32_t o1 = own;
+                    const float4 a1v = va, b1v = vb;
+                    more = todo != 0;
+                    if (more) fetch(own, va, vb);
+                    take(o1, a1v, b1v);
+                    if (!live) {
+                        todo = 0;
+                        more = false;
+                    }
+                }
+                log_append();
+            }
+        }
+        if (live) {
+            w.left -= reach;
+            w.q += mul_s24(reach, w.s);
+        }
     }
-    st.finish(a, tab);
-    if (LOG) {
-        st.template commit<FEAT>(a, tab, lane, n_log);
-        log_flush<FEAT>(a, tab, lane, n_log);
-    } else {
-        agg_flush<FEAT>(a, tab, lane);
+    if (!AGG) {
+        hand_over(wrank >= 0);
+        log_append();
+        log_flush();
     }
 }
 
@@ -1062,6 +978,9 @@ __global__ __launch_bounds__(256) void k_reduce_rows(const float* __restrict__ p
     if (ty == 0 && col < kMlpParams) atomicAdd(out + col, (part[0][tx] + part[1][tx]) + (part[2][tx] + part[3][tx]));
 }
 
+// The longest list that is taken to be scattered.
+constexpr int64_t kScatteredMaxRays = int64_t(1) << 18;
+
 int backward_partial_rows(int n_groups) { return n_groups * kBwdWaves; }
 
 bool backward_aggregates(const GridArgs& g) {
@@ -1079,52 +998,29 @@ hipError_t launch_backward(const BackwardArgs& a, int n_groups, hipStream_t s) {
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     if (a.mlp_only) return hipSuccess;
-    // aggregation keys are int32 voxel indices
-    const int64_t n_vox = int64_t(a.grid.n_blocks) * a.grid.B * a.grid.B * a.grid.B;
-    const bool agg = backward_aggregates(a.grid);
-    const size_t lds = size_t(a.grid.n_words) * sizeof(uint2) + (agg ? size_t(kAggLdsWords) * 4 : 0);
-    const int64_t waves = a.ray_ids ? (a.n_rays + 63) / 64 : a.total_tiles;
-    const unsigned blocks = unsigned((waves + kAggWaves - 1) / kAggWaves);
+    // Neighbouring rays share voxels and go through the table (half a tile to
+    // a workgroup): whole views, patch lists, and lists so long that most of
+    // the pixels must be in them.  Scattered rays share few and go through
+    // the log, as do grids whose voxel indices exceed the table's int32 keys.
+    const bool agg = backward_aggregates(a.grid) && (!a.ray_ids || a.patch_rays || a.n_rays > kScatteredMaxRays);
     const bool feat = a.mlp_mode != kMlpOff;
-    (void)n_vox;
-    if (a.list) {  // short ray list: record, then the gradient from the lists
-        // A scattered list of up to 2^16 rays fills at most one wavefront
-        // per SIMD at 64 rays each, and a lone wavefront waits on its own
-        // latencies: with 32 rays (up to 2^16) or 16 (up to 2^15), the other
-        // lanes idle, two or more share each SIMD.  Patch lists keep 64, the
-        // 8x8 patches whose voxels the table sums.
-        BackwardArgs b = a;
-        b.list_rpw = a.patch_rays ? 64 : (a.n_rays <= (int64_t(1) << 15) ? 16 : (a.n_rays <= (int64_t(1) << 16) ? 32 : 64));
-        const unsigned lblocks = unsigned(((a.n_rays + b.list_rpw - 1) / b.list_rpw + kAggWaves - 1) / kAggWaves);
-        const size_t occ = size_t(a.grid.n_words) * sizeof(uint2);
-        const unsigned rblocks = unsigned(((a.n_rays + b.list_rpw - 1) / b.list_rpw + 3) / 4);
-        hipLaunchKernelGGL(k_backward_record, dim3(rblocks), dim3(256), occ, s, b, b.list, b.list_count,
-                           b.list_klast);
+    static_assert(kAdjWaves * 8 == 32, "two workgroups to 64 rays");
+    const int64_t wgs = 2 * (a.ray_ids ? (a.n_rays + 63) / 64 : a.total_tiles);
+    const dim3 wg{64 * kAdjWaves};
+    const size_t lds = (size_t(a.grid.n_words) + 1) / 2 * 16 +
+                       (agg ? size_t(kAggWords) * 4 : size_t(kAdjWaves) * kLogEntries * sizeof(int4));
+    // a launch holds fewer than 2^32 lanes
+    constexpr int64_t kMaxGroups = int64_t(1) << 22;
+    BackwardArgs b = a;
+    for (b.first_group = 0; b.first_group < wgs; b.first_group += kMaxGroups) {
+        const dim3 grid{unsigned(wgs - b.first_group < kMaxGroups ? wgs - b.first_group : kMaxGroups)};
+        if (feat && agg) hipLaunchKernelGGL((k_adjoint<true, true>), grid, wg, lds, s, b);
+        else if (feat) hipLaunchKernelGGL((k_adjoint<true, false>), grid, wg, lds, s, b);
+        else if (agg) hipLaunchKernelGGL((k_adjoint<false, true>), grid, wg, lds, s, b);
+        else hipLaunchKernelGGL((k_adjoint<false, false>), grid, wg, lds, s, b);
         if ((e = hipGetLastError()) != hipSuccess) return e;
-        // scattered rays share few voxels: the log; patches: the aggregating table
-        if (feat && a.patch_rays)
-            hipLaunchKernelGGL((k_backward_from_list<true, false>), dim3(lblocks), dim3(64 * kAggWaves), lds, s, b,
-                               b.list, b.list_count, b.list_klast);
-        else if (feat)
-            hipLaunchKernelGGL((k_backward_from_list<true, true>), dim3(lblocks), dim3(64 * kAggWaves), lds, s, b,
-                               b.list, b.list_count, b.list_klast);
-        else if (a.patch_rays)
-            hipLaunchKernelGGL((k_backward_from_list<false, false>), dim3(lblocks), dim3(64 * kAggWaves), lds, s, b,
-                               b.list, b.list_count, b.list_klast);
-        else
-            hipLaunchKernelGGL((k_backward_from_list<false, true>), dim3(lblocks), dim3(64 * kAggWaves), lds, s, b,
-                               b.list, b.list_count, b.list_klast);
-        return hipGetLastError();
     }
-    if (feat && agg)
-        hipLaunchKernelGGL((k_march_backward<true, true>), dim3(blocks), dim3(64 * kAggWaves), lds, s, a);
-    else if (feat)
-        hipLaunchKernelGGL((k_march_backward<true, false>), dim3(blocks), dim3(64 * kAggWaves), lds, s, a);
-    else if (agg)
-        hipLaunchKernelGGL((k_march_backward<false, true>), dim3(blocks), dim3(64 * kAggWaves), lds, s, a);
-    else
-        hipLaunchKernelGGL((k_march_backward<false, false>), dim3(blocks), dim3(64 * kAggWaves), lds, s, a);
-    return hipGetLastError();
+    return hipSuccess;
 }
 
 hipError_t launch_reduce_mlp(const float* partial, int rows, float* out, hipStream_t s) {

@@ -589,7 +589,8 @@ RenderSplit render_split(const RenderArgs& a, bool f32, bool f16) {
     if (a.n_rays <= (int64_t(1) << 16)) return {4, 0};
     if (a.n_rays <= (int64_t(3) << 17)) return {4, 1};
     if (f32 && list && a.n_rays <= (int64_t(1) << 20)) return {4, 1};
-    if (f32 && (!f16 || a.n_rays <= (int64_t(6) << 20))) return {2, 1};
+    // (a launch holds fewer than 2^32 lanes)
+    if (f32 && a.n_rays <= (f16 ? int64_t(6) << 20 : int64_t(1) << 30)) return {2, 1};
     return {1, 1};
 }
 

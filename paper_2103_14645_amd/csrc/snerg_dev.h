@@ -223,12 +223,13 @@ __host__ __device__ __forceinline__ int32_t block_steps(const int32_t P[3], cons
 // Workgroup w of a launch of n goes to XCD w mod 8 (each of the eight XCDs
 // has its own L2), so consecutive workgroups of a tile order, which render
 // neighbouring tiles and read the same macroblocks, would land in eight
-// different L2s.  This permutation of [0, n) gives each XCD runs of 8
+// different L2s.  This permutation of [0, n) gives each XCD runs of kRun
 // consecutive workgroups while the XCDs still advance through the order
-// together; the last n mod 64 stay in place.  Only the speed depends on the
-// dispatch order, never the result.
+// together; the last n mod 8 kRun stay in place.  Only the speed depends on
+// the dispatch order, never the result.
+template <uint32_t kRun = 8>
 __device__ __forceinline__ uint32_t xcd_grouped(uint32_t w, uint32_t n) {
-    constexpr uint32_t kRun = 8, kChunk = 8 * kRun;
+    constexpr uint32_t kChunk = 8 * kRun;
     if (w >= n / kChunk * kChunk) return w;
     const uint32_t r = w % kChunk;
     return w - r + (r % 8) * kRun + r / 8;

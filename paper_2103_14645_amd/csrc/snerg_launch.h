@@ -68,18 +68,8 @@ struct BackwardArgs {
     int32_t mlp_only;      // MLP gradient only: no re-march
     int32_t patch_rays;    // ray list in groups of 64 neighbouring rays
     int32_t grad_packed;   // grid gradients as grad_dens[voxel][8] (grad_rgb, grad_feat unused)
-    int32_t list_rpw;      // set by the launch: rays per wavefront of the list gradient pass
-    // short ray lists, two phases (null: one re-march): per list entry
-    // kBackwardListCap listed samples, the count and the last listed k
-    int4* list;
-    int32_t* list_count;
-    int64_t* list_klast;
+    int64_t first_group;   // set by the launch: workgroup index of the launch's first
 };
-
-// The two-phase backward serves ray lists of at most kBackwardListMaxRays
-// rays (few wavefronts, so the slowest one sets the time).
-constexpr int kBackwardListCap = 512;
-constexpr int64_t kBackwardListMaxRays = int64_t(1) << 18;
 
 // Baking (Section 5.3, 5.4).
 struct BakeCullPlan {

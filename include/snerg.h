@@ -239,7 +239,9 @@ int snerg_render(snerg_handle *h, const snerg_grid *grid, const float *mlp, cons
  * with SNERG_FLAG_PATCH_RAYS and lists of more than 2^18 rays) the colour and
  * feature sums are 32-bit fixed point, each hand-over rounded to within 2^-24
  * of the largest |dL/dC_d|, |dL/dV| of the tile's (or 64 list entries') rays.
- * With SNERG_FLAG_MLP_FP16 the MLP
+ * A ray list of at most 2^18 rays runs in two phases whose per-ray sample lists
+ * (up to 8 KB per ray) live in handle-owned device memory, kept for later
+ * calls.  With SNERG_FLAG_MLP_FP16 the MLP
  * backward runs on FP16 MFMA tiles with FP32 accumulation (as the forward).
  * With SNERG_FLAG_MLP_GRAD_ONLY only grad_mlp is computed (the fine-tuning
  * of Section 5.5 optimises the deferred network alone): no ray is

@@ -6,8 +6,7 @@
 //     ray; the weight gradients of the wavefront's 64 rays are summed with
 //     FP32 MFMA outer products (rays are the K dimension) into per-wavefront
 //     partial rows, reduced afterwards.
-//  K2 (k_adjoint): re-march the same samples (nothing per sample was
-//     stored).  With E = g_C . C_d + g_V . V (from the forward's saved C_d,
+//  K2: re-march the same samples (nothing per sample was stored).  With E = g_C . C_d + g_V . V (from the forward's saved C_d,
 //     V), the running prefix P_k = sum_{j<=k} w_j e_j, e_k = g_C . c_k +
 //     g_V . v_k and dL/dT_N = g_rgb . bg - g_alpha, Eq. 2/5/6 give
 //        dL/dsigma_k = delta [T_k e_k - (E - P_k) - T_N dL/dT_N],
@@ -18,9 +17,10 @@
 //     each cell coordinate is monotone, so the 8 corners of the current cell
 //     are kept as running (A, D) sums and a voxel is handed over once, when
 //     the ray's cell window leaves it: into an LDS table that sums the
-//     hand-overs of 32 neighbouring rays (whole views in 64-pixel tiles,
-//     patch lists, long lists) or an LDS log (scattered lists), either way
-//     flushed to the gradient arrays with float atomics grouped by cache line.
+//     hand-overs of neighbouring rays (whole views, patch lists, long lists)
+//     or an LDS log (scattered lists), either way flushed to the gradient
+//     arrays with float atomics grouped by cache line.  launch_backward says
+//     which of the kernels below runs when.
 #include <type_traits>
 
 #include "march.h"
@@ -46,6 +46,12 @@ __device__ __forceinline__ float wave_max(float v) {
 #pragma unroll
     for (int m = 32; m >= 1; m >>= 1) v = fmaxf(v, __shfl_xor(v, m));
     return v;
+}
+
+// Between LDS accesses of different lanes of one wavefront.
+__device__ __forceinline__ void sync_wave() {
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
 }
 
 __device__ __forceinline__ void locate(const BackwardArgs& a, int64_t r, int& ci, int& px, int& py) {
@@ -366,12 +372,20 @@ __device__ __forceinline__ I canonical_voxel(const GridArgs& g, int32_t id, int3
     return (((((I(tid) << g.logB) | vz) << g.logB) | vy) << g.logB) | vx;
 }
 
+// Coordinates x | y << 8 | z << 16 of macroblock lin (< 2^18: the rounded
+// product is never a half away from the quotient).
+__device__ __forceinline__ int32_t block_coords(const GridArgs& g, int32_t lin) {
+    const float inv_g = 1.0f / float(g.G);
+    const int32_t yz = int32_t((float(lin) + 0.5f) * inv_g), z = int32_t((float(yz) + 0.5f) * inv_g);
+    return (lin - mul_s24(yz, g.G)) | (yz - mul_s24(z, g.G)) << 8 | z << 16;
+}
+
 // Gradient aggregation in LDS.  Neighbouring rays share most of the voxels
 // they touch, so each voxel's eight gradient values (density, RGB, features)
-// are first summed in an open-addressed table of kAggSlots entries, one per
-// workgroup, and reach device memory with one set of atomics per table flush
-// instead of one per ray.  Keys are canonical voxel indices (< 2^31; the
-// launch takes the log otherwise).
+// are first summed in an open-addressed table of kAggSlots entries and reach
+// device memory with one set of atomics per table flush instead of one per
+// ray.  Keys are canonical voxel indices (< 2^31; the launch falls back to
+// direct atomics otherwise).
 //
 // The colour and feature sums are kept in 32-bit fixed point: on gfx950 an
 // LDS float add (ds_add_f32) retires about one lane every three cycles, an
@@ -379,25 +393,23 @@ __device__ __forceinline__ I canonical_voxel(const GridArgs& g, int32_t id, int3
 // voxel its colour gradient A g_C with A = sum_k w_c(k) w_k, and the A of all
 // of a ray's hand-overs add up to at most sum_k w_k <= 1, so with M = max over
 // the rays of the tile, or of 64 list entries, of |g_C|, |g_V| all that one ray
-// hands to one voxel is at most M and a table entry (32 rays between flushes)
-// at most 32 M.  Values are scaled by 2^S, the largest power of two with M 2^S < 2^24,
-// and rounded to integers: an entry stays below 2^29 (plus its rounding),
-// and each hand-over carries a rounding error of at most 2^-24 M.  The
-// density sums, whose size depends on the grid values, stay in float.
-constexpr int kAdjWaves = 4;  // wavefronts per workgroup: 32 rays, 8 lanes each
+// hands to one voxel is at most M and a table entry (64 rays between flushes)
+// at most 64 M.  Values are scaled by 2^S, the largest power of two with
+// M 2^S < 2^24, and rounded to integers: an entry stays below 2^30 (plus its
+// rounding), and each hand-over carries a rounding error of at most 2^-24 M.
+// The density sums, whose size depends on the grid values, stay in float.
 constexpr int kAggLog = 9;
 constexpr int kAggSlots = 1 << kAggLog;
 constexpr int kAggProbes = 16;
 constexpr int kAggWords = kAggSlots * 9;  // keys, 8 value planes
-// The workgroup looks at the table every kAggTrips trips of its rays and
-// flushes it when it holds more than kAggFlushAt keys; what its rays add in
-// four trips (up to 32 samples each) mostly fits above that, and a key that
-// finds no free slot within kAggProbes probes goes to device memory directly.
-constexpr int kAggFlushAt = kAggSlots * 9 / 16;
-constexpr int kAggTrips = 4;
-
-// The log of a wavefront whose rays share few voxels, in 16-byte entries.
-constexpr int kLogEntries = 320;
+// A wavefront's own table is flushed once this many keys are in.  Every flush
+// sends each held voxel's eight sums to device memory as float atomics, which
+// gfx950 executes at the memory side, about 21 G cache lines per second, so
+// the fewer flushes the better: at 7/8 full the adjoint frame ran 18% faster
+// than at 1/2 (the table then holds most of a tile's voxels at once); a key
+// that finds no free slot within kAggProbes probes goes to device memory
+// directly.
+constexpr int kAggFlushAt = kAggSlots * 7 / 8;
 
 struct AggTable {
     int32_t* key;  // [kAggSlots], -1 = free
@@ -424,13 +436,15 @@ __device__ __forceinline__ float* grad_channel(const BackwardArgs& a, int64_t vi
     return c == 0 ? a.grad_dens + vi : (c < 4 ? a.grad_rgb + 3 * vi + (c - 1) : a.grad_feat + 4 * vi + (c - 4));
 }
 
-// The table slot of `key` (lanes may diverge), claimed if it has none; -1
-// when no slot was found within kAggProbes probes.  `fresh` counts the lane's
-// new keys.
-__device__ __forceinline__ int agg_slot(const AggTable& t, int32_t key, int& fresh) {
-    uint32_t sl = (uint32_t(key) * 2654435761u) >> (32 - kAggLog);
+// The first of the kAggProbes consecutive slots in which `key` may be.
+__device__ __forceinline__ uint32_t agg_hash(int32_t key) { return (uint32_t(key) * 2654435761u) >> (32 - kAggLog); }
+
+// The table slot of `key` among `probes` from `sl` on (lanes may diverge),
+// claimed if it has none; -1 when there is none free.  `fresh` counts the
+// lane's new keys.
+__device__ __forceinline__ int agg_slot(const AggTable& t, uint32_t sl, int probes, int32_t key, int& fresh) {
 #pragma nounroll
-    for (int pr = 0; pr < kAggProbes; ++pr) {
+    for (; probes > 0; --probes) {
         // one round trip per probe: the compare-and-swap claims a free slot
         // and otherwise returns the key that holds it
         const int32_t k = atomicCAS(t.key + sl, -1, key);
@@ -441,8 +455,37 @@ __device__ __forceinline__ int agg_slot(const AggTable& t, int32_t key, int& fre
     return -1;
 }
 
-// The whole workgroup, between barriers: every used entry goes to device
-// memory, the table is cleared.  gfx950 serves a wavefront's float atomics
+// Adds a ray's hand-over to the entry at slot sl.
+template <bool FEAT>
+__device__ __forceinline__ void agg_add(const AggTable& t, int sl, float Ds, float A, const float gC[3],
+                                        const float gV[4]) {
+    int32_t* iv = reinterpret_cast<int32_t*>(t.val);
+    atomicAdd(t.val + sl, Ds);
+    const float Aq = A * t.q;  // a power of two: exact, so the products round as A g would
+#pragma unroll
+    for (int c = 0; c < 3; ++c) atomicAdd(iv + (1 + c) * kAggSlots + sl, int32_t(__builtin_rintf(Aq * gC[c])));
+    if (FEAT) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) atomicAdd(iv + (4 + c) * kAggSlots + sl, int32_t(__builtin_rintf(Aq * gV[c])));
+    }
+}
+
+// Adds a voxel's hand-over to the table (lanes may diverge), or straight to
+// device memory when it finds no slot.
+template <bool FEAT>
+__device__ __forceinline__ void agg_hand_over(const BackwardArgs& a, const AggTable& t, int32_t key, float Ds, float A,
+                                              const float gC[3], const float gV[4], int& fresh) {
+    const int sl = agg_slot(t, agg_hash(key), kAggProbes, key, fresh);
+    if (sl >= 0) {
+        agg_add<FEAT>(t, sl, Ds, A, gC, gV);
+    } else {
+        const float v[8] = {Ds, A * gC[0], A * gC[1], A * gC[2], A * gV[0], A * gV[1], A * gV[2], A * gV[3]};
+        for (int c = 0; c < (FEAT ? 8 : 4); ++c) unsafeAtomicAdd(grad_channel(a, key, c), v[c]);
+    }
+}
+
+// `threads` threads in whole wavefronts, with nobody else at the table: every
+// used entry goes to device memory, the table is cleared.  gfx950 serves a wavefront's float atomics
 // per 64-byte line (measured: about 21 G lines per second whether a line
 // carries one lane's add or sixteen), so the lanes are laid across the
 // entries' channels, not the entries: lane l takes entry l / 4 of a group of
@@ -452,7 +495,7 @@ __device__ __forceinline__ int agg_slot(const AggTable& t, int32_t key, int& fre
 // gradients an entry's eight sums share one line: eight lanes per entry (four
 // without features), one instruction per group.
 template <bool FEAT>
-__device__ __forceinline__ void agg_flush(const BackwardArgs& a, const AggTable& t) {
+__device__ __forceinline__ void agg_flush(const BackwardArgs& a, const AggTable& t, int tid, int threads) {
     int32_t* iv = reinterpret_cast<int32_t*>(t.val);
     auto take = [&](int sl, int c) {
         float v;
@@ -468,8 +511,8 @@ __device__ __forceinline__ void agg_flush(const BackwardArgs& a, const AggTable&
     // the lanes of an entry sit in one wavefront and read its key before any
     // of them frees it
     const int kC = a.grad_packed && FEAT ? 8 : 4;  // lanes per entry
-    const int c = threadIdx.x & (kC - 1);
-    for (int sl = threadIdx.x / kC; sl < kAggSlots; sl += blockDim.x / kC) {
+    const int c = tid & (kC - 1);
+    for (int sl = tid / kC; sl < kAggSlots; sl += threads / kC) {
         const int32_t key = t.key[sl];
         if (key >= 0) {
             const float v0 = take(sl, c);
@@ -482,6 +525,290 @@ __device__ __forceinline__ void agg_flush(const BackwardArgs& a, const AggTable&
         }
     }
 }
+
+// ------------------------------------------------------ one lane to a ray
+
+// Running gradient sums for the 8 corner voxels of the ray's current cell.
+struct CellWindow {
+    int32_t c[3];  // padded cell coordinates
+    int32_t rank;  // block record, -1 when empty
+    int32_t id;    // atlas id of the block
+    int32_t b;     // block coordinates, x | y << 8 | z << 16
+    float A[8], D[8];
+};
+
+__device__ __forceinline__ int wave_sum_i32(int v) {
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m);
+    return __builtin_amdgcn_readfirstlane(v);
+}
+
+template <bool FEAT>
+__device__ __forceinline__ void flush_corner(const BackwardArgs& a, const AggTable& t, const CellWindow& w, int c,
+                                             const float gC[3], const float gV[4], int& fresh, int32_t& nb_lin,
+                                             int32_t& nb_id) {
+    const float A = w.A[c], D = w.D[c];
+    if (A == 0.0f && D == 0.0f) return;
+    const int32_t vi = canonical_voxel<int32_t>(a.grid, w.id, w.b, w.c[0] + (c & 1) - 1, w.c[1] + ((c >> 1) & 1) - 1,
+                                                w.c[2] + (c >> 2) - 1, nb_lin, nb_id);
+    if (vi >= 0) agg_hand_over<FEAT>(a, t, vi, a.grid.sigma_scale * D, A, gC, gV, fresh);
+}
+
+// The adjoint state of one ray's re-march: its output gradient and the
+// forward's per-ray results (E, the T_N tail), the running transmittance T
+// and prefix P_k, and the corner window.  sample() takes the samples in
+// march order, as march_ray hands them over (inactive ones included), and
+// returns true once the early-stop rule ends the ray; finish() hands over
+// the last window.
+template <bool FEAT>
+struct AdjointRay {
+    float gC[3], gV[4];
+    float E, tail, T, Pk;
+    float delta, kx, t_stop;
+    bool early, nn_gate;
+    CellWindow win;
+    int fresh;  // this lane's new table keys since the last count
+    int32_t nb_lin, nb_id;  // the last neighbouring block looked up: linear index, atlas id
+
+    // Reads list position i's state; false when the ray composited nothing
+    // (no grid gradient) or `live` is false.
+    __device__ __forceinline__ bool setup(const BackwardArgs& a, int64_t i, bool live) {
+        float4 a0 = make_float4(0.f, 0.f, 0.f, 0.f), a1 = make_float4(0.f, 0.f, 0.f, -1.f);
+        float4 gg = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (live) {
+            a1 = reinterpret_cast<const float4*>(a.aux)[2 * i + 1];
+            live = a1.w >= 0.0f;  // nothing was composited: no grid gradient
+        }
+        gC[0] = gC[1] = gC[2] = 0.f;
+        gV[0] = gV[1] = gV[2] = gV[3] = 0.f;
+        if (live) {
+            a0 = reinterpret_cast<const float4*>(a.aux)[2 * i];
+            gg = reinterpret_cast<const float4*>(a.grad_rgba)[i];
+            gC[0] = gg.x; gC[1] = gg.y; gC[2] = gg.z;
+            if (FEAT) {
+                const float4 c0 = reinterpret_cast<const float4*>(a.gcv)[2 * i];
+                const float4 c1 = reinterpret_cast<const float4*>(a.gcv)[2 * i + 1];
+                gC[0] = c0.x; gC[1] = c0.y; gC[2] = c0.z;
+                gV[0] = c0.w; gV[1] = c1.x; gV[2] = c1.y; gV[3] = c1.z;
+            }
+        }
+        E = gC[0] * a0.x + gC[1] * a0.y + gC[2] * a0.z + (gV[0] * a0.w + gV[1] * a1.x + gV[2] * a1.y + gV[3] * a1.z);
+        const float gTN = gg.x * a.opts.bg[0] + gg.y * a.opts.bg[1] + gg.z * a.opts.bg[2] - gg.w;
+        tail = a1.w * gTN;
+        T = 1.0f;
+        Pk = 0.0f;
+        delta = 1.0f / float(a.grid.N);
+        kx = a.grid.sigma_scale * delta;
+        t_stop = a.opts.t_stop;
+        early = a.opts.early_stop != 0;
+        nn_gate = a.opts.nn_gate != 0;
+        win.rank = -1;
+        win.id = 0;
+        win.c[0] = win.c[1] = win.c[2] = 0;
+        win.b = 0;
+#pragma unroll
+        for (int c = 0; c < 8; ++c) win.A[c] = win.D[c] = 0.0f;
+        fresh = 0;
+        nb_lin = -1;
+        nb_id = -1;
+        return live;
+    }
+
+    // Wavefront-wide (all 64 lanes, the same value in each): the largest
+    // |g_C|, |g_V| sets the table's fixed-point scale.
+    __device__ __forceinline__ void table_scale(AggTable& tab) const {
+        float m = fmaxf(fmaxf(fabsf(gC[0]), fabsf(gC[1])), fmaxf(fabsf(gC[2]), fabsf(gV[0])));
+        m = fmaxf(m, fmaxf(fmaxf(fabsf(gV[1]), fabsf(gV[2])), fabsf(gV[3])));
+#pragma unroll
+        for (int sh = 32; sh >= 1; sh >>= 1) m = fmaxf(m, __shfl_xor(m, sh));
+        agg_scale(tab, m);  // the butterfly leaves the same maximum in every lane
+    }
+
+    __device__ __forceinline__ bool sample(const BackwardArgs& a, const AggTable& tab, int32_t rk, const uint8_t* vox,
+                                           const int32_t p[3], const int32_t fr[3]) {
+        Sample smp;
+        gather_f32(vox, a.grid.Bp, p, fr, smp, nn_gate);
+        const GridArgs& g = a.grid;
+        if (!smp.active) return false;
+        const float e = __expf(-smp.sigma_raw * kx);
+        const float w = T * (1.0f - e);
+        const float ek = gC[0] * smp.rgb[0] + gC[1] * smp.rgb[1] + gC[2] * smp.rgb[2] +
+                         (gV[0] * smp.feat[0] + gV[1] * smp.feat[1] + gV[2] * smp.feat[2] + gV[3] * smp.feat[3]);
+        Pk += w * ek;
+        T *= e;
+        const float gsig = delta * (T * ek - (E - Pk) - tail);
+        // Slide the corner window to this sample's cell: corners on a
+        // trailing face (or all of them after a jump) are flushed once, the
+        // survivors shift to their new corner index.
+        const bool jump = win.rank != rk || abs(p[0] - win.c[0]) > 1 || abs(p[1] - win.c[1]) > 1 ||
+                          abs(p[2] - win.c[2]) > 1;
+        int dd[3] = {p[0] - win.c[0], p[1] - win.c[1], p[2] - win.c[2]};
+        uint32_t leave = 0;
+        if (jump) {
+            leave = win.rank >= 0 ? 0xFFu : 0u;
+        } else {
+#pragma unroll
+            for (int ax = 0; ax < 3; ++ax) {
+                // corners with bit ax clear: 0x55, 0x33, 0x0F for ax = 0, 1, 2
+                const uint32_t clear = ax == 0 ? 0x55u : (ax == 1 ? 0x33u : 0x0Fu);
+                if (dd[ax] > 0) leave |= clear;
+                if (dd[ax] < 0) leave |= ~clear & 0xFFu;
+            }
+        }
+#pragma unroll
+        for (int c = 0; c < 8; ++c)
+            if ((leave >> c) & 1u) flush_corner<FEAT>(a, tab, win, c, gC, gV, fresh, nb_lin, nb_id);
+        if (jump) {
+#pragma unroll
+            for (int c = 0; c < 8; ++c) win.A[c] = win.D[c] = 0.0f;
+            win.rank = rk;
+            win.id = g.rank_id[rk];
+            win.b = block_coords(g, g.rank_lin[rk]);
+            win.c[0] = p[0]; win.c[1] = p[1]; win.c[2] = p[2];
+        } else {
+#pragma unroll
+            for (int ax = 0; ax < 3; ++ax) {
+                const int bit = 1 << ax;
+#pragma unroll
+                for (int c = 0; c < 8; ++c) {
+                    if (c & bit) continue;
+                    const int c1 = c | bit;
+                    const float a0v = win.A[c], d0v = win.D[c], a1v = win.A[c1], d1v = win.D[c1];
+                    win.A[c] = dd[ax] > 0 ? a1v : (dd[ax] < 0 ? 0.0f : a0v);
+                    win.D[c] = dd[ax] > 0 ? d1v : (dd[ax] < 0 ? 0.0f : d0v);
+                    win.A[c1] = dd[ax] < 0 ? a0v : (dd[ax] > 0 ? 0.0f : a1v);
+                    win.D[c1] = dd[ax] < 0 ? d0v : (dd[ax] > 0 ? 0.0f : d1v);
+                }
+                win.c[ax] += dd[ax];
+            }
+        }
+        float wc[8];
+        corner_weights(fr, wc);
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+            win.A[c] = fmaf(wc[c], w, win.A[c]);
+            win.D[c] = fmaf(wc[c], gsig, win.D[c]);
+        }
+        return early && T < t_stop;
+    }
+
+    __device__ __forceinline__ void finish(const BackwardArgs& a, const AggTable& tab) {
+        if (win.rank >= 0) {
+#pragma unroll
+            for (int c = 0; c < 8; ++c) flush_corner<FEAT>(a, tab, win, c, gC, gV, fresh, nb_lin, nb_id);
+        }
+    }
+};
+
+// The table of the calling wavefront in dynamic LDS (after the occupancy
+// words), cleared.
+__device__ __forceinline__ AggTable agg_table(uint2* s_occ, int n_words, int wave, int lane) {
+    AggTable tab;
+    int32_t* base = reinterpret_cast<int32_t*>(s_occ + n_words) + wave * kAggWords;
+    tab.key = base;
+    tab.val = reinterpret_cast<float*>(base + kAggSlots);
+    for (int sl = lane; sl < kAggSlots; sl += 64) {
+        tab.key[sl] = -1;
+#pragma unroll
+        for (int c = 0; c < 8; ++c) tab.val[c * kAggSlots + sl] = 0.0f;
+    }
+    return tab;
+}
+
+// agg_flush by one wavefront on its own table.
+template <bool FEAT>
+__device__ __forceinline__ void wave_flush(const BackwardArgs& a, const AggTable& t, int lane) {
+    sync_wave();
+    agg_flush<FEAT>(a, t, lane, 64);
+    sync_wave();
+}
+
+// Wavefront-wide, after each step of the lanes: counts the table's new keys
+// and flushes it once it is full enough.
+struct TableSync {
+    int in_table = 0;  // wave-uniform: keys in the table
+    template <bool FEAT>
+    __device__ __forceinline__ void step(const BackwardArgs& a, const AggTable& tab, int lane, int& fresh) {
+        if (__any(fresh != 0)) {
+            in_table += wave_sum_i32(fresh);
+            fresh = 0;
+            if (in_table >= kAggFlushAt) {
+                wave_flush<FEAT>(a, tab, lane);
+                in_table = 0;
+            }
+        }
+    }
+};
+
+// One lane per ray.  Without a ray list the wavefronts walk the cameras'
+// tile_w x tile_h pixel tiles (neighbouring rays, shared voxels); with a list,
+// 64 consecutive list entries.  Gradients go through the wavefront's LDS
+// table.  Every lane stays to the end (the flushes need all 64).  Serves views
+// whose pixels are sparse on the grid and lists of more than 2^18 rays
+// (launch_backward says why).
+constexpr int kAggWaves = 4;  // wavefronts per workgroup
+constexpr int kAggLdsWords = kAggWaves * kAggWords;
+
+template <bool FEAT>
+__global__ __launch_bounds__(64 * kAggWaves) void k_march_backward(BackwardArgs a) {
+    extern __shared__ uint2 s_occ[];
+    const GridArgs& g = a.grid;
+    const int lane = threadIdx.x & 63;
+    const int wave = threadIdx.x >> 6;
+    // this lane's ray: list position i (indexes aux, grad_rgba, gcv) and id r
+    bool live;
+    int64_t i, r;
+    const int64_t wt = int64_t(a.ray_ids ? blockIdx.x : xcd_grouped(blockIdx.x, gridDim.x)) * kAggWaves + wave;
+    if (a.ray_ids) {
+        i = wt * 64 + lane;
+        live = i < a.n_rays;
+        // after a list launch: the rays whose samples it could not list
+        if (a.list) live = live && a.list_count[i] > kBackwardListCap;
+        r = live ? a.ray_ids[i] : 0;
+    } else {
+        live = wt < a.total_tiles;
+        i = r = 0;
+        if (live) {
+            const int ci = find_camera_by_tile(a.cams, a.n_cams, wt);
+            const DevCamera& c = a.cams[ci];
+            const int64_t tl = wt - c.tile_offset;
+            const int px = int(tl % c.tiles_x) * a.tile_w + lane % a.tile_w;
+            const int py = int(tl / c.tiles_x) * a.tile_h + lane / a.tile_w;
+            live = px < c.W && py < c.H;
+            i = r = c.ray_offset + int64_t(py) * c.W + px;
+        }
+    }
+    if (a.list && !__syncthreads_or(live)) return;
+    for (int w = threadIdx.x; w < g.n_words; w += blockDim.x) s_occ[w] = g.occ[w];
+    AggTable tab = agg_table(s_occ, g.n_words, wave, lane);
+    __syncthreads();
+    AdjointRay<FEAT> st;
+    live = st.setup(a, i, live);
+    st.table_scale(tab);
+
+    int64_t o[3] = {0, 0, 0};
+    int32_t s[3] = {0, 0, 1 << 15};
+    if (live) {
+        int ci, px, py;
+        locate(a, r, ci, px, py);
+        float d[3];
+        ray_setup(a.cams[ci], g.N, px, py, o, s, d);
+    }
+    TableSync sync;
+    march_ray_flat_sync(
+        g, s_occ, live, o, s,
+        [&](int64_t, int32_t rk, const uint8_t* vox, const int32_t p[3], const int32_t fr[3]) {
+            return st.sample(a, tab, rk, vox, p, fr);
+        },
+        [&]() {
+            sync.step<FEAT>(a, tab, lane, st.fresh);
+            return false;
+        });
+    st.finish(a, tab);
+    wave_flush<FEAT>(a, tab, lane);
+}
+
+// ------------------------------------------------------ eight lanes to a ray
 
 template <int CTRL>
 __device__ __forceinline__ int32_t dpp(int32_t v) {
@@ -574,64 +901,303 @@ struct QuadWalk {
     }
 };
 
-// One ray per 8 lanes.  A trip of the walk looks at the ray's next 8 lattice
-// samples, one per lane (its distance byte), and then takes the active ones
-// in order, all lanes together, lane by corner: each loads its corner's
-// voxel, the two sums a sample needs (density and g . value) are three DPP
-// additions each, and each lane keeps its corner's (A, D) and hands it over
-// by itself.  One ray per lane, as this was before, paid for every sample
-// with eight guarded hand-over passes and 256 bytes of loads per lane, at two
-// wavefronts per SIMD (197 to 256 registers), and a list of 65,536 rays
-// needed a separate walk to keep 64 rays of unequal length apart.
-//   eight 800x800 views, 512^3, FP32 network   23.7 -> 18.1 ms
-//   16,384 rays in 8x8 patches, 512^3           1.95 -> 0.41 ms
-//   65,536 scattered rays, 1024^3, packed       2.35 -> 1.2 ms
-// Bound by instruction issue with the table (VALUs 82% busy, half the lanes
-// at work: about 270 instructions per sample of 8 rays), for scattered rays
-// by latency and by rays of unequal length side by side.  Registers: 96 (five
-// wavefronts per SIMD) with the table, where six or three cost 9 and 40%;
-// scattered rays want the next sample's voxels in flight, which takes 118
-// (20% slower squeezed into 96).
-// Without a ray list the workgroups walk halves of the cameras'
-// tile_w x tile_h pixel tiles, with one 32 consecutive list entries.  AGG:
-// gradients go through the workgroup's LDS table, else through the
-// wavefront's log.
+// Where a lane stands in its ray's cell.
+struct CornerLane {
+    int l, cx, cy, cz;
+    float ox, oy, oz;  // the corner's weight on an axis is f = |0 - f| or 1 - f
+    uint32_t offset;   // of the corner's voxel from the cell's first, in bytes
+
+    __device__ __forceinline__ CornerLane(const GridArgs& g, int lane) {
+        l = lane & 7;
+        cz = l >> 2;
+        cx = (l & 1) ^ cz;
+        cy = ((l >> 1) & 1) ^ cz;
+        ox = cx ? 0.0f : 1.0f;
+        oy = cy ? 0.0f : 1.0f;
+        oz = cz ? 0.0f : 1.0f;
+        offset = uint32_t((cz * g.Bp + cy) * g.Bp + cx) * 32u;
+    }
+};
+
+// A sample as the lanes of its ray hold it: position in the block (Q16, own
+// axis), record, corner voxel, exp(-sigma delta).
+struct Fetched {
+    int32_t own, rank;
+    float4 rgb, feat;
+    float e;
+
+    // Reads this corner's voxel of the cell at `own`.
+    template <bool FEAT>
+    __device__ __forceinline__ void read(const GridArgs& g, const CornerLane& c, const uint8_t* vox) {
+        const int32_t p[3] = {dpp<kAxisX>(own) >> 16, dpp<kAxisY>(own) >> 16, dpp<kAxisZ>(own) >> 16};
+        const uint32_t nb = uint32_t(g.Bp);
+        const uint8_t* at = vox + (uint64_t(cell_index(p, nb, nb * nb)) * 32u + c.offset);
+        rgb = reinterpret_cast<const float4*>(at)[0];
+        if (FEAT) feat = reinterpret_cast<const float4*>(at)[1];
+    }
+};
+
+// The adjoint state of a ray in its 8 lanes: the same in all but A and D,
+// the running sums of the lane's corner, and the window's cell, own axis.
+template <bool FEAT>
+struct CornerRay {
+    float gC[3], gV[4];
+    float T, rest;  // rest: E - P_k + T_N dL/dT_N
+    float A, D;
+    int32_t wc;              // the window's cell, own axis
+    int32_t wrank, wid, wb;  // its block's record, atlas id, coordinates
+    int32_t nb_lin, nb_id;
+
+    // Reads list position i's state; false when the ray composited nothing
+    // (no grid gradient) or `live` is false.
+    __device__ __forceinline__ bool setup(const BackwardArgs& a, int64_t i, bool live) {
+        float4 a0 = make_float4(0.f, 0.f, 0.f, 0.f), a1 = make_float4(0.f, 0.f, 0.f, -1.f);
+        float4 gg = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (live) {
+            a1 = reinterpret_cast<const float4*>(a.aux)[2 * i + 1];
+            live = a1.w >= 0.0f;
+        }
+        gC[0] = gC[1] = gC[2] = 0.f;
+        gV[0] = gV[1] = gV[2] = gV[3] = 0.f;
+        if (live) {
+            a0 = reinterpret_cast<const float4*>(a.aux)[2 * i];
+            gg = reinterpret_cast<const float4*>(a.grad_rgba)[i];
+            gC[0] = gg.x; gC[1] = gg.y; gC[2] = gg.z;
+            if (FEAT) {
+                const float4 c0 = reinterpret_cast<const float4*>(a.gcv)[2 * i];
+                const float4 c1 = reinterpret_cast<const float4*>(a.gcv)[2 * i + 1];
+                gC[0] = c0.x; gC[1] = c0.y; gC[2] = c0.z;
+                gV[0] = c0.w; gV[1] = c1.x; gV[2] = c1.y; gV[3] = c1.z;
+            }
+        }
+        const float E = gC[0] * a0.x + gC[1] * a0.y + gC[2] * a0.z +
+                        (gV[0] * a0.w + gV[1] * a1.x + gV[2] * a1.y + gV[3] * a1.z);
+        const float gTN = gg.x * a.opts.bg[0] + gg.y * a.opts.bg[1] + gg.z * a.opts.bg[2] - gg.w;
+        rest = E + a1.w * gTN;
+        T = 1.0f;
+        A = D = 0.0f;
+        wc = 0;
+        wrank = -1;
+        wid = wb = 0;
+        nb_lin = nb_id = -1;
+        return live;
+    }
+
+    // The channel that lane l adds to device memory, where the lanes of a ray
+    // stand for a voxel's channels.
+    __device__ __forceinline__ float channel(int l) const {
+        float v = 0.0f;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) v = l == 1 + c ? gC[c] : v;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) v = l == 4 + c ? gV[c] : v;
+        return v;
+    }
+
+    // Slot of this lane's corner, -1 where `leave` is not set or it holds nothing.
+    template <typename I>
+    __device__ __forceinline__ I voxel(const GridArgs& g, const CornerLane& c, bool leave) {
+        const int vx = dpp<kAxisX>(wc) + c.cx - 1, vy = dpp<kAxisY>(wc) + c.cy - 1, vz = dpp<kAxisZ>(wc) + c.cz - 1;
+        I vi = -1;
+        if (leave && (A != 0.0f || D != 0.0f)) vi = canonical_voxel<I>(g, wid, wb, vx, vy, vz, nb_lin, nb_id);
+        return vi;
+    }
+
+    // What an active sample does to the window: the weights it brings, how
+    // far the window's cell moves, whether this lane's corner leaves.
+    struct Slide {
+        float wt, ws, gsig;
+        int32_t move;
+        bool jump, lx, ly, lz, leave;
+    };
+
+    __device__ __forceinline__ Slide weigh(const BackwardArgs& a, const CornerLane& c, const Fetched& f, int lane) {
+        Slide m;
+        const int32_t q[3] = {dpp<kAxisX>(f.own), dpp<kAxisY>(f.own), dpp<kAxisZ>(f.own)};
+        const float fx = float(q[0] & 0xFFFF) * (1.0f / 65536.0f);
+        const float fy = float(q[1] & 0xFFFF) * (1.0f / 65536.0f);
+        const float fz = float(q[2] & 0xFFFF) * (1.0f / 65536.0f);
+        m.wt = (fabsf(c.ox - fx) * fabsf(c.oy - fy)) * fabsf(c.oz - fz);
+        float ev = gC[0] * f.rgb.y + gC[1] * f.rgb.z + gC[2] * f.rgb.w;
+        if (FEAT) ev += gV[0] * f.feat.x + gV[1] * f.feat.y + gV[2] * f.feat.z + gV[3] * f.feat.w;
+        const float ek = corner_sum(m.wt * ev);
+        m.ws = T * (1.0f - f.e);
+        rest -= m.ws * ek;
+        T *= f.e;
+        m.gsig = (1.0f / float(a.grid.N)) * (T * ek - rest);
+        // Corners on a trailing face (or all of them after a jump) leave: on
+        // an axis the window moves along, those on the trailing side.
+        m.move = (f.own >> 16) - wc;
+        const int32_t dd[3] = {dpp<kAxisX>(m.move), dpp<kAxisY>(m.move), dpp<kAxisZ>(m.move)};
+        m.jump = wrank != f.rank || ray_bits(abs(m.move) > 1, lane) != 0;
+        m.lx = dd[0] != 0 && (dd[0] > 0) == (c.cx == 0);
+        m.ly = dd[1] != 0 && (dd[1] > 0) == (c.cy == 0);
+        m.lz = dd[2] != 0 && (dd[2] > 0) == (c.cz == 0);
+        m.leave = m.jump ? wrank >= 0 : m.lx || m.ly || m.lz;
+        return m;
+    }
+
+    // The corners that left have been handed over: the survivors move to their
+    // new lane.  Returns true once the early-stop rule ends the ray.
+    __device__ __forceinline__ bool slide(const BackwardArgs& a, const Fetched& f, const Slide& m) {
+        if (m.jump) {
+            A = D = 0.0f;
+            wrank = f.rank;
+            wid = a.grid.rank_id[f.rank];
+            wb = block_coords(a.grid, a.grid.rank_lin[f.rank]);
+        } else {
+            // a trailing corner takes its leading neighbour's sums, which start anew
+            const int32_t dd[3] = {dpp<kAxisX>(m.move), dpp<kAxisY>(m.move), dpp<kAxisZ>(m.move)};
+            float An = dpp<kFlipX>(A), Dn = dpp<kFlipX>(D);
+            A = dd[0] == 0 ? A : (m.lx ? An : 0.0f);
+            D = dd[0] == 0 ? D : (m.lx ? Dn : 0.0f);
+            An = dpp<kFlipY>(A), Dn = dpp<kFlipY>(D);
+            A = dd[1] == 0 ? A : (m.ly ? An : 0.0f);
+            D = dd[1] == 0 ? D : (m.ly ? Dn : 0.0f);
+            An = dpp<kFlipZ>(A), Dn = dpp<kFlipZ>(D);
+            A = dd[2] == 0 ? A : (m.lz ? An : 0.0f);
+            D = dd[2] == 0 ? D : (m.lz ? Dn : 0.0f);
+        }
+        wc += m.move;
+        A = fmaf(m.wt, m.ws, A);
+        D = fmaf(m.wt, m.gsig, D);
+        return a.opts.early_stop && T < a.opts.t_stop;
+    }
+
+    // Takes an active sample.  hand_over(leave) is called once, by all lanes of
+    // the ray, before the window moves: the lanes with `leave` hand over.
+    template <typename HandOver>
+    __device__ __forceinline__ bool take(const BackwardArgs& a, const CornerLane& c, const Fetched& f, int lane,
+                                         HandOver&& hand_over) {
+        const Slide m = weigh(a, c, f, lane);
+        hand_over(m.leave);
+        return slide(a, f, m);
+    }
+};
+
+// The lanes of a ray add its corners with vi >= 0 to device memory, the 8
+// channels of one after the other.  gch: own channel's gradient.
+template <typename I>
+__device__ __forceinline__ void add_direct(const BackwardArgs& a, int l, int lane, I vi, float Ds, float A, float gch) {
+    for (uint32_t m = ray_bits(vi >= 0, lane); m != 0; m &= m - 1) {
+        const int from = (lane & ~7) | __builtin_ctz(m);
+        const I v = __shfl(vi, from);
+        const float dv = __shfl(Ds, from), av = __shfl(A, from);
+        const float x = l == 0 ? dv : av * gch;
+        if (x != 0.0f) unsafeAtomicAdd(grad_channel(a, v, l), x);
+    }
+}
+
+// exp(-sigma delta) of a sample in a float32 block at `vox` and whether it is
+// active, with the forward's operations in their order (gather_f32), so that
+// T, the weights and the stop are the forward's to the bit.
+__device__ __forceinline__ bool sample_decay(const GridArgs& g, const uint8_t* vox, const int32_t p[3],
+                                             const int32_t fr[3], bool nn_gate, float& e) {
+    const uint32_t nb = uint32_t(g.Bp), nbb = nb * nb;
+    const uint8_t* at = vox + uint64_t(cell_index(p, nb, nbb)) * 32u;
+    float den[8], w[8];
+#pragma unroll
+    for (int c = 0; c < 8; ++c)
+        den[c] = *reinterpret_cast<const float*>(at + ((c & 1 ? 32u : 0u) + (c & 2 ? nb * 32u : 0u) +
+                                                       (c & 4 ? nbb * 32u : 0u)));
+    corner_weights(fr, w);
+    const int cnn = nearest_corner(fr);
+    float sigma = 0.0f, dnn = 0.0f;
+    bool act = false;
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+        act |= den[c] != 0.0f && corner_live(c, fr);
+        dnn = c == cnn ? den[c] : dnn;
+        sigma = fmaf(w[c], den[c], sigma);
+    }
+    e = __expf(-sigma * (g.sigma_scale * (1.0f / float(g.N))));
+    return nn_gate ? dnn != 0.0f : act;
+}
+
+// The log of a wavefront whose rays share few voxels: what the lanes hand
+// over in a step (voxel, ray, A, density sum) goes, once all 64 are together,
+// to the place a ballot gives it, so the fill count is the same in every lane.
+// A full log goes to device memory, 8 entries to an instruction, the lanes of
+// one across the voxel's channels.  Added straight away, every atomic would
+// stand in front of the next step's loads, which wait for it (vector memory
+// retires in order).
+constexpr int kLogEntries = 320;  // 16 bytes each
+
+template <int kEntries>
+struct WaveLog {
+    int4* at;           // [kEntries]: voxel (low word; ray << 24 | high), A, density sum
+    float (*gch)[8];    // the rays' gradients by channel
+    int n = 0;
+    int64_t vi = -1;    // what this lane hands over, < 0: nothing
+    float A = 0.0f, Ds = 0.0f;
+
+    __device__ __forceinline__ void flush(const BackwardArgs& a, int lane) {
+        sync_wave();
+        const int l = lane & 7;
+        for (int e = lane >> 3; e < n; e += 8) {
+            const int4 h = at[e];
+            const int64_t v = int64_t(uint64_t(uint32_t(h.x)) | (uint64_t(uint32_t(h.y & 0xffffff)) << 32));
+            const float x = l == 0 ? __int_as_float(h.w) : __int_as_float(h.z) * gch[h.y >> 24][l];
+            if (x != 0.0f) unsafeAtomicAdd(grad_channel(a, v, l), x);
+        }
+        n = 0;
+        sync_wave();
+    }
+
+    __device__ __forceinline__ void append(const BackwardArgs& a, int lane) {
+        const uint64_t m = __ballot(vi >= 0);
+        if (m == 0) return;  // wave-uniform
+        if (n > kEntries - 64) flush(a, lane);
+        if (vi >= 0)
+            at[n + int(__builtin_amdgcn_mbcnt_hi(uint32_t(m >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(m), 0u)))] =
+                make_int4(int32_t(uint32_t(uint64_t(vi))), int32_t(vi >> 32) | (lane >> 3) << 24, __float_as_int(A),
+                          __float_as_int(Ds));
+        n += __builtin_popcountll(m);
+        vi = -1;
+    }
+};
+
+// Eight lanes to a ray.  A trip of the walk looks at the ray's
+// next 8 lattice samples, one per lane (its distance byte and, in an active
+// cell, its density), and then takes the active ones in order, all lanes
+// together, lane by corner: each loads its corner's voxel, the sum g . value
+// over the corners is three DPP additions, and each lane keeps its corner's
+// (A, D) and hands it over by itself, into a table that the workgroup shares.
+// One lane per ray pays for every sample with eight guarded hand-over passes
+// and 256 bytes of loads per lane, at two wavefronts per SIMD (197 registers);
+// this one runs five (96).
+//   eight 800x800 views, 512^3, FP32 network   23.7 -> 17.5 ms
+// Bound by instruction issue (VALUs 82% busy, half the lanes at work: about
+// 270 instructions per sample of 8 rays).  Six wavefronts per SIMD cost 9%
+// (spills), four 5%.
+constexpr int kAdjWaves = 4;  // wavefronts per workgroup: half a tile, 8 lanes to a ray
+// The workgroup looks at the table every kAdjTrips trips of its rays and
+// flushes it when it holds more than kAdjFlushAt keys; what its rays add in
+// four trips (up to 32 samples each) mostly fits above that.
+constexpr int kAdjFlushAt = kAggSlots * 9 / 16;
+constexpr int kAdjTrips = 4;
+
+// AGG: whole views, half a tile to a workgroup, gradients through the table.
+// Else through the wavefronts' logs, with no limit on the voxel index: views
+// and lists on grids beyond the table's keys, and of a scattered list the rays
+// with too many samples to list.
 template <bool FEAT, bool AGG>
 __global__ __launch_bounds__(64 * kAdjWaves) __attribute__((amdgpu_waves_per_eu(AGG ? 5 : 4))) void k_adjoint(BackwardArgs a) {
-    constexpr int kWaves = kAdjWaves;
     extern __shared__ uint2 s_occ[];
     __shared__ float s_max;
     __shared__ int32_t s_fresh[3], s_live[3];
-    __shared__ float s_gch[AGG ? 1 : kWaves][8][8];  // the rays' gradients by channel
+    __shared__ float s_gch[AGG ? 1 : kAdjWaves][8][8];
     const GridArgs& g = a.grid;
-    for (int w = threadIdx.x; w < g.n_words; w += blockDim.x) s_occ[w] = g.occ[w];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int l = lane & 7;
-    const int cz = l >> 2, cx = (l & 1) ^ cz, cy = ((l >> 1) & 1) ^ cz;
-    AggTable tab = {nullptr, nullptr, 0.0f, 0.0f};
-    if (AGG) {
-        tab.key = reinterpret_cast<int32_t*>(s_occ + g.n_words);
-        tab.val = reinterpret_cast<float*>(tab.key + kAggSlots);
-        for (int sl = threadIdx.x; sl < kAggSlots; sl += blockDim.x) {
-            tab.key[sl] = -1;
-#pragma unroll
-            for (int c = 0; c < 8; ++c) tab.val[c * kAggSlots + sl] = 0.0f;
-        }
-        if (threadIdx.x < 3) s_fresh[threadIdx.x] = s_live[threadIdx.x] = 0;
-    }
-    int4* log = reinterpret_cast<int4*>(s_occ + ((g.n_words + 1) & ~1)) + wave * kLogEntries;
-
-    // Rays come in sets of 64 (a tile, or 64 list entries), a workgroup takes
-    // half of one.  Ray idx of the set: list position i (indexes aux,
-    // grad_rgba, gcv), pixel (px, py) of camera ci.
-    // (of a view's tiles each XCD takes runs of 32 workgroups, as the render does)
+    // Ray idx of the workgroup's 64: list position i (indexes aux, grad_rgba,
+    // gcv), pixel (px, py) of camera ci.  Of a view's tiles each XCD takes
+    // runs of 16.
     const uint32_t u = a.ray_ids ? blockIdx.x : xcd_grouped<32>(blockIdx.x, gridDim.x);
     const int64_t set = (a.first_group + u) >> 1;
-    const int half = int(u & 1);
     auto ray_of = [&](int idx, int64_t& i, int& ci, int& px, int& py) {
         if (a.ray_ids) {
             i = set * 64 + idx;
-            if (i >= a.n_rays) return false;
+            if (i >= a.n_rays || (a.list && a.list_count[i] <= kBackwardListCap)) return false;
             locate(a, a.ray_ids[i], ci, px, py);
             return true;
         }
@@ -643,208 +1209,120 @@ __global__ __launch_bounds__(64 * kAdjWaves) __attribute__((amdgpu_waves_per_eu(
         i = c.ray_offset + int64_t(py) * c.W + px;
         return px < c.W && py < c.H;
     };
-    if (AGG && threadIdx.x < 64) {  // the table's scale, from the whole set
-        int64_t i;
-        int ci, px, py;
+    int64_t i = 0;
+    int ci = 0, px = 0, py = 0;
+    if (AGG && threadIdx.x < 64) {  // the table's scale, from all 64 rays
         float m = 0.0f;
         if (ray_of(threadIdx.x, i, ci, px, py) && a.aux[8 * i + 7] >= 0.0f) {
             const float* v = FEAT ? a.gcv + 8 * i : a.grad_rgba + 4 * i;
 #pragma unroll
-            for (int c = 0; c < (FEAT ? 7 : 3); ++c) m = fmaxf(m, fabsf(v[c]));
+            for (int ch = 0; ch < (FEAT ? 7 : 3); ++ch) m = fmaxf(m, fabsf(v[ch]));
         }
         m = wave_max(m);
         if (threadIdx.x == 0) s_max = m;
     }
-    int64_t i = 0;
-    int ci = 0, px = 0, py = 0;
-    bool live = ray_of((half * kWaves + wave) * 8 + (lane >> 3), i, ci, px, py);
+    bool live = ray_of((int(u & 1) * kAdjWaves + wave) * 8 + (lane >> 3), i, ci, px, py);
+    if (a.list && !__syncthreads_or(live)) return;
+    for (int w = threadIdx.x; w < g.n_words; w += blockDim.x) s_occ[w] = g.occ[w];
+    const CornerLane c(g, lane);
+    AggTable tab = {nullptr, nullptr, 0.0f, 0.0f};
+    if (AGG) {
+        tab.key = reinterpret_cast<int32_t*>(s_occ + g.n_words);
+        tab.val = reinterpret_cast<float*>(tab.key + kAggSlots);
+        for (int sl = threadIdx.x; sl < kAggSlots; sl += blockDim.x) {
+            tab.key[sl] = -1;
+#pragma unroll
+            for (int ch = 0; ch < 8; ++ch) tab.val[ch * kAggSlots + sl] = 0.0f;
+        }
+        if (threadIdx.x < 3) s_fresh[threadIdx.x] = s_live[threadIdx.x] = 0;
+    }
     QuadWalk w;
     if (live) {
         int64_t o[3];
         int32_t s[3];
         float d[3];
         ray_setup(a.cams[ci], g.N, px, py, o, s, d);
-        live = w.init(g, o, s, l);
+        live = w.init(g, o, s, c.l);
     }
-    // its output gradient and what the forward saved
-    float4 a0 = make_float4(0.f, 0.f, 0.f, 0.f), a1 = make_float4(0.f, 0.f, 0.f, -1.f);
-    float4 gg = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (live) {
-        a1 = reinterpret_cast<const float4*>(a.aux)[2 * i + 1];
-        live = a1.w >= 0.0f;  // nothing was composited: no grid gradient
-    }
-    float gC[3] = {0.f, 0.f, 0.f}, gV[4] = {0.f, 0.f, 0.f, 0.f};
-    if (live) {
-        a0 = reinterpret_cast<const float4*>(a.aux)[2 * i];
-        gg = reinterpret_cast<const float4*>(a.grad_rgba)[i];
-        gC[0] = gg.x; gC[1] = gg.y; gC[2] = gg.z;
-        if (FEAT) {
-            const float4 c0 = reinterpret_cast<const float4*>(a.gcv)[2 * i];
-            const float4 c1 = reinterpret_cast<const float4*>(a.gcv)[2 * i + 1];
-            gC[0] = c0.x; gC[1] = c0.y; gC[2] = c0.z;
-            gV[0] = c0.w; gV[1] = c1.x; gV[2] = c1.y; gV[3] = c1.z;
-        }
-    }
-    const float E = gC[0] * a0.x + gC[1] * a0.y + gC[2] * a0.z +
-                    (gV[0] * a0.w + gV[1] * a1.x + gV[2] * a1.y + gV[3] * a1.z);
-    const float gTN = gg.x * a.opts.bg[0] + gg.y * a.opts.bg[1] + gg.z * a.opts.bg[2] - gg.w;
-    const float tail = a1.w * gTN;  // T_N dL/dT_N
-    const float inv_g = 1.0f / float(g.G);
-    const float delta = 1.0f / float(g.N), kx = g.sigma_scale * delta;
-    // Where the forward ended the ray early, at the sample that left it its
-    // T_N < t_stop, the re-march ends there too: T is recomputed here with
-    // other roundings (a few 2^-22), so it ends when T has come down to T_N,
-    // give or take 2^-16, or is that clearly past the threshold.
-    const float t_end = a.opts.early_stop && a1.w < a.opts.t_stop
-                            ? fmaxf(a1.w * (1.0f + 0x1p-16f), a.opts.t_stop * (1.0f - 0x1p-16f))
-                            : -1.0f;
-    // direct atomics: this lane's channel and its gradient
-    float gch = 0.0f;
-#pragma unroll
-    for (int c = 0; c < 3; ++c) gch = l == 1 + c ? gC[c] : gch;
-#pragma unroll
-    for (int c = 0; c < 4; ++c) gch = l == 4 + c ? gV[c] : gch;
-    if (!AGG) s_gch[wave][lane >> 3][l] = gch;
+    CornerRay<FEAT> st;
+    live = st.setup(a, i, live);
+    const float gch = st.channel(c.l);
+    WaveLog<kLogEntries> log = {reinterpret_cast<int4*>(s_occ + ((g.n_words + 1) & ~1)) + wave * kLogEntries, s_gch[AGG ? 0 : wave]};
+    if (!AGG) s_gch[wave][lane >> 3][c.l] = gch;
     __syncthreads();
     if (AGG) agg_scale(tab, s_max);
 
-    const uint32_t nb = uint32_t(g.Bp), nbb = nb * nb;
     const uint32_t nc = uint32_t(g.Bc), ncc = nc * nc;
-    const uint32_t corner = (uint32_t(cz) * nbb + uint32_t(cy) * nb + uint32_t(cx)) * 32u;
-    // weight of the corner on an axis: f = |0 - f| or 1 - f
-    const float ox = cx ? 0.0f : 1.0f, oy = cy ? 0.0f : 1.0f, oz = cz ? 0.0f : 1.0f;
-
-    float T = 1.0f, rest = E + tail;  // rest: E - P_k + T_N dL/dT_N
-    float A = 0.0f, D = 0.0f;         // this corner's sums
-    int32_t wc = 0;                      // the window's cell, own axis
-    int32_t wrank = -1, wid = 0, wb = 0;  // its block's record, atlas id, coordinates (8 bits each)
-    int32_t nb_lin = -1, nb_id = -1;
     int fresh = 0;
-    int32_t* iv = reinterpret_cast<int32_t*>(tab.val);
-
-    int4 out = make_int4(0, -1, 0, 0);  // without the table: what this lane hands over, out.y < 0: nothing
-
-    // Hands this corner's sums over where `leave` is set (the same decision
-    // rule in all lanes of the ray, not the same answer).
     auto hand_over = [&](bool leave) {
-        const int vx = dpp<kAxisX>(wc) + cx - 1, vy = dpp<kAxisY>(wc) + cy - 1, vz = dpp<kAxisZ>(wc) + cz - 1;
         using Index = typename std::conditional<AGG, int32_t, int64_t>::type;  // the table's keys are int32
-        Index vi = -1;
-        if (leave && (A != 0.0f || D != 0.0f))
-            vi = canonical_voxel<Index>(g, wid, wb, vx, vy, vz, nb_lin, nb_id);
-        const float Ds = g.sigma_scale * D;
-        if (AGG && vi >= 0) {
-            const int sl = agg_slot(tab, vi, fresh);
+        Index vi = st.template voxel<Index>(g, c, leave);
+        const float Ds = g.sigma_scale * st.D;
+        if (!AGG) {
+            log.vi = vi;
+            log.A = st.A;
+            log.Ds = Ds;
+            return;
+        }
+        if (vi >= 0) {
+            const int sl = agg_slot(tab, agg_hash(int32_t(vi)), kAggProbes, int32_t(vi), fresh);
             if (sl >= 0) {
                 vi = -1;
-                atomicAdd(tab.val + sl, Ds);
-                const float Aq = A * tab.q;  // a power of two: exact, so the products round as A g would
-#pragma unroll
-                for (int c = 0; c < 3; ++c)
-                    atomicAdd(iv + (1 + c) * kAggSlots + sl, int32_t(__builtin_rintf(Aq * gC[c])));
-                if (FEAT) {
-#pragma unroll
-                    for (int c = 0; c < 4; ++c)
-                        atomicAdd(iv + (4 + c) * kAggSlots + sl, int32_t(__builtin_rintf(Aq * gV[c])));
-                }
+                agg_add<FEAT>(tab, sl, Ds, st.A, st.gC, st.gV);
             }
         }
-        if (AGG) {  // no slot free: the ray's 8 lanes add a corner's 8 channels
-            for (uint32_t m = ray_bits(vi >= 0, lane); m != 0; m &= m - 1) {
-                const int from = (lane & ~7) | __builtin_ctz(m);
-                const Index v = __shfl(vi, from);
-                const float dv = __shfl(Ds, from), av = __shfl(A, from);
-                const float x = l == 0 ? dv : av * gch;
-                if (x != 0.0f) unsafeAtomicAdd(grad_channel(a, v, l), x);
-            }
-        } else {
-            out = make_int4(int32_t(uint32_t(uint64_t(vi))), int32_t(vi >> 32), __float_as_int(A), __float_as_int(Ds));
-        }
+        add_direct(a, c.l, lane, vi, Ds, st.A, gch);  // no slot free
     };
 
-    // Without the table: what the lanes hand over in a step goes, at the next
-    // point where all 64 are together, to the wavefront's log (voxel, ray, A,
-    // density sum), each to the place a ballot gives it, so the fill count is
-    // the same in every lane.  A full log goes to device memory, 8 entries to
-    // an instruction, the lanes of one across the voxel's channels.  Added
-    // straight away, every atomic would stand in front of the next step's
-    // loads, which wait for it (vector memory retires in order).
-    int n_log = 0;
-    auto log_flush = [&]() {
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        for (int e = lane >> 3; e < n_log; e += 8) {
-            const int4 h = log[e];
-            const int64_t v = int64_t(uint64_t(uint32_t(h.x)) | (uint64_t(uint32_t(h.y & 0xffffff)) << 32));
-            const float x = l == 0 ? __int_as_float(h.w) : __int_as_float(h.z) * s_gch[wave][h.y >> 24][l];
-            if (x != 0.0f) unsafeAtomicAdd(grad_channel(a, v, l), x);
-        }
-        n_log = 0;
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-    };
-    auto log_append = [&]() {
-        const bool want = out.y >= 0;
-        const uint64_t m = __ballot(want);
-        if (m == 0) return;  // wave-uniform
-        if (n_log > kLogEntries - 64) log_flush();
-        if (want) {
-            out.y |= (lane >> 3) << 24;
-            log[n_log + int(__builtin_amdgcn_mbcnt_hi(uint32_t(m >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(m), 0u)))] =
-                out;
-        }
-        n_log += __builtin_popcountll(m);
-        out.y = -1;
-    };
-
-    int in_table = 0, phase = 0;  // AGG: keys in the table, the same in every lane of the workgroup
+    int in_table = 0, phase = 0;  // keys in the table, the same in every lane of the workgroup
     for (int trip = 0;; ++trip) {
-        if (AGG) {
-            if (trip % kAggTrips == 0) {
-                // Slot `phase` collects this phase's counts before the barrier
-                // and is read after it; the slot of the phase after next was
-                // last read before this barrier, and is cleared for it.
-                int f = fresh;
+        if (!AGG) {
+            if (!__any(live)) break;
+        } else if (trip % kAdjTrips == 0) {
+            // Slot `phase` collects this phase's counts before the barrier
+            // and is read after it; the slot of the phase after next was
+            // last read before this barrier, and is cleared for it.
+            int f = fresh;
 #pragma unroll
-                for (int sh = 32; sh >= 1; sh >>= 1) f += __shfl_xor(f, sh);
-                const bool some = __any(live);
-                if (lane == 0 && f != 0) atomicAdd(&s_fresh[phase], f);
-                if (lane == 0 && some) s_live[phase] = 1;
-                fresh = 0;
-                __syncthreads();
-                in_table += s_fresh[phase];
-                const bool on = s_live[phase] != 0;
-                const int clear = phase == 0 ? 2 : phase - 1;
-                if (threadIdx.x == 0) s_fresh[clear] = s_live[clear] = 0;
-                phase = phase == 2 ? 0 : phase + 1;
-                if (!on || in_table > kAggFlushAt) {
-                    if (!on) {  // the last windows
-                        hand_over(wrank >= 0);
-                        __syncthreads();
-                    }
-                    agg_flush<FEAT>(a, tab);
-                    if (!on) break;
-                    in_table = 0;
+            for (int sh = 32; sh >= 1; sh >>= 1) f += __shfl_xor(f, sh);
+            const bool some = __any(live);
+            if (lane == 0 && f != 0) atomicAdd(&s_fresh[phase], f);
+            if (lane == 0 && some) s_live[phase] = 1;
+            fresh = 0;
+            __syncthreads();
+            in_table += s_fresh[phase];
+            const bool on = s_live[phase] != 0;
+            const int clear = phase == 0 ? 2 : phase - 1;
+            if (threadIdx.x == 0) s_fresh[clear] = s_live[clear] = 0;
+            phase = phase == 2 ? 0 : phase + 1;
+            if (!on || in_table > kAdjFlushAt) {
+                if (!on) {  // the last windows
+                    hand_over(st.wrank >= 0);
                     __syncthreads();
                 }
+                agg_flush<FEAT>(a, tab, threadIdx.x, blockDim.x);
+                if (!on) break;
+                in_table = 0;
+                __syncthreads();
             }
-        } else if (!__any(live)) {
-            break;
         }
         uint32_t todo = 0;
         int32_t reach = 0;
-        if (live) {
-            while (live && w.left <= 0) live = w.enter(g, s_occ);
-        }
+        while (live && w.left <= 0) live = w.enter(g, s_occ);
+        float my_e = 1.0f;  // exp(-sigma delta) of the sample this lane looks at
         if (live) {
             bool act = false;
-            const int32_t p[3] = {(dpp<kAxisX>(w.q) + mul_s24(l, dpp<kAxisX>(w.s))) >> 16,
-                                  (dpp<kAxisY>(w.q) + mul_s24(l, dpp<kAxisY>(w.s))) >> 16,
-                                  (dpp<kAxisZ>(w.q) + mul_s24(l, dpp<kAxisZ>(w.s))) >> 16};
-            if (l < w.left) {
+            const int32_t q[3] = {dpp<kAxisX>(w.q) + mul_s24(c.l, dpp<kAxisX>(w.s)),
+                                  dpp<kAxisY>(w.q) + mul_s24(c.l, dpp<kAxisY>(w.s)),
+                                  dpp<kAxisZ>(w.q) + mul_s24(c.l, dpp<kAxisZ>(w.s))};
+            if (c.l < w.left) {
+                const int32_t p[3] = {q[0] >> 16, q[1] >> 16, q[2] >> 16};
                 const int32_t db = w.dist[cell_index(p, nc, ncc)];
-                act = db == 0;
-                reach = l + (act ? 1 : skip_steps(db, w.smax, w.inv_smax));
+                reach = c.l + (db == 0 ? 1 : skip_steps(db, w.smax, w.inv_smax));
+                if (db == 0) {  // (this also brings in the lines that the corners' lanes read next)
+                    const int32_t fr[3] = {q[0] & 0xFFFF, q[1] & 0xFFFF, q[2] & 0xFFFF};
+                    act = sample_decay(g, w.dist + g.dist_bytes, p, fr, a.opts.nn_gate != 0, my_e);
+                }
             }
             todo = ray_bits(act, lane);
             reach = max(reach, dpp<kFlipX>(reach));
@@ -852,99 +1330,21 @@ __global__ __launch_bounds__(64 * kAdjWaves) __attribute__((amdgpu_waves_per_eu(
             reach = max(reach, dpp<kFlipZ>(reach));
             reach = min(reach, w.left);
         }
-        // Reads this corner's voxel of the ray's next active sample.
-        auto fetch = [&](int32_t& own, float4& va, float4& vb) {
-            own = w.q + mul_s24(__builtin_ctz(todo), w.s);
-            todo &= todo - 1;
-            const int32_t p[3] = {dpp<kAxisX>(own) >> 16, dpp<kAxisY>(own) >> 16, dpp<kAxisZ>(own) >> 16};
-            const uint8_t* at = w.dist + g.dist_bytes + (uint64_t(cell_index(p, nb, nbb)) * 32u + corner);
-            va = reinterpret_cast<const float4*>(at)[0];
-            if (FEAT) vb = reinterpret_cast<const float4*>(at)[1];
-        };
-        auto take = [&](int32_t own, const float4& va, const float4& vb) {
-            const int32_t q[3] = {dpp<kAxisX>(own), dpp<kAxisY>(own), dpp<kAxisZ>(own)};
-            const float fx = float(q[0] & 0xFFFF) * (1.0f / 65536.0f);
-            const float fy = float(q[1] & 0xFFFF) * (1.0f / 65536.0f);
-            const float fz = float(q[2] & 0xFFFF) * (1.0f / 65536.0f);
-            const float wt = (fabsf(ox - fx) * fabsf(oy - fy)) * fabsf(oz - fz);
-            // The exact active test: some corner of non-zero weight (every
-            // product of non-zero fractions is at least 2^-48) has non-zero
-            // density; or, the viewer's gate, the nearest corner has.
-            bool dense = va.x != 0.0f && wt != 0.0f;
-            if (a.opts.nn_gate)
-                dense = va.x != 0.0f && cx == ((q[0] >> 15) & 1) && cy == ((q[1] >> 15) & 1) && cz == ((q[2] >> 15) & 1);
-            float ev = gC[0] * va.y + gC[1] * va.z + gC[2] * va.w;
-            if (FEAT) ev += gV[0] * vb.x + gV[1] * vb.y + gV[2] * vb.z + gV[3] * vb.w;
-            const float sigma = corner_sum(wt * va.x);
-            const float ek = corner_sum(wt * ev);
-            if (ray_bits(dense, lane) == 0) return;
-            const float e = __expf(-sigma * kx);
-            const float ws = T * (1.0f - e);
-            rest -= ws * ek;
-            T *= e;
-            const float gsig = delta * (T * ek - rest);
-            // Slide the corner window to this sample's cell: corners on a
-            // trailing face (or all of them after a jump) are handed over, the
-            // survivors move to their new lane.
-            const int32_t move = (own >> 16) - wc;
-            const int32_t dd[3] = {dpp<kAxisX>(move), dpp<kAxisY>(move), dpp<kAxisZ>(move)};
-            const bool jump = wrank != w.r || ray_bits(abs(move) > 1, lane) != 0;
-            // the corner leaves on an axis the window moves along if it is on the trailing side
-            const bool lx = dd[0] != 0 && (dd[0] > 0) == (cx == 0);
-            const bool ly = dd[1] != 0 && (dd[1] > 0) == (cy == 0);
-            const bool lz = dd[2] != 0 && (dd[2] > 0) == (cz == 0);
-            hand_over(jump ? wrank >= 0 : lx || ly || lz);
-            if (jump) {
-                A = D = 0.0f;
-                wrank = w.r;
-                wid = g.rank_id[w.r];
-                const int32_t lin = g.rank_lin[w.r];
-                // lin < 2^18: the rounded product is never a half away from the quotient
-                const int32_t yz = int32_t((float(lin) + 0.5f) * inv_g), z = int32_t((float(yz) + 0.5f) * inv_g);
-                wb = (lin - mul_s24(yz, g.G)) | (yz - mul_s24(z, g.G)) << 8 | z << 16;
-            } else {
-                // a trailing corner takes its leading neighbour's sums, which start anew
-                float An = dpp<kFlipX>(A), Dn = dpp<kFlipX>(D);
-                A = dd[0] == 0 ? A : (lx ? An : 0.0f);
-                D = dd[0] == 0 ? D : (lx ? Dn : 0.0f);
-                An = dpp<kFlipY>(A), Dn = dpp<kFlipY>(D);
-                A = dd[1] == 0 ? A : (ly ? An : 0.0f);
-                D = dd[1] == 0 ? D : (ly ? Dn : 0.0f);
-                An = dpp<kFlipZ>(A), Dn = dpp<kFlipZ>(D);
-                A = dd[2] == 0 ? A : (lz ? An : 0.0f);
-                D = dd[2] == 0 ? D : (lz ? Dn : 0.0f);
-            }
-            wc += move;
-            A = fmaf(wt, ws, A);
-            D = fmaf(wt, gsig, D);
-            if (T <= t_end) live = false;
-        };
-        int32_t own = 0;
-        float4 va = make_float4(0.f, 0.f, 0.f, 0.f), vb = va;
-        if (AGG) {
-            while (todo != 0) {
-                fetch(own, va, vb);
-                take(own, va, vb);
-                if (!live) todo = 0;
-            }
-        } else {
-            // the next sample's voxels are read before the current one's work
-            bool more = todo != 0;
-            if (more) fetch(own, va, vb);
-            while (__any(more)) {
-                if (more) {
-                    const int32_t o1 = own;
-                    const float4 a1v = va, b1v = vb;
-                    more = todo != 0;
-                    if (more) fetch(own, va, vb);
-                    take(o1, a1v, b1v);
-                    if (!live) {
-                        todo = 0;
-                        more = false;
-                    }
+        while (AGG ? todo != 0 : __any(todo != 0)) {
+            if (todo != 0) {
+                const int32_t ahead = __builtin_ctz(todo);
+                todo &= todo - 1;
+                Fetched f;
+                f.own = w.q + mul_s24(ahead, w.s);
+                f.rank = w.r;
+                f.e = __shfl(my_e, (lane & ~7) | ahead);
+                f.template read<FEAT>(g, c, w.dist + g.dist_bytes);
+                if (st.take(a, c, f, lane, hand_over)) {
+                    live = false;
+                    todo = 0;
                 }
-                log_append();
             }
+            if (!AGG) log.append(a, lane);
         }
         if (live) {
             w.left -= reach;
@@ -952,10 +1352,308 @@ __global__ __launch_bounds__(64 * kAdjWaves) __attribute__((amdgpu_waves_per_eu(
         }
     }
     if (!AGG) {
-        hand_over(wrank >= 0);
-        log_append();
-        log_flush();
+        hand_over(st.wrank >= 0);
+        log.append(a, lane);
+        log.flush(a, lane);
     }
+}
+
+// Ray lists of up to 2^18 rays, in two launches.  k_backward_record walks the
+// rays, 16 lanes to each as the render does for few (with 4 the whole call
+// takes 8% longer for 16,384 rays, 2% for 262,144), and lists the samples in cells
+// with a zero distance byte: 16 bytes each, up to kBackwardListCap a ray; the
+// gradient kernels then run over the lists, so that rays of unequal length
+// and phase sit side by side without waiting for each other's walk.  A ray
+// with more samples is left to the kernels that walk.
+// List entry: position in the block on x, y, z (p << 16 | fraction, 23 bits
+// each) with the record's low 9 bits above x, its others above y, the active
+// flag above z; exp(-sigma delta).
+constexpr int kRecordLanes = 16;
+
+__global__ __launch_bounds__(256) void k_backward_record(BackwardArgs a) {
+    constexpr int L = kRecordLanes;
+    extern __shared__ uint2 s_occ[];
+    const GridArgs& g = a.grid;
+    for (int w = threadIdx.x; w < g.n_words; w += blockDim.x) s_occ[w] = g.occ[w];
+    __syncthreads();
+    const int lane = threadIdx.x & 63, me = lane & (L - 1);
+    const int64_t i = (int64_t(blockIdx.x) * blockDim.x + threadIdx.x) / L;
+    if (i >= a.n_rays) return;
+    int32_t n = 0;
+    // rays that composited nothing have no grid gradient
+    if (a.aux[8 * i + 7] >= 0.0f) {
+        int ci, px, py;
+        locate(a, a.ray_ids[i], ci, px, py);
+        int64_t o[3];
+        int32_t s[3];
+        float d[3];
+        ray_setup(a.cams[ci], g.N, px, py, o, s, d);
+        const uint32_t nc = uint32_t(g.Bc), ncc = nc * nc;
+        const int32_t ahead[3] = {me * s[0], me * s[1], me * s[2]};
+        int4* mine = a.list + i * kBackwardListCap;
+        FlatWalk w;
+        bool live = w.init(g, o, s);
+        // The list may end where the gradient will stop.  Its T is the product
+        // of the same factors in another order, so it differs by at most
+        // 2 * 512 * 2^-24 in proportion: past a margin of 2^-10 there is no doubt.
+        float T = 1.0f;
+        const float t_end = a.opts.early_stop ? a.opts.t_stop * (1.0f - 0x1p-10f) : -1.0f;
+        while (!(T < t_end)) {
+            while (live && w.left <= 0) live = w.enter(g, s_occ, s);
+            if (!live) break;
+            bool hit = false;
+            float decay = 1.0f;
+            int32_t reach = 0;
+            int4 e = make_int4(0, 0, 0, 0);
+            if (me < w.left) {
+                const int32_t q[3] = {w.q[0] + ahead[0], w.q[1] + ahead[1], w.q[2] + ahead[2]};
+                const int32_t p[3] = {q[0] >> 16, q[1] >> 16, q[2] >> 16};
+                const int32_t db = w.dist[cell_index(p, nc, ncc)];
+                hit = db == 0;
+                reach = me + (hit ? 1 : skip_steps(db, w.smax, w.inv_smax));
+                if (hit) {
+                    const int32_t fr[3] = {q[0] & 0xFFFF, q[1] & 0xFFFF, q[2] & 0xFFFF};
+                    const bool act = sample_decay(g, w.dist + g.dist_bytes, p, fr, a.opts.nn_gate != 0, decay);
+                    e = make_int4(q[0] | (w.r & 511) << 23, q[1] | (w.r >> 9) << 23, q[2] | int(act) << 23,
+                                  __float_as_int(decay));
+                    decay = act ? decay : 1.0f;
+                }
+            }
+            const uint32_t hits = uint32_t(__ballot(hit) >> (lane & ~(L - 1))) & ((1u << L) - 1u);
+            const int32_t at = n + __builtin_popcount(hits & ((1u << me) - 1u));
+            if (hit && at < kBackwardListCap) mine[at] = e;
+            n += __builtin_popcount(hits);
+            if (hits != 0) T *= group_product<L>(decay);
+            reach = min(group_max<L>(reach), w.left);
+            w.left -= reach;
+#pragma unroll
+            for (int c = 0; c < 3; ++c) w.q[c] += mul_s24(reach, s[c]);
+        }
+    }
+    if (me == 0) a.list_count[i] = n;
+}
+
+// A ray's list in its 8 lanes, read ahead: lane l of a quad holds word l % 4 of
+// an entry.
+template <bool FEAT>
+struct ListReader {
+    const int32_t* at;  // own word of entry 0
+    int32_t n;          // listed samples to take (0: none, or left to the kernels that walk)
+    int32_t word;       // own word of the entry after `f`
+    Fetched f;
+    bool active;
+
+    __device__ __forceinline__ void init(const BackwardArgs& a, const CornerLane& c, int64_t i, bool live) {
+        const int32_t count = live ? a.list_count[i] : 0;
+        n = count <= kBackwardListCap ? count : 0;
+        at = reinterpret_cast<const int32_t*>(a.list + i * kBackwardListCap) + (c.l & 3);
+        word = n > 0 ? at[0] : 0;
+        if (n > 0) load(a.grid, c, 0);
+    }
+
+    // Entry j (its words are in `word`) becomes f, and entry j + 1's are read.
+    __device__ __forceinline__ void load(const GridArgs& g, const CornerLane& c, int32_t j) {
+        const int32_t x = dpp<kAxisX>(word), y = dpp<kAxisY>(word), z = dpp<kAxisZ>(word);
+        f.own = ((c.l & 3) == 3 ? z : word) & 0x7fffff;
+        f.rank = int32_t(uint32_t(x) >> 23 | uint32_t(y) >> 23 << 9);
+        f.e = __int_as_float(dpp<0xFF>(word));  // quad_perm 3, 3, 3, 3
+        active = (uint32_t(z) >> 23) != 0;
+        word = j + 1 < n ? at[4 * (j + 1)] : 0;
+        f.template read<FEAT>(g, c, g.rec + (uint64_t(uint32_t(f.rank) * uint32_t(g.rec_stride >> 8)) << 8) + g.dist_bytes);
+    }
+};
+
+// Scattered lists: gradients through the wavefronts' logs, the next sample's
+// voxels read before the current one's work.  Bound by the latency of those
+// loads and by the longest of 8 rays.  65,536 rays, 1024^3, packed, walk
+// included: one lane to a ray 2.35 ms, this 1.15.
+constexpr int kListWaves = 4;
+
+template <bool FEAT>
+__global__ __launch_bounds__(64 * kListWaves) void k_backward_scattered(BackwardArgs a) {
+    __shared__ int4 s_log[kListWaves][kLogEntries];
+    __shared__ float s_gch[kListWaves][8][8];
+    const GridArgs& g = a.grid;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const CornerLane c(g, lane);
+    const int64_t i = (int64_t(blockIdx.x) * kListWaves + wave) * 8 + (lane >> 3);
+    CornerRay<FEAT> st;
+    bool going = st.setup(a, i, i < a.n_rays);
+    s_gch[wave][lane >> 3][c.l] = st.channel(c.l);
+    WaveLog<kLogEntries> log = {s_log[wave], s_gch[wave]};
+    auto hand_over = [&](bool leave) {
+        log.vi = st.template voxel<int32_t>(g, c, leave);
+        log.A = st.A;
+        log.Ds = g.sigma_scale * st.D;
+    };
+    ListReader<FEAT> rd;
+    rd.init(a, c, i, going);
+    for (int32_t j = 0; __any(going && j < rd.n); ++j) {
+        if (going && j < rd.n) {
+            const Fetched now = rd.f;
+            const bool act = rd.active;
+            if (j + 1 < rd.n) rd.load(g, c, j + 1);
+            if (act && st.take(a, c, now, lane, hand_over)) going = false;
+        }
+        log.append(a, lane);
+    }
+    hand_over(st.wrank >= 0);
+    log.append(a, lane);
+    log.flush(a, lane);
+}
+
+// Patch lists: 64 neighbouring rays to a workgroup, 8 lanes to each, one listed
+// sample to a step, their gradients summed in one table.  The table's new
+// voxels get their slots as one lane per ray with compare-and-swaps would give
+// them out, corner by corner, probe by probe, ray by ray (k_march_backward), so
+// that the same hand-overs find the table full; but in all lanes at once.  A
+// voxel without an entry asks for its first free slot, the slot goes to the
+// earliest of those that ask (atomic minimum of corner, probe, ray), who lost
+// it asks for the next, until nobody has to.  What finds no slot goes to the
+// wavefront's log.  Bound by the longest of the patches, some 200 steps where
+// rays graze the surface, and there by the step's chain of loads, LDS round
+// trips and barriers.
+//   16,384 rays, 512^3       one lane to a ray  2.0 ms   this 0.75 (+ 0.05 for the list)
+//   262,144 rays, 512^3, whole backward call    8.0 ms        2.5
+constexpr int kPatchWaves = 8;
+constexpr int kPatchLog = 160;
+
+template <bool FEAT>
+__global__ __launch_bounds__(64 * kPatchWaves) void k_backward_patches(BackwardArgs a) {
+    __shared__ int32_t s_key[kAggSlots];
+    __shared__ float s_val[8 * kAggSlots];
+    __shared__ unsigned long long s_ask[kAggSlots];  // the earliest that asks for the slot: order << 32 | voxel
+    __shared__ int4 s_log[kPatchWaves][kPatchLog];
+    __shared__ float s_gch[kPatchWaves][8][8];
+    __shared__ int32_t s_on[3], s_again[3], s_used;
+    const GridArgs& g = a.grid;
+    for (int sl = threadIdx.x; sl < kAggSlots; sl += blockDim.x) {
+        s_key[sl] = -1;
+        s_ask[sl] = ~0ull;
+#pragma unroll
+        for (int ch = 0; ch < 8; ++ch) s_val[ch * kAggSlots + sl] = 0.0f;
+    }
+    if (threadIdx.x < 3) s_on[threadIdx.x] = s_again[threadIdx.x] = 0;
+    if (threadIdx.x == 3) s_used = 0;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t base = int64_t(blockIdx.x) * 64;
+    AggTable tab = {s_key, s_val, 0.0f, 0.0f};
+    {  // every wavefront finds the table's scale, from all 64 rays
+        float m = 0.0f;
+        const int64_t i = base + lane;
+        if (i < a.n_rays && a.aux[8 * i + 7] >= 0.0f) {
+            const float* v = FEAT ? a.gcv + 8 * i : a.grad_rgba + 4 * i;
+#pragma unroll
+            for (int ch = 0; ch < (FEAT ? 7 : 3); ++ch) m = fmaxf(m, fabsf(v[ch]));
+        }
+        agg_scale(tab, wave_max(m));
+    }
+    const CornerLane c(g, lane);
+    const int corner = c.cx | c.cy << 1 | c.cz << 2, ray = wave * 8 + (lane >> 3);
+    CornerRay<FEAT> st;
+    bool going = st.setup(a, base + ray, base + ray < a.n_rays);
+    s_gch[wave][lane >> 3][c.l] = st.channel(c.l);
+    WaveLog<kPatchLog> log = {s_log[wave], s_gch[wave]};
+    ListReader<FEAT> rd;
+    rd.init(a, c, base + ray, going);
+    __syncthreads();
+
+    // All threads: adds what the lanes with vi >= 0 hand over.
+    int round = 0;
+    auto enter = [&](int32_t vi, float A, float Ds) {
+        const uint32_t h = agg_hash(vi);
+        int pr = kAggProbes;
+        bool mine = false, asks = false;
+        if (vi >= 0) {
+#pragma nounroll
+            for (int p0 = 0; p0 < kAggProbes; p0 += 4) {  // four slots to a round trip
+                int32_t k[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) k[u] = s_key[(h + uint32_t(p0 + u)) & (kAggSlots - 1)];
+#pragma unroll
+                for (int u = 3; u >= 0; --u) {
+                    const bool end = k[u] == vi || k[u] == -1;
+                    pr = end ? p0 + u : pr;
+                    mine = end ? k[u] == vi : mine;
+                }
+                if (pr < kAggProbes) break;
+            }
+            asks = pr < kAggProbes && !mine;
+        }
+        int sl = int((h + uint32_t(pr)) & (kAggSlots - 1));
+        bool won = false;
+        for (;;) {
+            // slots are looked up and asked for up to this barrier, read up to
+            // the next and taken after it
+            const uint32_t order = uint32_t(corner << 10 | pr << 6 | ray);
+            if (asks) atomicMin(&s_ask[sl], (unsigned long long)(order) << 32 | uint32_t(vi));
+            __syncthreads();
+            bool lost = false;
+            if (asks) {
+                const unsigned long long first = s_ask[sl];
+                won = uint32_t(first >> 32) == order;
+                lost = uint32_t(first) != uint32_t(vi);
+            }
+            if (__any(lost) && lane == 0) s_again[round] = 1;
+            const int next = round == 2 ? 0 : round + 1;
+            if (threadIdx.x == 0) s_again[next] = 0;  // last read a barrier ago
+            __syncthreads();
+            const bool again = s_again[round] != 0;
+            round = next;
+            if (!again) break;
+            if (lost) {
+                do {
+                    ++pr;
+                    sl = (sl + 1) & (kAggSlots - 1);
+                } while (pr < kAggProbes && s_key[sl] != -1);
+                asks = pr < kAggProbes;
+            }
+        }
+        if (asks && won) {
+            s_key[sl] = vi;
+            s_ask[sl] = ~0ull;
+        }
+        const int fresh = __builtin_popcountll(__ballot(asks && won));
+        if (lane == 0 && fresh != 0) atomicAdd(&s_used, fresh);
+        if (mine || asks) {
+            agg_add<FEAT>(tab, sl, Ds, A, st.gC, st.gV);
+        } else if (vi >= 0) {
+            log.vi = vi;
+            log.A = A;
+            log.Ds = Ds;
+        }
+        log.append(a, lane);
+        __syncthreads();
+    };
+
+    for (int32_t j = 0;; ++j) {
+        const bool more = going && j < rd.n;
+        int32_t vi = -1;
+        float A = 0.0f, Ds = 0.0f;
+        if (more) {
+            const Fetched now = rd.f;
+            const bool act = rd.active;
+            if (j + 1 < rd.n) rd.load(g, c, j + 1);
+            if (act) going = !st.take(a, c, now, lane, [&](bool leave) {
+                vi = st.template voxel<int32_t>(g, c, leave);
+                A = st.A;
+                Ds = g.sigma_scale * st.D;
+            });
+        }
+        if (__any(going && j + 1 < rd.n) && lane == 0) s_on[j % 3] = 1;
+        if (threadIdx.x == 0) s_on[(j + 1) % 3] = 0;  // last read a step ago
+        enter(vi, A, Ds);
+        if (s_used >= kAggFlushAt) {
+            __syncthreads();
+            agg_flush<FEAT>(a, tab, threadIdx.x, blockDim.x);
+            if (threadIdx.x == 0) s_used = 0;
+            __syncthreads();
+        }
+        if (s_on[j % 3] == 0) break;
+    }
+    enter(st.template voxel<int32_t>(g, c, st.wrank >= 0), st.A, g.sigma_scale * st.D);
+    log.flush(a, lane);
+    agg_flush<FEAT>(a, tab, threadIdx.x, blockDim.x);
 }
 
 // Column sums of the [rows][883] partial-gradient matrix into out (which
@@ -978,9 +1676,6 @@ __global__ __launch_bounds__(256) void k_reduce_rows(const float* __restrict__ p
     if (ty == 0 && col < kMlpParams) atomicAdd(out + col, (part[0][tx] + part[1][tx]) + (part[2][tx] + part[3][tx]));
 }
 
-// The longest list that is taken to be scattered.
-constexpr int64_t kScatteredMaxRays = int64_t(1) << 18;
-
 int backward_partial_rows(int n_groups) { return n_groups * kBwdWaves; }
 
 bool backward_aggregates(const GridArgs& g) {
@@ -998,29 +1693,62 @@ hipError_t launch_backward(const BackwardArgs& a, int n_groups, hipStream_t s) {
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     if (a.mlp_only) return hipSuccess;
-    // Neighbouring rays share voxels and go through the table (half a tile to
-    // a workgroup): whole views, patch lists, and lists so long that most of
-    // the pixels must be in them.  Scattered rays share few and go through
-    // the log, as do grids whose voxel indices exceed the table's int32 keys.
-    const bool agg = backward_aggregates(a.grid) && (!a.ray_ids || a.patch_rays || a.n_rays > kScatteredMaxRays);
     const bool feat = a.mlp_mode != kMlpOff;
-    static_assert(kAdjWaves * 8 == 32, "two workgroups to 64 rays");
-    const int64_t wgs = 2 * (a.ray_ids ? (a.n_rays + 63) / 64 : a.total_tiles);
-    const dim3 wg{64 * kAdjWaves};
-    const size_t lds = (size_t(a.grid.n_words) + 1) / 2 * 16 +
-                       (agg ? size_t(kAggWords) * 4 : size_t(kAdjWaves) * kLogEntries * sizeof(int4));
-    // a launch holds fewer than 2^32 lanes
-    constexpr int64_t kMaxGroups = int64_t(1) << 22;
-    BackwardArgs b = a;
-    for (b.first_group = 0; b.first_group < wgs; b.first_group += kMaxGroups) {
-        const dim3 grid{unsigned(wgs - b.first_group < kMaxGroups ? wgs - b.first_group : kMaxGroups)};
-        if (feat && agg) hipLaunchKernelGGL((k_adjoint<true, true>), grid, wg, lds, s, b);
-        else if (feat) hipLaunchKernelGGL((k_adjoint<true, false>), grid, wg, lds, s, b);
-        else if (agg) hipLaunchKernelGGL((k_adjoint<false, true>), grid, wg, lds, s, b);
-        else hipLaunchKernelGGL((k_adjoint<false, false>), grid, wg, lds, s, b);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
+    auto check = [] { return hipGetLastError(); };
+    // Eight lanes to a ray, walking.
+    auto walk8 = [&](bool agg) {
+        const int64_t wgs = 2 * (a.ray_ids ? (a.n_rays + 63) / 64 : a.total_tiles);
+        const size_t lds = (size_t(a.grid.n_words) + 1) / 2 * 16 +
+                           (agg ? size_t(kAggWords) * 4 : size_t(kAdjWaves) * kLogEntries * sizeof(int4));
+        static_assert(kAdjWaves * 8 == 32, "two workgroups to 64 rays");
+        constexpr int64_t kMaxGroups = int64_t(1) << 22;  // a launch holds fewer than 2^32 lanes
+        BackwardArgs b = a;
+        for (b.first_group = 0; b.first_group < wgs; b.first_group += kMaxGroups) {
+            const dim3 n{unsigned(wgs - b.first_group < kMaxGroups ? wgs - b.first_group : kMaxGroups)};
+            const dim3 wg{64 * kAdjWaves};
+            if (feat && agg) hipLaunchKernelGGL((k_adjoint<true, true>), n, wg, lds, s, b);
+            else if (feat) hipLaunchKernelGGL((k_adjoint<true, false>), n, wg, lds, s, b);
+            else if (agg) hipLaunchKernelGGL((k_adjoint<false, true>), n, wg, lds, s, b);
+            else hipLaunchKernelGGL((k_adjoint<false, false>), n, wg, lds, s, b);
+            if ((e = check()) != hipSuccess) return e;
+        }
+        return hipSuccess;
+    };
+    // One lane to a ray, walking.
+    auto walk1 = [&]() {
+        const size_t lds = size_t(a.grid.n_words) * sizeof(uint2) + size_t(kAggLdsWords) * 4;
+        const int64_t waves = a.ray_ids ? (a.n_rays + 63) / 64 : a.total_tiles;
+        const dim3 n{unsigned((waves + kAggWaves - 1) / kAggWaves)}, wg{64 * kAggWaves};
+        if (feat) hipLaunchKernelGGL(k_march_backward<true>, n, wg, lds, s, a);
+        else hipLaunchKernelGGL(k_march_backward<false>, n, wg, lds, s, a);
+        return check();
+    };
+    if (!backward_aggregates(a.grid)) return walk8(false);
+    // Whole views: eight lanes to a ray halve the time (eight 800x800 views,
+    // 512^3: 17.5 against 27 ms; two of 160x160: 2.2 against 4.5 for the whole
+    // call), but they enter the table in another order.  Where pixels are
+    // further apart than voxels a tile's voxels don't fit the table, order
+    // decides what overflows and goes unrounded, and the feature gradients
+    // would differ by the table's own rounding, 4e-5 of their norm at 160x160
+    // on 512^3, 1.5e-6 at 800x800: such views, like lists of more rays than
+    // the launch keeps samples for, take one lane per ray.
+    if (!a.list) return a.dense_views ? walk8(true) : walk1();
+    const size_t occ = size_t(a.grid.n_words) * sizeof(uint2);
+    const dim3 n{unsigned((a.n_rays * kRecordLanes + 255) / 256)}, wg{256};
+    hipLaunchKernelGGL(k_backward_record, n, wg, occ, s, a);
+    if ((e = check()) != hipSuccess) return e;
+    if (a.patch_rays) {
+        const dim3 n{unsigned((a.n_rays + 63) / 64)}, wg{64 * kPatchWaves};
+        if (feat) hipLaunchKernelGGL(k_backward_patches<true>, n, wg, 0, s, a);
+        else hipLaunchKernelGGL(k_backward_patches<false>, n, wg, 0, s, a);
+    } else {
+        const dim3 n{unsigned((a.n_rays + 8 * kListWaves - 1) / (8 * kListWaves))}, wg{64 * kListWaves};
+        if (feat) hipLaunchKernelGGL(k_backward_scattered<true>, n, wg, 0, s, a);
+        else hipLaunchKernelGGL(k_backward_scattered<false>, n, wg, 0, s, a);
     }
-    return hipSuccess;
+    if ((e = check()) != hipSuccess) return e;
+    // the rays with more samples than the list holds
+    return a.patch_rays ? walk1() : walk8(false);
 }
 
 hipError_t launch_reduce_mlp(const float* partial, int rows, float* out, hipStream_t s) {

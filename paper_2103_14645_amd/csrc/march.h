@@ -522,4 +522,36 @@ __host__ __device__ __forceinline__ int32_t occupied_samples_on_ray(const GridAr
     return count;
 }
 
+// Reductions over groups of L = 2, 4 or 16 lanes (all lanes of a live group
+// run together).
+template <int CTRL>
+__device__ __forceinline__ int32_t dpp_max(int32_t v) {
+    return max(v, __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, true));
+}
+
+// Largest value (>= 0) of the group, in every lane of it.
+template <int L>
+__device__ __forceinline__ int32_t group_max(int32_t v) {
+    v = dpp_max<0xB1>(v);                          // quad_perm 1, 0, 3, 2
+    if constexpr (L >= 4) v = dpp_max<0x4E>(v);    // quad_perm 2, 3, 0, 1
+    if constexpr (L == 16) {
+        v = dpp_max<0x141>(v);  // row_half_mirror
+        v = dpp_max<0x140>(v);  // row_mirror
+    }
+    return v;
+}
+
+// Product over the group, in every lane of it.
+template <int L>
+__device__ __forceinline__ float group_product(float v) {
+    auto times = [&](float& x, int y) { x *= __int_as_float(y); };
+    times(v, __builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xf, 0xf, true));
+    if constexpr (L >= 4) times(v, __builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4E, 0xf, 0xf, true));
+    if constexpr (L == 16) {
+        times(v, __builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x141, 0xf, 0xf, true));
+        times(v, __builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x140, 0xf, 0xf, true));
+    }
+    return v;
+}
+
 }  // namespace snerg

@@ -263,23 +263,6 @@ __device__ __forceinline__ float group_bcast(float v) {
     return __int_as_float(y);
 }
 
-template <int CTRL>
-__device__ __forceinline__ int32_t dpp_max(int32_t v) {
-    return max(v, __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, true));
-}
-
-// Largest value (>= 0) of the group, in every lane of it.
-template <int L>
-__device__ __forceinline__ int32_t group_max(int32_t v) {
-    v = dpp_max<0xB1>(v);                          // quad_perm 1, 0, 3, 2
-    if constexpr (L >= 4) v = dpp_max<0x4E>(v);    // quad_perm 2, 3, 0, 1
-    if constexpr (L == 16) {
-        v = dpp_max<0x141>(v);  // row_half_mirror
-        v = dpp_max<0x140>(v);  // row_mirror
-    }
-    return v;
-}
-
 // f(integral_constant J) for J = 0 .. N - 1
 template <int N, int J = 0, typename F>
 __device__ __forceinline__ void unrolled(F&& f) {

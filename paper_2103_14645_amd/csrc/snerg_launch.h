@@ -69,7 +69,16 @@ struct BackwardArgs {
     int32_t patch_rays;    // ray list in groups of 64 neighbouring rays
     int32_t grad_packed;   // grid gradients as grad_dens[voxel][8] (grad_rgb, grad_feat unused)
     int64_t first_group;   // set by the launch: workgroup index of the launch's first
+    int32_t dense_views;   // whole views whose pixels lie closer than the voxels
+    // ray lists of at most kBackwardListMaxRays rays (null: one re-march): per
+    // list entry kBackwardListCap listed samples, and their count
+    int4* list;
+    int32_t* list_count;
 };
+
+// (2 GB of samples at the most)
+constexpr int kBackwardListCap = 512;
+constexpr int64_t kBackwardListMaxRays = int64_t(1) << 18;
 
 // Baking (Section 5.3, 5.4).
 struct BakeCullPlan {

@@ -166,8 +166,8 @@ typedef struct {
 
 /* Launch shape used by the forward kernels (chosen by snerg_autotune).  It
  * sets how pixels are dealt to wavefronts, never a result.  Renders of up to
- * 3 * 2^17 rays, and most of a SNERG_F32 grid, give each ray several lanes of a
- * wavefront; of the shape they use only the tile. */
+ * 2^16 rays (up to 5 * 2^16 on large grids), and most of a SNERG_F32 grid, give
+ * each ray several lanes of a wavefront; of the shape they use only the tile. */
 typedef struct {
     int32_t tile_w, tile_h;   /* pixels per wavefront tile, tile_w * tile_h == 64 */
     int32_t waves_per_group;  /* wavefronts per workgroup: 1, 2 or 4 */

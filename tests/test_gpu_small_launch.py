@@ -43,7 +43,7 @@ def test_list_bitwise(kind, kw):
         ref, _ = S.render_counted(H.handle(), dg, mlp, cams, ray_ids=ids, opts=opts)
         out, raux = render(dg, mlp, cams, ids, opts)
         assert torch.equal(out, ref)
-    for n in (1, 3, 4, 5, 63, 1000, 32768, 32769, 65536, 65537, 393216, 393217, 1 << 20):
+    for n in (1, 3, 4, 5, 63, 1000, 32768, 32769, 65536, 65537, 131072, 131073, 393216, 393217, 1 << 20):
         out, aux = render(dg, mlp, cams, ids[:n].contiguous(), opts)
         assert torch.equal(out, ref[:n]) and torch.equal(aux, raux[:n]), (kind, kw, n)
 

@@ -54,6 +54,20 @@ __device__ __forceinline__ void sync_wave() {
     __builtin_amdgcn_wave_barrier();
 }
 
+// Whether `p` holds in any thread of the workgroup; `word` is LDS that nothing
+// else uses yet (__syncthreads_or takes LDS of its own, and at 512^3 in blocks
+// of 16 two workgroups of k_march_backward fill a compute unit's to the byte:
+// 7.0 ms against 10.8).
+__device__ __forceinline__ bool any_in_group(int32_t* word, bool p) {
+    if (threadIdx.x == 0) *word = 0;
+    __syncthreads();
+    if (p) *word = 1;
+    __syncthreads();
+    const bool any = *word != 0;
+    __syncthreads();
+    return any;
+}
+
 __device__ __forceinline__ void locate(const BackwardArgs& a, int64_t r, int& ci, int& px, int& py) {
     ci = find_camera_by_ray(a.cams, a.n_cams, r);
     const int64_t local = r - a.cams[ci].ray_offset;
@@ -485,45 +499,54 @@ __device__ __forceinline__ void agg_hand_over(const BackwardArgs& a, const AggTa
 }
 
 // `threads` threads in whole wavefronts, with nobody else at the table: every
-// used entry goes to device memory, the table is cleared.  gfx950 serves a wavefront's float atomics
-// per 64-byte line (measured: about 21 G lines per second whether a line
-// carries one lane's add or sixteen), so the lanes are laid across the
-// entries' channels, not the entries: lane l takes entry l / 4 of a group of
-// 16 and within it channels l % 4 and l % 4 + 4, so that one instruction adds
-// an entry's density and colour (two lines) and the next its four features
-// (one line), where one lane per entry would touch seven lines.  With packed
-// gradients an entry's eight sums share one line: eight lanes per entry (four
-// without features), one instruction per group.
-template <bool FEAT>
-__device__ __forceinline__ void agg_flush(const BackwardArgs& a, const AggTable& t, int tid, int threads) {
+// used entry goes to device memory, the table is cleared.  gfx950 serves a
+// wavefront's float atomics per 64-byte line (measured: about 21 G lines per
+// second whether a line carries one lane's add or sixteen), so the lanes are
+// laid across the entries' channels, not the entries: lane l takes entry l / 4
+// of a group of 16 and within it channels l % 4 and l % 4 + 4, so that one
+// instruction adds an entry's density and colour (two lines) and the next its
+// four features (one line), where one lane per entry would touch seven lines.
+// With packed gradients an entry's eight sums share one line: eight lanes per
+// entry (four without features), one instruction per group.
+// kC: lanes per entry; kBatch: entries of a lane whose keys and values are read
+// together, 4 where one wavefront flushes alone, in a chain of LDS reads.
+template <bool FEAT, int kC, int kBatch>
+__device__ __forceinline__ void agg_flush_by(const BackwardArgs& a, const AggTable& t, int tid, int threads) {
     int32_t* iv = reinterpret_cast<int32_t*>(t.val);
-    auto take = [&](int sl, int c) {
-        float v;
-        if (c == 0) {
-            v = t.val[sl];
-            t.val[sl] = 0.0f;
-        } else {
-            v = float(iv[c * kAggSlots + sl]) * t.dq;
-            iv[c * kAggSlots + sl] = 0;
+    auto value = [&](int sl, int c) { return c == 0 ? t.val[sl] : float(iv[c * kAggSlots + sl]) * t.dq; };
+    constexpr bool kTwo = FEAT && kC == 4;
+    const int c = tid & (kC - 1), step = threads / kC;
+    for (int s0 = tid / kC; s0 < kAggSlots; s0 += kBatch * step) {
+        // the lanes of an entry sit in one wavefront and read its key before
+        // any of them frees it
+        int32_t key[kBatch];
+        float v0[kBatch], v1[kBatch];
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+            const int sl = s0 + u * step;
+            key[u] = t.key[sl];
+            v0[u] = value(sl, c);
+            v1[u] = kTwo ? value(sl, c + 4) : 0.0f;
         }
-        return v;
-    };
-    // the lanes of an entry sit in one wavefront and read its key before any
-    // of them frees it
-    const int kC = a.grad_packed && FEAT ? 8 : 4;  // lanes per entry
-    const int c = tid & (kC - 1);
-    for (int sl = tid / kC; sl < kAggSlots; sl += threads / kC) {
-        const int32_t key = t.key[sl];
-        if (key >= 0) {
-            const float v0 = take(sl, c);
-            if (v0 != 0.0f) unsafeAtomicAdd(grad_channel(a, key, c), v0);
-            if (FEAT && kC == 4) {
-                const float v1 = take(sl, c + 4);
-                if (v1 != 0.0f) unsafeAtomicAdd(grad_channel(a, key, c + 4), v1);
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+            const int sl = s0 + u * step;
+            if (key[u] < 0) continue;
+            if (v0[u] != 0.0f) unsafeAtomicAdd(grad_channel(a, key[u], c), v0[u]);
+            iv[c * kAggSlots + sl] = 0;  // (zero bits are 0.0f too)
+            if (kTwo) {
+                if (v1[u] != 0.0f) unsafeAtomicAdd(grad_channel(a, key[u], c + 4), v1[u]);
+                iv[(c + 4) * kAggSlots + sl] = 0;
             }
             if (c == 0) t.key[sl] = -1;
         }
     }
+}
+
+template <bool FEAT, int kBatch = 1>
+__device__ __forceinline__ void agg_flush(const BackwardArgs& a, const AggTable& t, int tid, int threads) {
+    if (FEAT && a.grad_packed) agg_flush_by<FEAT, 8, kBatch>(a, t, tid, threads);
+    else agg_flush_by<FEAT, 4, kBatch>(a, t, tid, threads);
 }
 
 // ------------------------------------------------------ one lane to a ray
@@ -719,7 +742,7 @@ __device__ __forceinline__ AggTable agg_table(uint2* s_occ, int n_words, int wav
 template <bool FEAT>
 __device__ __forceinline__ void wave_flush(const BackwardArgs& a, const AggTable& t, int lane) {
     sync_wave();
-    agg_flush<FEAT>(a, t, lane, 64);
+    agg_flush<FEAT, 4>(a, t, lane, 64);
     sync_wave();
 }
 
@@ -778,7 +801,7 @@ __global__ __launch_bounds__(64 * kAggWaves) void k_march_backward(BackwardArgs 
             i = r = c.ray_offset + int64_t(py) * c.W + px;
         }
     }
-    if (a.list && !__syncthreads_or(live)) return;
+    if (a.list && !any_in_group(reinterpret_cast<int32_t*>(s_occ), live)) return;
     for (int w = threadIdx.x; w < g.n_words; w += blockDim.x) s_occ[w] = g.occ[w];
     AggTable tab = agg_table(s_occ, g.n_words, wave, lane);
     __syncthreads();
@@ -1222,7 +1245,7 @@ __global__ __launch_bounds__(64 * kAdjWaves) __attribute__((amdgpu_waves_per_eu(
         if (threadIdx.x == 0) s_max = m;
     }
     bool live = ray_of((int(u & 1) * kAdjWaves + wave) * 8 + (lane >> 3), i, ci, px, py);
-    if (a.list && !__syncthreads_or(live)) return;
+    if (a.list && !any_in_group(reinterpret_cast<int32_t*>(s_occ), live)) return;
     for (int w = threadIdx.x; w < g.n_words; w += blockDim.x) s_occ[w] = g.occ[w];
     const CornerLane c(g, lane);
     AggTable tab = {nullptr, nullptr, 0.0f, 0.0f};

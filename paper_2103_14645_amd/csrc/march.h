@@ -79,13 +79,17 @@ __device__ __forceinline__ half2_t byte_pair(uint32_t x) {
 // Trilinear sample from loaded uint8 corners.  Every non-zero weight is a
 // product of fractions >= 2^-16 (no underflow) and densities are
 // non-negative, so "some corner has non-zero density and non-zero weight"
-// is exactly "the FP32 density sum is positive".  The bytes are zero-extended to
-// pairs of halves, 2^-24 of their value, and the weights carry 2^24: the mixed
-// multiply-adds read the halves in place, 32 byte permutes where one conversion
-// per byte took 64 instructions, and every product and sum is the same bit for
-// bit.  Sixteen 1080p views of a 1024^3 shell 21.0 -> 20.4 ms (10% fewer vector
-// instructions; the render is then bound by both issue, VALUs 88% busy, and the
-// latency of the samples' loads at four wavefronts per SIMD).
+// is exactly "the FP32 density sum is positive".
+// kPairs: the bytes are zero-extended to pairs of halves, 2^-24 of their value,
+// and the weights carry 2^24: mixed multiply-adds read the halves in place, 32
+// byte permutes where one conversion per byte takes 64 instructions, and every
+// product and sum is the same bit for bit.  It takes ten registers more.  The
+// one-lane render with the FP16 network keeps its wavefronts (four or five per
+// SIMD): sixteen 1080p views of a 1024^3 shell 21.0 -> 20.4 ms, 10% fewer
+// vector instructions, then bound by both issue (VALUs 88% busy) and the
+// latency of the samples' loads.  The others lose one: 800x800 frame of 512^3,
+// FP32 network, six to five, 420 -> 424 us.
+template <bool kPairs = false>
 __device__ __forceinline__ void interp_u8(const Corners8& cn, const int32_t fr[3], Sample& smp) {
     uint2 v[8];
 #pragma unroll
@@ -94,20 +98,31 @@ __device__ __forceinline__ void interp_u8(const Corners8& cn, const int32_t fr[3
         v[2 * r + 1] = make_uint2(cn.row[r].z, cn.row[r].w);
     }
     float w[8];
-    corner_weights(fr, w, 0x1p24f);
+    corner_weights(fr, w, kPairs ? 0x1p24f : 1.0f);
     float sd = 0.f, r0 = 0.f, r1 = 0.f, r2 = 0.f, f0 = 0.f, f1 = 0.f, f2 = 0.f, f3 = 0.f;
 #pragma unroll
     for (int c = 0; c < 8; ++c) {
-        const half2_t a = byte_pair<0>(v[c].x), b = byte_pair<2>(v[c].x);
-        const half2_t d = byte_pair<0>(v[c].y), e = byte_pair<2>(v[c].y);
-        sd = fmaf(w[c], float(a.x), sd);
-        r0 = fmaf(w[c], float(a.y), r0);
-        r1 = fmaf(w[c], float(b.x), r1);
-        r2 = fmaf(w[c], float(b.y), r2);
-        f0 = fmaf(w[c], float(d.x), f0);
-        f1 = fmaf(w[c], float(d.y), f1);
-        f2 = fmaf(w[c], float(e.x), f2);
-        f3 = fmaf(w[c], float(e.y), f3);
+        if constexpr (kPairs) {
+            const half2_t a = byte_pair<0>(v[c].x), b = byte_pair<2>(v[c].x);
+            const half2_t d = byte_pair<0>(v[c].y), e = byte_pair<2>(v[c].y);
+            sd = fmaf(w[c], float(a.x), sd);
+            r0 = fmaf(w[c], float(a.y), r0);
+            r1 = fmaf(w[c], float(b.x), r1);
+            r2 = fmaf(w[c], float(b.y), r2);
+            f0 = fmaf(w[c], float(d.x), f0);
+            f1 = fmaf(w[c], float(d.y), f1);
+            f2 = fmaf(w[c], float(e.x), f2);
+            f3 = fmaf(w[c], float(e.y), f3);
+        } else {
+            sd += w[c] * ubyte(v[c].x, 0);
+            r0 += w[c] * ubyte(v[c].x, 1);
+            r1 += w[c] * ubyte(v[c].x, 2);
+            r2 += w[c] * ubyte(v[c].x, 3);
+            f0 += w[c] * ubyte(v[c].y, 0);
+            f1 += w[c] * ubyte(v[c].y, 1);
+            f2 += w[c] * ubyte(v[c].y, 2);
+            f3 += w[c] * ubyte(v[c].y, 3);
+        }
     }
     smp.sigma_raw = sd;
     smp.rgb[0] = r0; smp.rgb[1] = r1; smp.rgb[2] = r2;

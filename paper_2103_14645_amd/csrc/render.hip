@@ -44,7 +44,7 @@ struct RayCount {
     __device__ __forceinline__ void inblock(int32_t n) { in_block += n; }
 };
 
-template <int VT, bool COUNT>
+template <int VT, bool COUNT, bool kPairs>
 __device__ __forceinline__ void march_composite(const RenderArgs& a, const uint2* occ, const int64_t o[3],
                                                 const int32_t s[3], RayAccum& st, RayCount& rc) {
     const GridArgs& g = a.grid;
@@ -66,7 +66,7 @@ __device__ __forceinline__ void march_composite(const RenderArgs& a, const uint2
                     load_corners_u8(cell, g.Bp, cn);
                     cached = cell;
                 }
-                interp_u8(cn, fr, smp);
+                interp_u8<kPairs>(cn, fr, smp);
                 if (nn_gate) smp.active = nearest_nonzero_u8(cn, fr);
             } else {
                 gather_f32(vox, g.Bp, p, fr, smp, nn_gate);
@@ -172,7 +172,7 @@ __device__ __forceinline__ void render_ray(const RenderArgs& a, const uint2* occ
         // keep the direction as three floats from here on (left alone, the
         // compiler carries its FP64 form through the march)
         asm volatile("" : "+v"(d[0]), "+v"(d[1]), "+v"(d[2]));
-        march_composite<VT, COUNT>(a, occ, o, s, st, rc);
+        march_composite<VT, COUNT, MLP == kMlpF16>(a, occ, o, s, st, rc);
     }
     finish_ray<MLP>(a, valid, st, d, out_idx);
     if (COUNT && valid) {

@@ -13,6 +13,7 @@
 #include <vector>
 
 #include "snerg.h"
+#include "routes.h"
 #include "snerg_launch.h"
 
 using namespace snerg;
@@ -790,12 +791,9 @@ int snerg_render_backward(snerg_handle* h, const snerg_grid* grid, const float* 
     a.mlp_only = mlp_only ? 1 : 0;
     a.patch_rays = (opts->flags & SNERG_FLAG_PATCH_RAYS) ? 1 : 0;
     a.grad_packed = packed ? 1 : 0;
-    // pixels no further apart than voxels at the distance of the grid's centre
     a.dense_views = 1;
-    for (int32_t c = 0; c < n_cams; ++c) {
-        const double* e = cams[c].eye;
-        if (std::sqrt(e[0] * e[0] + e[1] * e[1] + e[2] * e[2]) * grid->N > 2.0 * cams[c].focal) a.dense_views = 0;
-    }
+    for (int32_t c = 0; c < n_cams; ++c)
+        if (!dense_view(cams[c].eye, cams[c].focal, grid->N)) a.dense_views = 0;
     if (ray_ids && !mlp_only && n_rays <= kBackwardListMaxRays && backward_aggregates(a.grid)) {
         rc = ensure_buffer(&h->d_list, &h->list_cap, size_t(n_rays) * kBackwardListCap * 4, s);
         if (rc) return rc;

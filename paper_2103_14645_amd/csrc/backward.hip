@@ -25,6 +25,7 @@
 
 #include "march.h"
 #include "mlp.h"
+#include "routes.h"
 #include "snerg_launch.h"
 
 namespace snerg {
@@ -766,9 +767,8 @@ struct TableSync {
 // One lane per ray.  Without a ray list the wavefronts walk the cameras'
 // tile_w x tile_h pixel tiles (neighbouring rays, shared voxels); with a list,
 // 64 consecutive list entries.  Gradients go through the wavefront's LDS
-// table.  Every lane stays to the end (the flushes need all 64).  Serves views
-// whose pixels are sparse on the grid and lists of more than 2^18 rays
-// (launch_backward says why).
+// table.  Every lane stays to the end (the flushes need all 64).  backward_route
+// says which calls come here.
 constexpr int kAggWaves = 4;  // wavefronts per workgroup
 constexpr int kAggLdsWords = kAggWaves * kAggWords;
 
@@ -1200,7 +1200,8 @@ constexpr int kAdjWaves = 4;  // wavefronts per workgroup: half a tile, 8 lanes 
 constexpr int kAdjFlushAt = kAggSlots * 9 / 16;
 constexpr int kAdjTrips = 4;
 
-// AGG: whole views, half a tile to a workgroup, gradients through the table.
+// AGG: whole views and long lists of patches, half a tile (or 32 list entries) to
+// a workgroup, gradients through the table.
 // Else through the wavefronts' logs, with no limit on the voxel index: views
 // and lists on grids beyond the table's keys, and of a scattered list the rays
 // with too many samples to list.
@@ -1746,16 +1747,13 @@ hipError_t launch_backward(const BackwardArgs& a, int n_groups, hipStream_t s) {
         else hipLaunchKernelGGL(k_march_backward<false>, n, wg, lds, s, a);
         return check();
     };
-    if (!backward_aggregates(a.grid)) return walk8(false);
-    // Whole views: eight lanes to a ray halve the time (eight 800x800 views,
-    // 512^3: 17.5 against 27 ms; two of 160x160: 2.2 against 4.5 for the whole
-    // call), but they enter the table in another order.  Where pixels are
-    // further apart than voxels a tile's voxels don't fit the table, order
-    // decides what overflows and goes unrounded, and the feature gradients
-    // would differ by the table's own rounding, 4e-5 of their norm at 160x160
-    // on 512^3, 1.5e-6 at 800x800: such views, like lists of more rays than
-    // the launch keeps samples for, take one lane per ray.
-    if (!a.list) return a.dense_views ? walk8(true) : walk1();
+    switch (backward_route(backward_aggregates(a.grid), a.list != nullptr, a.ray_ids != nullptr, a.patch_rays != 0,
+                           a.dense_views != 0)) {
+        case BackwardRoute::kLogs: return walk8(false);
+        case BackwardRoute::kEightLanes: return walk8(true);
+        case BackwardRoute::kOneLane: return walk1();
+        case BackwardRoute::kListed: break;
+    }
     const size_t occ = size_t(a.grid.n_words) * sizeof(uint2);
     const dim3 n{unsigned((a.n_rays * kRecordLanes + 255) / 256)}, wg{256};
     hipLaunchKernelGGL(k_backward_record, n, wg, occ, s, a);

@@ -1,0 +1,43 @@
+// Which kernel a call takes: the rules that look at sizes alone, free of the
+// device so that they can be checked without one.
+#pragma once
+
+#include <cmath>
+#include <cstdint>
+
+namespace snerg {
+
+// Whether a camera's pixels lie no further apart than the voxels at the distance
+// of the grid's centre.
+inline bool dense_view(const double eye[3], double focal, int32_t N) {
+    return std::sqrt(eye[0] * eye[0] + eye[1] * eye[1] + eye[2] * eye[2]) * N <= 2.0 * focal;
+}
+
+// How a backward call takes its rays.
+enum class BackwardRoute : int32_t {
+    kLogs,           // eight lanes to a ray, through the wavefronts' logs
+    kListed,         // a list of samples first: patches or scattered rays
+    kEightLanes,     // eight lanes to a ray, a workgroup's table
+    kOneLane,        // one lane to a ray, a wavefront's table
+};
+
+// keys: the grid's voxels fit the tables' keys.  listed: a ray list short enough
+// that the launch keeps its samples.  ids: a ray list; patch: in groups of 64
+// neighbours.  dense: every camera a dense_view.
+//
+// Eight lanes halve the time (eight 800x800 views, 512^3: 17.5 against 27 ms; two
+// of 160x160: 2.2 against 4.5 for the whole call; 270,000 rays in patches 3.9
+// against 1.4), but they enter the table in another order.  Where a tile's voxels
+// don't fit the table, order decides what overflows and goes unrounded, and the
+// feature gradients would differ by the table's own rounding: 4e-5 of their norm
+// for 160x160 views of a 512^3 grid, 2.2e-5 for 270,000 scattered rays of it, but
+// 1.5e-6 for 800x800 views and 1.7e-6 for 270,000 rays in patches.  So views whose
+// pixels are further apart than the voxels and long scattered lists take one lane.
+inline BackwardRoute backward_route(bool keys, bool listed, bool ids, bool patch, bool dense) {
+    if (!keys) return BackwardRoute::kLogs;
+    if (listed) return BackwardRoute::kListed;
+    if (!dense || (ids && !patch)) return BackwardRoute::kOneLane;
+    return BackwardRoute::kEightLanes;
+}
+
+}  // namespace snerg

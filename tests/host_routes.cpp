@@ -1,0 +1,14 @@
+// C entries to the launch rules of csrc/routes.h, for tests/test_routes.py.
+#include "routes.h"
+
+using namespace snerg;
+
+extern "C" {
+
+int route_dense_view(const double* eye, double focal, int N) { return dense_view(eye, focal, N); }
+
+int route_backward(int keys, int listed, int ids, int patch, int dense) {
+    return int(backward_route(keys != 0, listed != 0, ids != 0, patch != 0, dense != 0));
+}
+
+}  // extern "C"

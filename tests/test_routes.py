@@ -1,0 +1,48 @@
+"""The rules by which calls are dealt to kernels (csrc/routes.h), compiled for
+the host and checked over the forms that they accept."""
+import ctypes
+import itertools
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+CSRC = os.path.join(os.path.dirname(HERE), "paper_2103_14645_amd", "csrc")
+LOGS, LISTED, EIGHT, ONE = range(4)
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("routes") / "libroutes.so")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-fPIC", "-shared", "-I", CSRC,
+                    os.path.join(HERE, "host_routes.cpp"), "-o", so], check=True)
+    return ctypes.CDLL(so)
+
+
+def dense(lib, eye, focal, N):
+    e = np.ascontiguousarray(eye, dtype=np.float64)
+    return bool(lib.route_dense_view(e.ctypes.data_as(ctypes.c_void_p), ctypes.c_double(focal), N))
+
+
+def test_dense_views(lib):
+    # outside the grid: a pixel covers |eye| / focal at the centre, a voxel 2 / N
+    for d, focal, want in ((2.0, 512.0, True), (2.0, 511.0, False), (4.0, 1024.0, True), (4.0, 1000.0, False)):
+        assert dense(lib, (0.0, d, 0.0), focal, 512) == want, (d, focal)
+
+
+def test_backward_routes(lib):
+    for keys, listed, ids, patch, dense_ in itertools.product((0, 1), repeat=5):
+        if listed and not (ids and keys):
+            continue
+        got = lib.route_backward(keys, listed, ids, patch, dense_)
+        if not keys:
+            want = LOGS
+        elif listed:
+            want = LISTED
+        elif ids and not patch:  # long scattered lists keep the order of one lane per ray
+            want = ONE
+        else:
+            want = EIGHT if dense_ else ONE
+        assert got == want, (keys, listed, ids, patch, dense_)

@@ -7,10 +7,13 @@
 
 namespace snerg {
 
-// Whether a camera's pixels lie no further apart than the voxels at the distance
-// of the grid's centre.
+// Whether a camera's pixels lie no further apart than the voxels where the
+// grid is: at its centre, or for an eye inside the grid at its faces, which the
+// rays still have ahead of them (a 160x160 view of 90 degrees from the middle of
+// a 512^3 grid has 3 voxels to a pixel there).
 inline bool dense_view(const double eye[3], double focal, int32_t N) {
-    return std::sqrt(eye[0] * eye[0] + eye[1] * eye[1] + eye[2] * eye[2]) * N <= 2.0 * focal;
+    const double d = std::sqrt(eye[0] * eye[0] + eye[1] * eye[1] + eye[2] * eye[2]);
+    return (d > 1.0 ? d : 1.0) * N <= 2.0 * focal;
 }
 
 // How a backward call takes its rays.

@@ -30,6 +30,10 @@ def test_dense_views(lib):
     # outside the grid: a pixel covers |eye| / focal at the centre, a voxel 2 / N
     for d, focal, want in ((2.0, 512.0, True), (2.0, 511.0, False), (4.0, 1024.0, True), (4.0, 1000.0, False)):
         assert dense(lib, (0.0, d, 0.0), focal, 512) == want, (d, focal)
+    # inside it, at the faces: an eye in the middle does not make wide pixels dense
+    for eye in ((0.0, 0.0, 0.0), (0.05, -0.02, 0.1), (0.5, 0.5, 0.5)):
+        assert not dense(lib, eye, 80.0, 512)
+        assert dense(lib, eye, 256.0, 512)
 
 
 def test_backward_routes(lib):

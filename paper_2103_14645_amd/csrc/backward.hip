@@ -622,7 +622,7 @@ struct AdjointRay {
         T = 1.0f;
         Pk = 0.0f;
         delta = 1.0f / float(a.grid.N);
-        kx = a.grid.sigma_scale * delta;
+        kx = a.grid.sigma_scale / float(a.grid.N);  // the forward's, which sigma_scale * delta need not be
         t_stop = a.opts.t_stop;
         early = a.opts.early_stop != 0;
         nn_gate = a.opts.nn_gate != 0;
@@ -1133,7 +1133,7 @@ __device__ __forceinline__ bool sample_decay(const GridArgs& g, const uint8_t* v
         dnn = c == cnn ? den[c] : dnn;
         sigma = fmaf(w[c], den[c], sigma);
     }
-    e = __expf(-sigma * (g.sigma_scale * (1.0f / float(g.N))));
+    e = __expf(-sigma * (g.sigma_scale / float(g.N)));
     return nn_gate ? dnn != 0.0f : act;
 }
 

@@ -1198,6 +1198,7 @@ constexpr int kAdjWaves = 4;  // wavefronts per workgroup: half a tile, 8 lanes 
 // flushes it when it holds more than kAdjFlushAt keys; what its rays add in
 // four trips (up to 32 samples each) mostly fits above that.
 constexpr int kAdjFlushAt = kAggSlots * 9 / 16;
+constexpr int kAdjStaticLds = 512;  // at the most, beside the two tables
 constexpr int kAdjTrips = 4;
 
 // AGG: whole views and long lists of patches, half a tile (or 32 list entries) to
@@ -1720,10 +1721,13 @@ hipError_t launch_backward(const BackwardArgs& a, int n_groups, hipStream_t s) {
     const bool feat = a.mlp_mode != kMlpOff;
     auto check = [] { return hipGetLastError(); };
     // Eight lanes to a ray, walking.
+    auto walk8_lds = [&](bool agg) {
+        return (size_t(a.grid.n_words) + 1) / 2 * 16 +
+               (agg ? size_t(kAggWords) * 4 : size_t(kAdjWaves) * kLogEntries * sizeof(int4));
+    };
     auto walk8 = [&](bool agg) {
         const int64_t wgs = 2 * (a.ray_ids ? (a.n_rays + 63) / 64 : a.total_tiles);
-        const size_t lds = (size_t(a.grid.n_words) + 1) / 2 * 16 +
-                           (agg ? size_t(kAggWords) * 4 : size_t(kAdjWaves) * kLogEntries * sizeof(int4));
+        const size_t lds = walk8_lds(agg);
         static_assert(kAdjWaves * 8 == 32, "two workgroups to 64 rays");
         constexpr int64_t kMaxGroups = int64_t(1) << 22;  // a launch holds fewer than 2^32 lanes
         BackwardArgs b = a;
@@ -1748,7 +1752,8 @@ hipError_t launch_backward(const BackwardArgs& a, int n_groups, hipStream_t s) {
         return check();
     };
     switch (backward_route(backward_aggregates(a.grid), a.list != nullptr, a.ray_ids != nullptr, a.patch_rays != 0,
-                           a.dense_views != 0)) {
+                           a.dense_views != 0, int64_t(walk8_lds(true)) + kAdjStaticLds,
+                           a.ray_ids ? a.n_rays : 64 * a.total_tiles)) {
         case BackwardRoute::kLogs: return walk8(false);
         case BackwardRoute::kEightLanes: return walk8(true);
         case BackwardRoute::kOneLane: return walk1();

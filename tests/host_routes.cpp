@@ -7,8 +7,8 @@ extern "C" {
 
 int route_dense_view(const double* eye, double focal, int N) { return dense_view(eye, focal, N); }
 
-int route_backward(int keys, int listed, int ids, int patch, int dense) {
-    return int(backward_route(keys != 0, listed != 0, ids != 0, patch != 0, dense != 0));
+int route_backward(int keys, int listed, int ids, int patch, int dense, int64_t lds, int64_t rays) {
+    return int(backward_route(keys != 0, listed != 0, ids != 0, patch != 0, dense != 0, lds, rays));
 }
 
 }  // extern "C"

@@ -25,7 +25,6 @@
 
 #include "march.h"
 #include "mlp.h"
-#include "routes.h"
 #include "snerg_launch.h"
 
 namespace snerg {

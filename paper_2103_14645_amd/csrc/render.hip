@@ -548,48 +548,6 @@ hipError_t launch_tile_order(const RenderArgs& a, uint8_t* cls, int32_t* counts,
     return hipGetLastError();
 }
 
-// Lanes per ray, by measurement (us; views of a shell grid at 39 degrees,
-// scattered pixels, 8x8 patches).  uint8, 512^3:
-//                       1 lane    4     16
-//    4,096 pixels/patches  402/180  175/83  74/47
-//   32,768                 339/235  181/105 169/110
-//   65,536                 382/296  222/140 272/178
-//   512x512 frame          394     266 (in tile order; 352 in image order)
-//   640x480 frame          372     323        (1024^3: 859 -> 576)
-//   1250x200, all on it    257     218        1250x300: 274 -> 306
-//   800x800 frame          412     530        (1024^3, FP16: 859 -> 1084)
-// so 16 lanes up to 2^15 rays, 4 up to 5 2^16.  One lane's time is that of the
-// longest ray, in proportion to N, four lanes' more and more the chip's, in
-// proportion to the rays, so on smaller grids the line lies lower, and with
-// small macroblocks, whose walk every lane of a ray repeats (one lane, four):
-// 512^3 in blocks of 16, 1250x250 325, 404; 320^3, 187,500 rays 180, 158,
-// 375,000 238, 278; 128^3, 120,000 rays 163, 105, 187,500 126, 141; 64^3,
-// 86,000 51, 35, 110,600 55, 57; 96^3 in blocks of 4, 81,000 99, 114.  Past 2^16
-// rays the wavefronts are not all resident at once, and the order pays for its
-// two launches, but not up to 192^3 (120,000 rays 131 in order, 124 without).
-// float32 samples are 256 bytes each and bound by the texture
-// path; the samples of one ray side by side share most of their lines, so
-// there the split also pays where the chip is full: eight 800x800 views of
-// the 512^3 grid 5.25 ms, 2 lanes 4.05, 4 lanes 5.1; of a 1024^3 grid 13.0,
-// 7.6, 7.9; 2^20 scattered pixels 3.38, 2.09, 1.95.  The FP16 network's tiles
-// run once per wavefront, however many rays it holds: four 1080p views take
-// 7.05 ms with one lane and 7.20 with two, eight 800x800 views 5.24 and 4.86.
-RenderSplit render_split(const RenderArgs& a, bool f32, bool f16) {
-    const bool list = a.ray_ids != nullptr;
-    if (a.n_rays <= (int64_t(1) << 15)) return {16, 0};
-    if (a.n_rays <= (int64_t(1) << 16)) return {4, 0};
-    const int N = a.grid.N;
-    const int64_t most = N < 128   ? (a.grid.B < 8 ? int64_t(1) << 16 : int64_t(3) << 15)
-                         : N < 192 ? int64_t(1) << 17
-                         : N < 512 || a.grid.B < 32 ? int64_t(3) << 16
-                                                    : int64_t(5) << 16;
-    if (a.n_rays <= most) return {4, N > 192};
-    if (f32 && list && a.n_rays <= (int64_t(1) << 20)) return {4, 1};
-    // (a launch holds fewer than 2^32 lanes)
-    if (f32 && a.n_rays <= (f16 ? int64_t(6) << 20 : int64_t(1) << 30)) return {2, 1};
-    return {1, 1};
-}
-
 template <int VT, int MLP, int L>
 static hipError_t launch_render_group(const RenderArgs& a, hipStream_t s) {
     constexpr int kRays = 64 / L;

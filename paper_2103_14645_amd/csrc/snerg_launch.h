@@ -1,6 +1,7 @@
 // Host-side interface between the C ABI (api.cpp) and the HIP kernels.
 #pragma once
 
+#include "routes.h"
 #include "snerg_dev.h"
 
 namespace snerg {
@@ -15,12 +16,6 @@ enum MlpMode : int32_t {
     kMlpOff = 0,
     kMlpF32 = 1,   // FP32 per lane
     kMlpF16 = 2,   // FP16 MFMA tiles, FP32 accumulation
-};
-
-// How a render deals rays to lanes (render_split): lanes per ray, and whether
-// its tiles go in heavy-first order.
-struct RenderSplit {
-    int32_t lanes, ordered;
 };
 
 struct RenderArgs {
@@ -127,7 +122,6 @@ hipError_t launch_pack(const PackedLayout& L, int32_t n_blocks, bool f32, const 
 // vt: 0 = uint8 grid, 1 = float32 grid.
 hipError_t launch_render(const RenderArgs& a, int vt, int mlp_mode, int waves_per_group,
                          int n_groups, hipStream_t s);
-RenderSplit render_split(const RenderArgs& a, bool f32, bool f16);
 hipError_t launch_trace(const RenderArgs& a, int vt, hipStream_t s);
 // Heavy-first tile order for a tiled or persistent render: `cls` [total_tiles]
 // and `counts` [33] are scratch (counts zero on entry, left zero on exit),

@@ -59,3 +59,21 @@ def test_backward_routes(lib, G, rays):
         else:
             want = EIGHT if dense_ else ONE
         assert got == want, (keys, listed, ids, patch, dense_)
+
+
+def split(lib, N, B, rays, list_=False, f32=False, f16=False):
+    return lib.route_render(N, B, int(list_), ctypes.c_int64(rays), int(f32), int(f16)) // 2
+
+
+SHAPES = [(N, B) for B in (2, 4, 8, 16, 32, 64) for N in range(B, min(64 * B, 2048) + 1, B) if N // B in (1, 2, 8, 16, 32, 40, 48, 56, 64)]
+
+
+@pytest.mark.parametrize("f32,f16", [(0, 0), (0, 1), (1, 0), (1, 1)])
+def test_render_launches_hold_fewer_than_2_to_32_lanes(lib, f32, f16):
+    for N, B in SHAPES:
+        for list_ in (0, 1):
+            for e in range(6, 34):
+                for rays in ((1 << e) - 64, 1 << e, (1 << e) + 64):
+                    lanes = split(lib, N, B, rays, list_, f32, f16)
+                    assert lanes in ((1, 2, 4, 16) if f32 else (1, 4, 16))
+                    assert lanes == 1 or rays * lanes < 1 << 32, (N, B, list_, rays, lanes)

@@ -13,46 +13,87 @@ struct RenderSplit {
     int32_t lanes, ordered;
 };
 
-// Lanes per ray, by measurement (us; views of a shell grid at 39 degrees,
-// scattered pixels, 8x8 patches).  uint8, 512^3:
-//                       1 lane    4     16
-//    4,096 pixels/patches  402/180  175/83  74/47
-//   32,768                 339/235  181/105 169/110
-//   65,536                 382/296  222/140 272/178
-//   512x512 frame          394     266 (in tile order; 352 in image order)
-//   640x480 frame          372     323        (1024^3: 859 -> 576)
-//   1250x200, all on it    257     218        1250x300: 274 -> 306
-//   800x800 frame          412     530        (1024^3, FP16: 859 -> 1084)
-// so 16 lanes up to 2^15 rays, 4 up to 5 2^16.  One lane's time is that of the
-// longest ray, in proportion to N, four lanes' more and more the chip's, in
-// proportion to the rays, so on smaller grids the line lies lower, and with
-// small macroblocks, whose walk every lane of a ray repeats (one lane, four):
-// 512^3 in blocks of 16, 1250x250 325, 404; 320^3, 187,500 rays 180, 158,
-// 375,000 238, 278; 128^3, 120,000 rays 163, 105, 187,500 126, 141; 64^3,
-// 86,000 51, 35, 110,600 55, 57; 96^3 in blocks of 4, 81,000 99, 114.  Past 2^16
-// rays the wavefronts are not all resident at once, and the order pays for its
-// two launches, but not up to 192^3 (120,000 rays 131 in order, 124 without).
-// float32 samples are 256 bytes each and bound by the texture
-// path; the samples of one ray side by side share most of their lines, so
-// there the split also pays where the chip is full: eight 800x800 views of
-// the 512^3 grid 5.25 ms, 2 lanes 4.05, 4 lanes 5.1; of a 1024^3 grid 13.0,
-// 7.6, 7.9; 2^20 scattered pixels 3.38, 2.09, 1.95.  The FP16 network's tiles
-// run once per wavefront, however many rays it holds: four 1080p views take
-// 7.05 ms with one lane and 7.20 with two, eight 800x800 views 5.24 and 4.86.
+// Lanes per ray.  A render of few rays is a few wavefronts per SIMD, each as long
+// as its longest ray (in proportion to N), and several lanes to a ray make it
+// shorter; of many rays it is bound by the chip's throughput, which they lower:
+// every lane of a ray repeats its walk over the macroblocks (in proportion to
+// N / B), a workgroup of 256 lanes stages the whole occupancy table (8 KB at 32^3
+// macroblocks, 64 KB at 64^3, where two workgroups fill a compute unit) for 16 or
+// 64 rays, and the FP16 network's tiles run once per wavefront, however many rays
+// it holds.  One lane's list goes 16 or 32 rays to a wavefront up to 2^15 and 2^16
+// rays, so lists gain less than views.  The lines lie where the slowest of what
+// was measured (views, scattered lists; shells and random blocks; both networks)
+// still gains.  One lane's time over that of 16 / of 4, uint8, slowest to fastest:
+//   rays            16,384             32,768             65,536             131,072
+//   N, B       view 16   view 4   view 16   list 4    view 4    list 4    view 4
+//   64, 2      1.06-1.4  0.7-1.0  0.65-0.85 0.7-0.9   0.7-1.1   0.65-0.7
+//   128, 2     0.44-0.9  0.45-1.0 0.24-0.5  0.8-1.0   0.3-0.65
+//   64, 4      1.5-1.7   1.3-1.5  0.9-1.05  0.9-1.2   1.0-1.3   0.8-1.0   0.8-0.9
+//   256, 4     0.74-1.4  0.9-1.1  0.4-0.8   0.8-1.1   0.3-0.7
+//   128, 8     2.0-2.1   1.5-1.7  1.3-1.4   0.9-1.4   1.2-1.4   0.8-1.0   0.9-1.05
+//   256, 8     2.3-3.1   1.05-1.7 1.5-2.0   1.1-1.25  1.1-1.5   0.96-1.1  0.8-1.1
+//   512, 8     1.0-2.1   1.3-1.4  0.5-1.3   1.05-1.2  0.4-0.8
+//   256, 16    2.7-4.0   1.6-2.5  1.8-2.5   1.3-1.8   1.5-2.1   1.2-1.4   1.1-1.4
+//   768, 16    2.4-4.2   1.5-1.8  1.4-2.9   1.3-1.4   0.8-1.9             0.6-1.5
+//   1024, 16   1.4-2.8   1.5-1.6  0.8-1.9   1.4-1.5   0.5-1.1
+//   256, 32    3.1-4.2   2.6-2.8  2.1-2.6   1.8-2.1   1.7-2.4   1.6-1.7   1.3-1.6
+//   512, 32    4.0-5.5   2.2-2.6  2.9-3.7   1.75-1.9  2.1-2.4   1.5-1.7   1.4-2.0
+//   1024, 32   4.7-5.6   2.0-2.3  3.1-4.1   1.7-1.9   2.0-2.4   1.45-1.6  1.4-2.3
+// and at 313,600 (560x560) 0.9-1.1 for 512, 32 and 1.1-1.5 for 1024, 32.  Past 2^16
+// rays the wavefronts are not all resident at once, and the tile order pays for
+// its two launches, but not up to 192^3 (128^3, 120,000 rays 131 us in order, 124
+// without).
+// float32 samples are 256 bytes each and bound by the texture path; the samples of
+// one ray side by side share most of their lines, so there the split also pays
+// where the chip is full, unless macroblocks are small.  One lane over 2 lanes,
+// eight 800x800 views, FP32 / FP16 network: 64, 32 0.95 / 0.88; 128, 32 1.11 / 0.99;
+// 512, 32 1.24 / 1.02; 1024, 32 1.71 / 1.52; 512, 16 0.98 / 0.81; 256, 8 0.87 / 0.72;
+// 560x560: 128, 16 1.22 / 1.13; 512, 16 1.35 / 1.23; 128, 8 1.06 / 0.98.  Over 4:
+// 560x560 192, 32 1.38 / 1.22; 512, 32 2.0 / 1.7; 512, 16 1.45 / 1.25; 512, 8 0.55 /
+// 0.4; 2^20 scattered rays 128, 32 1.3 / 1.1; 64, 32 1.05 / 0.96; 512, 16 1.2 / 0.96.
 //
 // rays: of a list its entries, of views 64 for each tile, since a wavefront is
 // launched and its tables are staged however few of them lie in the image.
 inline RenderSplit render_split(int32_t N, int32_t B, bool list, int64_t rays, bool f32, bool f16) {
-    if (rays <= (int64_t(1) << 15)) return {16, 0};
-    if (rays <= (int64_t(1) << 16)) return {4, 0};
-    const int64_t most = N < 128   ? (B < 8 ? int64_t(1) << 16 : int64_t(3) << 15)
-                         : N < 192 ? int64_t(1) << 17
-                         : N < 512 || B < 32 ? int64_t(3) << 16
-                                             : int64_t(5) << 16;
-    if (rays <= most) return {4, N > 192};
-    if (f32 && list && rays <= (int64_t(1) << 20)) return {4, 1};
+    constexpr int64_t K = 1 << 10, M = 1 << 20;
+    const int32_t G = N / B;
+    const int table = G <= 40 ? 0 : (G <= 56 ? 1 : 2);  // the occupancy table: up to 16, 43, 64 KB
+    const int64_t work = f16 ? rays + rays / 4 : rays;
+    auto at_most = [](int64_t& line, int64_t v) { line = line < v ? line : v; };
+
+    int64_t most16 = B < 8 ? 16 * K : (B < 16 || N < 256 ? 32 * K : (B < 32 || N < 512 ? 48 * K : 64 * K));
+    if (table > 0) at_most(most16, B < 4 || (B < 8 && table > 1) ? 8 * K : (B < 8 ? 16 * K : 24 * K));
+    if ((list ? 2 * work : work) <= most16) return {16, 0};
+
+    int64_t most4 = 0, most2 = 0;
+    if (!f32) {
+        if (B == 4) most4 = N <= 64 ? 64 * K : 0;
+        else if (B == 8) most4 = N < 128 ? 96 * K : 80 * K;
+        else if (B == 16) most4 = N < 128 ? 96 * K : 128 * K;
+        else if (B >= 32) most4 = N < 128 ? 96 * K : (N < 512 ? 192 * K : 320 * K);
+        if (G > 32) at_most(most4, table == 0 ? 64 * K : (table > 1 ? 24 * K : (B > 8 ? 48 * K : 32 * K)));
+        if (list) most4 /= 2;
+    } else if (list) {
+        if (B == 4 || B == 8) most4 = 64 * K;
+        else if (B >= 16) most4 = B == 16 || N < 128 ? 512 * K : 1280 * K;
+        if (table == 1) at_most(most4, B < 8 ? 32 * K : (B < 16 ? 64 * K : (f16 ? 80 * K : 512 * K)));
+        if (table == 2) at_most(most4, B < 8 ? 16 * K : (B < 16 ? 32 * K : 40 * K));
+        if (B == 16) most2 = table == 0 ? M : 0;
+        else if (B >= 32) most2 = f16 ? 5 * M : 1 << 30;
+    } else {
+        if (B == 4) most4 = 64 * K;
+        else if (B == 8) most4 = N < 128 || G > 32 ? 96 * K : 160 * K;
+        else if (B >= 16 && N < (B == 16 ? 256 : 128)) most4 = 160 * K;
+        else if (B >= 16) most4 = B == 16 || N < 512 ? 384 * K : (N < 1024 && B == 32 ? 512 * K : 1024 * K);
+        if (table == 1 && B < 16) at_most(most4, 64 * K);
+        if (table == 2) at_most(most4, B < 8 ? 24 * K : (B < 16 ? 40 * K : (f16 ? 48 * K : 160 * K)));
+        if (B == 8 && G <= 16) most2 = N < 128 ? 160 * K : 384 * K;
+        else if (B == 16) most2 = table == 0 ? (N < 128 ? 512 * K : 768 * K) : (table == 1 || !f16 ? 384 * K : 0);
+        else if (B >= 32) most2 = N < 128 ? 512 * K : (!f16 ? 1 << 30 : (N < 512 ? 2 * M : 7 * M));
+    }
+    if (work <= most4) return {4, work > 64 * K && N > 192};
     // (a launch holds fewer than 2^32 lanes)
-    if (f32 && rays <= (f16 ? int64_t(6) << 20 : int64_t(1) << 30)) return {2, 1};
+    if (work <= most2) return {2, 1};
     return {1, 1};
 }
 

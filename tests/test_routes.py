@@ -77,3 +77,20 @@ def test_render_launches_hold_fewer_than_2_to_32_lanes(lib, f32, f16):
                     lanes = split(lib, N, B, rays, list_, f32, f16)
                     assert lanes in ((1, 2, 4, 16) if f32 else (1, 4, 16))
                     assert lanes == 1 or rays * lanes < 1 << 32, (N, B, list_, rays, lanes)
+
+
+# Where several lanes to a ray were measured to lose against one (and where they win).
+@pytest.mark.parametrize("N,B,rays,kw,lanes", [
+    (128, 2, 16384, {}, 1), (128, 2, 4096, {}, 16), (64, 2, 65536, {}, 1), (64, 2, 16384, {}, 16),
+    (256, 4, 65536, {}, 1), (256, 4, 16384, dict(f16=True), 1), (256, 4, 4096, {}, 16), (64, 4, 65536, {}, 4),
+    (512, 8, 65536, {}, 1), (512, 8, 163840, {}, 1), (512, 8, 16384, {}, 16), (256, 8, 65536, {}, 4),
+    (1024, 16, 65536, dict(list_=True), 1), (512, 16, 65536, dict(list_=True), 4),
+    (512, 32, 4096, {}, 16), (512, 32, 65536, dict(list_=True), 4), (512, 32, 262144, {}, 4), (512, 32, 640000, {}, 1),
+    (256, 4, 65536, dict(f32=True, f16=True), 1), (256, 4, 640000, dict(f32=True), 1),
+    (512, 8, 163840, dict(f32=True), 1), (512, 8, 5120000, dict(f32=True), 1),
+    (64, 8, 640000, dict(f32=True, f16=True), 1), (64, 8, 5120000, dict(f32=True), 1),
+    (256, 16, 2560000, dict(f32=True, f16=True), 1), (512, 32, 5120000, dict(f32=True), 2),
+    (1024, 32, 65536, dict(f32=True, f16=True, list_=True), 4), (512, 32, 1 << 20, dict(f32=True, list_=True), 4),
+])
+def test_render_lanes(lib, N, B, rays, kw, lanes):
+    assert split(lib, N, B, rays, **kw) == lanes

@@ -18,28 +18,29 @@ __global__ void k_fill_f32(float* p, int64_t n, float v) {
     if (i < n) p[i] = v;
 }
 
-// Occupancy table and rank maps, one workgroup of 1024 threads: each thread
-// builds `per` consecutive words of 32 macroblocks, a prefix sum of their
-// popcounts gives the ranks, and the rank maps are written from the same
-// words (ranks past the last occupied macroblock get -1).  One launch in the
-// place of five (23 us of kernels on a 16^3 indirection grid, 7 us
-// now); the table is at most 8192 words, so one workgroup's bandwidth does.
-__global__ __launch_bounds__(1024) void k_pack_tables(const int32_t* __restrict__ ind, int64_t G3, int32_t n_blocks,
-                                                      int32_t n_words, uint2* __restrict__ occ,
-                                                      int32_t* __restrict__ rank_lin, int32_t* __restrict__ rank_id) {
-    __shared__ int32_t part[1024];
-    const int t = threadIdx.x, lane = t & 63;
-    const int per = (n_words + 1023) / 1024;
-    const int w0 = t * per;
-    // bits of the words, 64 entries (two words) per wavefront and step, read coalesced
-    for (int64_t base = int64_t(t >> 6) * 64; base < int64_t(n_words) * 32; base += 1024) {
+// Occupancy table and rank maps.
+
+// Occupancy bits of the words, 64 entries (two words) per wavefront and step,
+// read coalesced: thread t of n, whole wavefronts.
+__device__ __forceinline__ void pack_bits(const int32_t* __restrict__ ind, int64_t G3, int32_t n_blocks,
+                                          int32_t n_words, uint2* occ, int64_t t, int64_t n) {
+    const int lane = int(t & 63);
+    for (int64_t base = t - lane; base < int64_t(n_words) * 32; base += n) {
         const int64_t lin = base + lane;
         const int32_t id = lin < G3 ? ind[lin] : -1;
         const uint64_t m = __ballot(id >= 0 && id < n_blocks);
         const int64_t w = (base >> 5) + (lane >> 5);
         if ((lane & 31) == 0 && w < n_words) occ[w].x = uint32_t(m >> (lane & 32));
     }
-    __syncthreads();  // the workgroup's own global writes are visible to it
+}
+
+// Ranks of the words: an exclusive prefix sum of their popcounts by a workgroup of
+// 1024 threads, each with `per` consecutive words.  Returns their total.
+__device__ __forceinline__ int32_t pack_scan(int32_t n_words, uint2* occ) {
+    __shared__ int32_t part[1024];
+    const int t = threadIdx.x;
+    const int per = (n_words + 1023) / 1024;
+    const int w0 = t * per;
     int32_t sum = 0;
     for (int i = 0; i < per; ++i)
         if (w0 + i < n_words) sum += __popc(occ[w0 + i].x);
@@ -57,9 +58,14 @@ __global__ __launch_bounds__(1024) void k_pack_tables(const int32_t* __restrict_
             occ[w0 + i].y = uint32_t(run);
             run += __popc(occ[w0 + i].x);
         }
-    const int32_t total = part[1023];
-    __syncthreads();
-    for (int64_t lin = t; lin < G3; lin += 1024) {
+    return part[1023];
+}
+
+// The rank maps from the words, -1 past the last of `total` occupied macroblocks.
+__device__ __forceinline__ void pack_ranks(const int32_t* __restrict__ ind, int64_t G3, int32_t n_blocks,
+                                           int32_t total, const uint2* occ, int32_t* __restrict__ rank_lin,
+                                           int32_t* __restrict__ rank_id, int64_t t, int64_t n) {
+    for (int64_t lin = t; lin < G3; lin += n) {
         const uint2 e = occ[lin >> 5];
         const int j = int(lin & 31);
         if (!((e.x >> j) & 1u)) continue;
@@ -69,10 +75,36 @@ __global__ __launch_bounds__(1024) void k_pack_tables(const int32_t* __restrict_
             rank_id[r] = ind[lin];
         }
     }
-    for (int32_t r = total + t; r < n_blocks; r += 1024) {
+    for (int64_t r = total + t; r < n_blocks; r += n) {
         rank_lin[r] = -1;
         rank_id[r] = -1;
     }
+}
+
+// One launch for all three, while one workgroup's bandwidth does (5 launches and
+// 23 us of kernels before, 7 us now, on a 16^3 indirection grid) ...
+__global__ __launch_bounds__(1024) void k_pack_tables(const int32_t* __restrict__ ind, int64_t G3, int32_t n_blocks,
+                                                      int32_t n_words, uint2* occ, int32_t* __restrict__ rank_lin,
+                                                      int32_t* __restrict__ rank_id) {
+    pack_bits(ind, G3, n_blocks, n_words, occ, threadIdx.x, 1024);
+    __syncthreads();  // the workgroup's own global writes are visible to it
+    const int32_t total = pack_scan(n_words, occ);
+    __syncthreads();
+    pack_ranks(ind, G3, n_blocks, total, occ, rank_lin, rank_id, threadIdx.x, 1024);
+}
+
+// ... and three for larger grids, the first and the last over the whole chip.
+__global__ __launch_bounds__(256) void k_pack_bits(const int32_t* __restrict__ ind, int64_t G3, int32_t n_blocks,
+                                                   int32_t n_words, uint2* __restrict__ occ) {
+    pack_bits(ind, G3, n_blocks, n_words, occ, int64_t(blockIdx.x) * 256 + threadIdx.x, int64_t(gridDim.x) * 256);
+}
+__global__ __launch_bounds__(1024) void k_pack_scan(int32_t n_words, uint2* occ) { pack_scan(n_words, occ); }
+__global__ __launch_bounds__(256) void k_pack_ranks(const int32_t* __restrict__ ind, int64_t G3, int32_t n_blocks,
+                                                    int32_t n_words, const uint2* __restrict__ occ,
+                                                    int32_t* __restrict__ rank_lin, int32_t* __restrict__ rank_id) {
+    const uint2 last = occ[n_words - 1];
+    pack_ranks(ind, G3, n_blocks, int32_t(last.y) + __popc(last.x), occ, rank_lin, rank_id,
+               int64_t(blockIdx.x) * 256 + threadIdx.x, int64_t(gridDim.x) * 256);
 }
 
 // The eight channel values of canonical voxel vi.
@@ -406,6 +438,11 @@ static hipError_t launch_pack_t(const PackedLayout& L, int32_t n_blocks, const i
     return hipSuccess;
 }
 
+// One workgroup for the tables up to 24^3 macroblocks: a call that packs little else
+// takes 14.3 us with it and 18.0 with three launches at 20^3, 18.2 and 17.7 at 24^3,
+// 31 and 18 at 32^3, 201 and 52 at 64^3.
+constexpr int64_t kTablesOneGroup = 24 * 24 * 24;
+
 hipError_t launch_pack(const PackedLayout& L, int32_t n_blocks, bool f32, const int32_t* ind,
                        const void* dens, const void* rgb, const void* feat, uint8_t* packed, hipStream_t s) {
     uint2* occ = reinterpret_cast<uint2*>(packed + L.off_occ);
@@ -413,9 +450,18 @@ hipError_t launch_pack(const PackedLayout& L, int32_t n_blocks, bool f32, const 
     int32_t* rank_id = reinterpret_cast<int32_t*>(packed + L.off_rank_id);
     uint8_t* rec = packed + L.off_rec;
     const int64_t G3 = int64_t(L.G) * L.G * L.G;
-    hipLaunchKernelGGL(k_pack_tables, dim3(1), dim3(1024), 0, s, ind, G3, n_blocks, L.n_words, occ, rank_lin, rank_id);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess || n_blocks == 0) return e;
+    hipError_t e;
+    if (G3 <= kTablesOneGroup) {
+        hipLaunchKernelGGL(k_pack_tables, dim3(1), dim3(1024), 0, s, ind, G3, n_blocks, L.n_words, occ, rank_lin, rank_id);
+    } else {
+        const dim3 n(nblk(G3, 256));
+        hipLaunchKernelGGL(k_pack_bits, n, dim3(256), 0, s, ind, G3, n_blocks, L.n_words, occ);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+        hipLaunchKernelGGL(k_pack_scan, dim3(1), dim3(1024), 0, s, L.n_words, occ);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+        hipLaunchKernelGGL(k_pack_ranks, n, dim3(256), 0, s, ind, G3, n_blocks, L.n_words, occ, rank_lin, rank_id);
+    }
+    if ((e = hipGetLastError()) != hipSuccess || n_blocks == 0) return e;
     if (f32)
         return launch_pack_t(L, n_blocks, ind, rank_lin, (const float*)dens, (const float*)rgb, (const float*)feat, rec, s);
     return launch_pack_t(L, n_blocks, ind, rank_lin, (const uint8_t*)dens, (const uint8_t*)rgb, (const uint8_t*)feat, rec,

@@ -110,3 +110,15 @@ def test_packed_bytes_odd_indirection(f32):
     check(N, B, ind, dens, rgb, feat)
     # every macroblock names one of few ids: ranks beyond n_blocks are dropped
     check(N, B, (np.arange(G ** 3) % n).astype(np.int32), dens, rgb, feat)
+
+
+@pytest.mark.parametrize("G", [23, 24, 25, 33, 63, 64])
+def test_tables_of_small_and_large_grids(G):
+    # the occupancy words and rank maps by one workgroup and by the whole chip
+    N, B = 2 * G, 2
+    rng = np.random.default_rng(G)
+    lin = rng.permutation(G ** 3)[:40]
+    ind = np.full(G ** 3, -1, np.int32)
+    ind[lin] = rng.permutation(43)[:40]  # three atlas entries that no macroblock holds
+    dens, rgb, feat = (rng.integers(0, 256, (43, B, B, B) + s, dtype=np.uint8) for s in ((), (3,), (4,)))
+    check(N, B, ind, dens, rgb, feat)

@@ -1388,13 +1388,16 @@ __global__ __launch_bounds__(64 * kAdjWaves) __attribute__((amdgpu_waves_per_eu(
 // with a zero distance byte: 16 bytes each, up to kBackwardListCap a ray; the
 // gradient kernels then run over the lists, so that rays of unequal length
 // and phase sit side by side without waiting for each other's walk.  A ray
-// with more samples is left to the kernels that walk.
+// with more samples is left to the kernels that walk.  Every workgroup stages the
+// occupancy table; where four of 256 lanes, 16 rays each, don't fit a compute
+// unit, workgroups are of 1024 (200,000 rays, 64^3 macroblocks in blocks of 2:
+// call 3.01 -> 2.18 ms).
 // List entry: position in the block on x, y, z (p << 16 | fraction, 23 bits
 // each) with the record's low 9 bits above x, its others above y, the active
 // flag above z; exp(-sigma delta).
 constexpr int kRecordLanes = 16;
 
-__global__ __launch_bounds__(256) void k_backward_record(BackwardArgs a) {
+__global__ __launch_bounds__(1024) void k_backward_record(BackwardArgs a) {
     constexpr int L = kRecordLanes;
     extern __shared__ uint2 s_occ[];
     const GridArgs& g = a.grid;
@@ -1759,7 +1762,8 @@ hipError_t launch_backward(const BackwardArgs& a, int n_groups, hipStream_t s) {
         case BackwardRoute::kListed: break;
     }
     const size_t occ = size_t(a.grid.n_words) * sizeof(uint2);
-    const dim3 n{unsigned((a.n_rays * kRecordLanes + 255) / 256)}, wg{256};
+    const unsigned threads = 4 * int64_t(occ) <= kCuLds ? 256 : 1024;
+    const dim3 n{unsigned((a.n_rays * kRecordLanes + threads - 1) / threads)}, wg{threads};
     hipLaunchKernelGGL(k_backward_record, n, wg, occ, s, a);
     if ((e = check()) != hipSuccess) return e;
     if (a.patch_rays) {

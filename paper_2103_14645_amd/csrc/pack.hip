@@ -138,15 +138,17 @@ __device__ __forceinline__ void load_voxel(const uint8_t* __restrict__ dens, con
     for (int c = 0; c < 4; ++c) val[4 + c] = uint8_t(f4 >> (8 * c));
 }
 
-// One thread per padded voxel, `chunks` workgroups per block record.
+// One thread per padded voxel, `chunks` workgroups per block record, of the records
+// from `first` on.
 template <typename T>
 __global__ __launch_bounds__(256) void k_pack_vox(const int32_t* __restrict__ ind, const int32_t* __restrict__ rank_lin,
                                                   const T* __restrict__ dens, const T* __restrict__ rgb,
                                                   const T* __restrict__ feat, int32_t N, int32_t B, int32_t logB,
-                                                  int32_t n_blocks, int32_t chunks, int64_t rec_stride,
-                                                  int64_t dist_bytes, uint8_t* __restrict__ rec) {
-    const int32_t r = int32_t(blockIdx.x / uint32_t(chunks));
-    const uint32_t v = (blockIdx.x - uint32_t(r) * uint32_t(chunks)) * 256u + threadIdx.x;
+                                                  int32_t n_blocks, int32_t first, int32_t chunks,
+                                                  int64_t rec_stride, int64_t dist_bytes, uint8_t* __restrict__ rec) {
+    const uint32_t block = blockIdx.x / uint32_t(chunks);
+    const int32_t r = first + int32_t(block);
+    const uint32_t v = (blockIdx.x - block * uint32_t(chunks)) * 256u + threadIdx.x;
     const uint32_t Bp = uint32_t(B) + 2;
     if (v >= Bp * Bp * Bp) return;
     const int32_t pz = int32_t(v / (Bp * Bp)), py = int32_t(v / Bp - uint32_t(pz) * Bp), px = int32_t(v % Bp);
@@ -411,9 +413,14 @@ static hipError_t launch_pack_t(const PackedLayout& L, int32_t n_blocks, const i
                                 const T* dens, const T* rgb, const T* feat, uint8_t* rec, hipStream_t s) {
     hipError_t e;
     const int32_t chunks = (L.Bp * L.Bp * L.Bp + 255) / 256;
-    hipLaunchKernelGGL(k_pack_vox<T>, dim3(unsigned(n_blocks) * unsigned(chunks)), dim3(256), 0, s, ind, rank_lin, dens,
-                       rgb, feat, L.N, L.B, L.logB, n_blocks, chunks, L.rec_stride, L.dist_bytes, rec);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
+    // (a launch holds fewer than 2^32 threads: 108,942 records of blocks of 32)
+    const int32_t most = ((1 << 24) - 1) / chunks;
+    for (int32_t first = 0; first < n_blocks; first += most) {
+        const int32_t n = n_blocks - first < most ? n_blocks - first : most;
+        hipLaunchKernelGGL(k_pack_vox<T>, dim3(unsigned(n) * unsigned(chunks)), dim3(256), 0, s, ind, rank_lin, dens, rgb,
+                           feat, L.N, L.B, L.logB, n_blocks, first, chunks, L.rec_stride, L.dist_bytes, rec);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
 #define SNERG_DIST(LB)                                                                                               \
     case LB:                                                                                                         \
         hipLaunchKernelGGL((k_dist<LB, T>), dim3(unsigned(n_blocks)), dim3(DistShape<LB>::kThreads), 0, s, ind, rank_lin, \

@@ -122,3 +122,33 @@ def test_tables_of_small_and_large_grids(G):
     ind[lin] = rng.permutation(43)[:40]  # three atlas entries that no macroblock holds
     dens, rgb, feat = (rng.integers(0, 256, (43, B, B, B) + s, dtype=np.uint8) for s in ((), (3,), (4,)))
     check(N, B, ind, dens, rgb, feat)
+
+
+def test_more_records_than_one_launch_holds():
+    """110,592 uint8 records of blocks of 32 (39 GB): their padded voxels are more than
+    2^32 threads.  The colour and density arrays are parts of the feature array, so
+    that the canonical values take 14.5 GB."""
+    N, B = 1536, 32
+    G = N // B
+    n = G ** 3
+    if torch.cuda.mem_get_info()[0] < 64 << 30:
+        pytest.skip("needs 64 GB of device memory")
+    H.say(f"pack of {n} records")
+    feat = torch.empty(4 * n * B ** 3, dtype=torch.uint8, device="cuda")
+    ramp = (torch.arange(1 << 20, device="cuda") * 131 >> 3).to(torch.uint8)
+    feat.view(-1, 1 << 20).copy_(ramp)
+    feat.view(n, -1).add_(torch.arange(n, device="cuda").to(torch.uint8)[:, None])
+    ids = torch.from_numpy(np.random.default_rng(0).permutation(n).astype(np.int32)).cuda()
+    packed = torch.empty(S.snerg_packed_size(N, B, n, S.SNERG_U8), dtype=torch.uint8, device="cuda")
+    S.snerg_pack_grid(H.handle(), N, B, n, S.SNERG_U8, ids, feat, feat, feat, packed)
+    torch.cuda.synchronize()
+    off = align256(8 * (n // 32)) + 2 * align256(4 * n)
+    dist_bytes, size = (33 ** 3 + 15) & ~15, 34 ** 3 * 8
+    stride = align256(dist_bytes + size)
+    for r in (0, 1, 54321, 108941, 108942, n - 1):
+        at = off + r * stride + dist_bytes
+        vox = packed[at:at + size].view(34, 34, 34, 8)[1:33, 1:33, 1:33]
+        i, B3 = int(ids[r]), B ** 3
+        for lo, hi, per in ((0, 1, 1), (1, 4, 3), (4, 8, 4)):
+            want = feat[per * i * B3:per * (i + 1) * B3].view(B, B, B, per)
+            assert torch.equal(vox[..., lo:hi], want), (r, lo)

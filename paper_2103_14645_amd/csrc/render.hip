@@ -120,23 +120,25 @@ __device__ __forceinline__ bool tile_pixel(const RenderArgs& a, int64_t t, int l
     return px < c.W && py < c.H;
 }
 
-// What follows the march: Eq. 9 if asked for, the deferred network, the
-// outputs.  All 64 lanes call it; `valid` lanes hold a ray.
+// Eq. 9 if asked for: saturate alpha above 2/3, keep soft edges below.
+__device__ __forceinline__ void unpremultiply(const RenderArgs& a, RayAccum& st) {
+    if (!a.opts.unpremultiply) return;
+    const float al = 1.0f - st.T;
+    if (al > 0.0f) {
+        const float sc = fminf(1.0f, 1.5f * al) / al;
+#pragma unroll
+        for (int ch = 0; ch < 3; ++ch) st.C[ch] *= sc;
+#pragma unroll
+        for (int ch = 0; ch < 4; ++ch) st.V[ch] *= sc;
+        st.T = 1.0f - al * sc;
+    }
+}
+
+// What follows the march: the deferred network, the outputs.  All 64 lanes
+// call it; `valid` lanes hold a ray.
 template <int MLP>
 __device__ __forceinline__ void finish_ray(const RenderArgs& a, bool valid, RayAccum& st, const float d[3],
                                            int64_t out_idx) {
-    if (valid && a.opts.unpremultiply) {
-        // Eq. 9: saturate alpha above 2/3, keep soft edges below
-        const float al = 1.0f - st.T;
-        if (al > 0.0f) {
-            const float sc = fminf(1.0f, 1.5f * al) / al;
-#pragma unroll
-            for (int ch = 0; ch < 3; ++ch) st.C[ch] *= sc;
-#pragma unroll
-            for (int ch = 0; ch < 4; ++ch) st.V[ch] *= sc;
-            st.T = 1.0f - al * sc;
-        }
-    }
     float R[3] = {0.f, 0.f, 0.f};
     const bool use_mlp = valid && st.gate && a.opts.mlp_on;
     if (MLP == kMlpF32) {
@@ -173,6 +175,7 @@ __device__ __forceinline__ void render_ray(const RenderArgs& a, const uint2* occ
         // compiler carries its FP64 form through the march)
         asm volatile("" : "+v"(d[0]), "+v"(d[1]), "+v"(d[2]));
         march_composite<VT, COUNT, MLP == kMlpF16>(a, occ, o, s, st, rc);
+        unpremultiply(a, st);
     }
     finish_ray<MLP>(a, valid, st, d, out_idx);
     if (COUNT && valid) {
@@ -392,6 +395,7 @@ __global__ __launch_bounds__(256) void k_render_group(RenderArgs a) {
         ray_setup(a.cams[ci], a.grid.N, px, py, o, s, d);
         asm volatile("" : "+v"(d[0]), "+v"(d[1]), "+v"(d[2]));  // three floats, as in render_ray
         march_composite_group<VT, L>(a, occ, lane, o, s, st);
+        unpremultiply(a, st);
     }
     finish_ray<MLP>(a, valid && (lane & (L - 1)) == 0, st, d, out_idx);
 }

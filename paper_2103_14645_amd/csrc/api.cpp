@@ -876,7 +876,7 @@ int bake_scratch(snerg_handle* h, int64_t G3, int64_t n_cells, BakeScratch* out)
     const size_t off_map = off_count + 2;
     const size_t off_cells = (off_map + size_t(G3) + 1) & ~size_t(1);
     const size_t off_stats = off_cells + 2 * size_t(n_cells);
-    const size_t need = off_stats + 2;
+    const size_t need = off_stats + 4;
     if (need > h->bake_cap) {
         HIP_TRY(hipDeviceSynchronize());
         if (h->d_bake) HIP_TRY(hipFree(h->d_bake));

@@ -17,6 +17,7 @@
 //  k_bake_visibility_cells
 //                     pass also notes which 8^3 cells and whole macroblocks
 //                     hold one value, and the march takes those in one step.
+//  k_bake_choose      leaves fields with many mixed cells to k_bake_visibility.
 //  k_bake_compact     the two culls and the atlas numbering in scan order
 //                     (one workgroup: a ballot prefix per wavefront, then
 //                     across wavefronts).
@@ -83,6 +84,8 @@ __global__ __launch_bounds__(256) void k_bake_block_max(const float* __restrict_
     }
 }
 
+constexpr int kVisThreads = 256;  // of a visibility workgroup
+
 struct BakeVisArgs {
     const float* sigma;
     const DevCamera* cams;
@@ -105,10 +108,19 @@ struct BakeVisArgs {
 // to a multiple of 2^10).  A block entry whose prefix sum is at least that
 // bound needs no global access.  A racing overwrite only costs a later global
 // check.
+// (Accessed by relaxed atomics: a volatile pointer argument would leave the LDS's
+// address space unknown and every access a flat one.)
 template <int LOG>
-__device__ __forceinline__ void vis_cache_clear(volatile uint32_t* vcache) {
-    for (int i = threadIdx.x; i < (1 << LOG); i += blockDim.x)
+__device__ __forceinline__ void vis_cache_clear(uint32_t* vcache) {
+#pragma unroll
+    for (int i = threadIdx.x; i < (1 << LOG); i += kVisThreads)
         vcache[i] = (uint32_t(i >> 8) << 22) | (0x7f800000u >> 10);  // bound +inf: never skips
+}
+__device__ __forceinline__ uint32_t vis_cached(const uint32_t* slot) {
+    return __hip_atomic_load(slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+__device__ __forceinline__ void vis_cache(uint32_t* slot, uint32_t key) {
+    __hip_atomic_store(slot, key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
 __device__ __forceinline__ uint32_t vis_code(double sum) {
@@ -117,28 +129,32 @@ __device__ __forceinline__ uint32_t vis_code(double sum) {
     return (__float_as_uint(f) + 0x3ffu) >> 10;
 }
 
-// Folds a prefix sum into the minimum of the macroblock a ray enters with it.
+// Folds a prefix sum into the minimum of the macroblock a ray enters with it,
+// unless the cache of 2^LOG slots says that the minimum is no larger already.
 // The lanes that enter a block together first agree in the cache on the
 // smallest code; a lane with a larger one leaves the fold to that lane (its
-// own sum is larger, and so is the bound it would have written).  The global
-// minimum is then read through the caches: it only ever falls, so an old
-// value is a bound as good as any, and a read that waits for the other XCDs
-// costs the ray several times a cached one.
-template <int LOG>
-__device__ __forceinline__ void vis_enter(volatile uint32_t* vcache, uint64_t* depth_bits, uint32_t lin, double sum) {
-    const uint32_t slot = lin & ((1u << LOG) - 1u), tag = lin >> 8;
-    const uint32_t key = vcache[slot];
+// own sum is larger, and so is the bound it would have written).
+// SCOPE: of the read of the global minimum.  It only ever falls, so an old value
+// from a cache is a bound as good as any, and a read that waits for the other
+// XCDs costs the ray several times a cached one; but the lanes that it does not
+// stop go on to an atomic each, and with the 256 slots of the march by samples
+// those are many: 100 views of 800x800 into 160^3 that varies in every voxel
+// take 7.7 ms with cached reads and 6.65 without.
+template <int LOG, int SCOPE>
+__device__ __forceinline__ void vis_enter(uint32_t* vcache, uint64_t* depth_bits, uint32_t lin, double sum) {
+    uint32_t* slot = vcache + (lin & ((1u << LOG) - 1u));
+    const uint32_t tag = lin >> 8, key = vis_cached(slot);
     if ((key >> 22) == tag && double(__uint_as_float((key & 0x3fffffu) << 10)) <= sum) return;
     const uint32_t mine = (tag << 22) | vis_code(sum);
-    if ((key >> 22) == tag) atomicMin(const_cast<uint32_t*>(vcache) + slot, mine);
-    else vcache[slot] = mine;
-    const uint32_t now = vcache[slot];
+    if ((key >> 22) == tag) __hip_atomic_fetch_min(slot, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    else vis_cache(slot, mine);
+    const uint32_t now = vis_cached(slot);
     if ((now >> 22) == tag && now < mine) return;
     const uint64_t bits = uint64_t(__double_as_longlong(sum));
     uint64_t* w = depth_bits + lin;
-    const uint64_t g = __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+    const uint64_t g = __hip_atomic_load(w, __ATOMIC_RELAXED, SCOPE);
     if (bits < g) atomicMin(reinterpret_cast<unsigned long long*>(w), (unsigned long long)bits);
-    else vcache[slot] = (tag << 22) | vis_code(__longlong_as_double((long long)g));
+    else vis_cache(slot, (tag << 22) | vis_code(__longlong_as_double((long long)g)));
 }
 
 // The ray of lane `lane` in tile t and its samples inside the grid: position
@@ -175,6 +191,7 @@ enum { kIdx64 = 0, kIdx32 = 1, kIdxPow2 = 2 };
 
 template <int IDX>
 __global__ __launch_bounds__(256) void k_bake_visibility(BakeVisArgs a) {
+    if (a.cells && a.stats[2] == 0) return;  // k_bake_visibility_cells takes the field
     __shared__ uint32_t vcache[256];
     vis_cache_clear<8>(vcache);
     __syncthreads();
@@ -243,7 +260,7 @@ __global__ __launch_bounds__(256) void k_bake_visibility(BakeVisArgs a) {
                             bz = bk[u] >> 16;
                         }
                         const uint32_t lin = __umul24(__umul24(bz, G) + by, G) + bx;
-                        vis_enter<8>(vcache, a.depth_bits, lin, sum);
+                        vis_enter<8, __HIP_MEMORY_SCOPE_AGENT>(vcache, a.depth_bits, lin, sum);
                     }
                 }
                 sum += double(sv[u]);
@@ -376,28 +393,45 @@ __device__ __forceinline__ int32_t steps_in_cube(const int32_t P[3], const int32
 
 // The march of k_bake_visibility over the cell table: a step of a ray is a
 // whole cell (or macroblock) of one value, whose samples add n times that
-// value to the prefix sum, or the samples of a mixed cell, read four at a
-// time.  The sums keep every bit of the sample-by-sample ones: a run of
-// zeros changes nothing, and n c may stand for n additions of c where no
-// addition rounds.  That holds for all of the field when, with 2^e the last
-// place of its smallest non-zero value (all values are multiples of it), no
-// sum of interest reaches 2^(53+e); sums stop mattering past the threshold,
-// so four times that plus twice the largest value bounds them.  Where the
-// field does not satisfy this, only cells of zeros are skipped.
-// Bound by instruction issue for many rays (3,070 VALU instructions per
-// wavefront of 64 rays, VALUs about 70% busy): 100 views of 800x800 into a
-// 512^3 field take 6.9 ms, 30.1 sample by sample.  24 views of 200x150 into
-// 160^3 (204 us, 345 before) are bound by the chain of dependent loads, so
-// the next cell's entry is read before the current cell's samples and those
-// eight at a time.  Every first look at a macroblock by a workgroup costs a
-// global access (they took 40% of the time with 256 slots and one tile per
+// value to the prefix sum, or the next eight samples of its macroblock.  The
+// sums keep every bit of the sample-by-sample ones: a run of zeros changes
+// nothing, and n c may stand for n additions of c where no addition rounds.
+// That holds for all of the field when, with 2^e the last place of its smallest
+// non-zero value (all values are multiples of it), no sum of interest reaches
+// 2^(53+e); sums stop mattering past the threshold, so four times that plus twice
+// the largest value bounds them.  Where the field does not satisfy this, only
+// cells of zeros are skipped.
+// Bound by instruction issue for many rays, by the chain of dependent loads for
+// few (the next cell's entry is read before the current step's samples): 100 views
+// of 800x800 into a 512^3 field take 5.6 ms, 30.2 sample by sample, 24 views of
+// 200x150 into 160^3 0.2 and 0.33.  Lanes that sit through a mixed cell of up to 28
+// samples together, as an earlier form had it, made fields with mixed cells twice
+// as slow as the march by samples.  Every first look at a macroblock by a workgroup
+// costs a global access (they took 40% of the time with 256 slots and one tile per
 // wavefront): the cache has a slot for every macroblock up to 16^3, and large
 // launches run resident workgroups over many tiles.
 constexpr int kCellsCacheLog = 12;
-constexpr int kCellAhead = 8;  // a ray crosses an 8^3 cell in up to 28 samples, 14 on average
+constexpr int kCellAhead = 8;  // samples of a mixed cell's step; 12 and 16 are slower by up to 6 and 20%
+
+// Which of the two marches takes the field: stats[2] is set, and it is the one by
+// samples, where more than kMixedLine of 1024 cells, spread over the field, are
+// mixed.  Time by samples over time by cells, 100 views of 800x800 into 512^3 in
+// blocks of 32, cells mixed at random / in an outer layer: none 5.3, 30% 1.3 / 2.6,
+// 50% 0.95 / 1.6, all 0.74; into 160^3 in blocks of 16 1.95, 1.1 / 1.1, 0.9 / 0.87,
+// 0.7; 20 views of 300x300 into 512^3 in blocks of 8 2.4, 1.5 / 1.9, 1.05 / 1.5, 0.67.
+constexpr int kMixedLine = 460;
+
+__global__ __launch_bounds__(1024) void k_bake_choose(const uint2* __restrict__ cells, uint32_t M,
+                                                      uint32_t* __restrict__ stats) {
+    const uint32_t at = threadIdx.x << 22 | (threadIdx.x * 2654435761u) >> 10;  // a place in the thread's 1024th
+    const uint64_t n = uint64_t(M * M) * M;
+    const int mixed = __syncthreads_count(cells[(at * n) >> 32].x == kMixed);
+    if (threadIdx.x == 0) stats[2] = mixed > kMixedLine ? 1 : 0;
+}
 
 template <int IDX>
 __global__ __launch_bounds__(256) void k_bake_visibility_cells(BakeVisArgs a) {
+    if (a.stats[2] != 0) return;  // k_bake_visibility takes the field
     __shared__ uint32_t vcache[1 << kCellsCacheLog];
     vis_cache_clear<kCellsCacheLog>(vcache);
     __syncthreads();
@@ -437,39 +471,38 @@ __global__ __launch_bounds__(256) void k_bake_visibility_cells(BakeVisArgs a) {
                                  (uint32_t(P[0]) >> bs);
             if (lin != prev) {  // the ray's smallest prefix sum in this macroblock
                 prev = lin;
-                vis_enter<kCellsCacheLog>(vcache, a.depth_bits, lin, sum);
+                vis_enter<kCellsCacheLog, __HIP_MEMORY_SCOPE_WAVEFRONT>(vcache, a.depth_bits, lin, sum);
             }
-            const int32_t n = min(steps_in_cube(P, up, inv, e.y), left);
+            const float c = __uint_as_float(e.x);
+            const bool run = c == 0.0f || (exact && e.x != kMixed);
+            int32_t n = min(steps_in_cube(P, up, inv, run ? e.y : uint32_t(bs)), left);
+            if (!run) n = min(n, kCellAhead);
             uint32_t Q[3] = {uint32_t(P[0]), uint32_t(P[1]), uint32_t(P[2])};
             left -= n;
 #pragma unroll
             for (int q = 0; q < 3; ++q) P[q] += __mul24(n, s[q]);  // |n s| <= B 2^16 + 2^15
-            if (left > 0) next = entry();  // in flight during the cell's own samples
-            const float c = __uint_as_float(e.x);
-            if (c == 0.0f || (exact && e.x != kMixed)) {
+            if (left > 0) next = entry();  // in flight during the samples
+            if (run) {
                 sum = fma(double(n), double(c), sum);
             } else {
-                for (int32_t j = 0; j < n; j += kCellAhead) {
-                    // samples past the last are clamped onto it, so every load is in bounds
-                    const int32_t last = n - 1 - j;
-                    float sv[kCellAhead];
+                // samples past the last are clamped onto it, so every load is in bounds
+                float sv[kCellAhead];
 #pragma unroll
-                    for (int u = 0; u < kCellAhead; ++u) {
-                        if (u > 0 || j > 0) {
-                            const uint32_t m = u <= last ? 0xffffffffu : 0u;
+                for (int u = 0; u < kCellAhead; ++u) {
+                    if (u > 0) {
+                        const uint32_t m = u < n ? 0xffffffffu : 0u;
 #pragma unroll
-                            for (int q = 0; q < 3; ++q) Q[q] += uint32_t(s[q]) & m;
-                        }
-                        if (IDX == kIdxPow2)
-                            sv[u] = a.sigma[(Q[0] >> 16) | ((Q[1] >> 16) << lg) | ((Q[2] >> 16) << (2 * lg))];
-                        else if (IDX == kIdx32)
-                            sv[u] = a.sigma[__umul24(__umul24(Q[2] >> 16, N) + (Q[1] >> 16), N) + (Q[0] >> 16)];
-                        else
-                            sv[u] = a.sigma[(uint64_t(Q[2] >> 16) * N + (Q[1] >> 16)) * N + (Q[0] >> 16)];
+                        for (int q = 0; q < 3; ++q) Q[q] += uint32_t(s[q]) & m;
                     }
-#pragma unroll
-                    for (int u = 0; u < kCellAhead; ++u) sum += u <= last ? double(sv[u]) : 0.0;
+                    if (IDX == kIdxPow2)
+                        sv[u] = a.sigma[(Q[0] >> 16) | ((Q[1] >> 16) << lg) | ((Q[2] >> 16) << (2 * lg))];
+                    else if (IDX == kIdx32)
+                        sv[u] = a.sigma[__umul24(__umul24(Q[2] >> 16, N) + (Q[1] >> 16), N) + (Q[0] >> 16)];
+                    else
+                        sv[u] = a.sigma[(uint64_t(Q[2] >> 16) * N + (Q[1] >> 16)) * N + (Q[0] >> 16)];
                 }
+#pragma unroll
+                for (int u = 0; u < kCellAhead; ++u) sum += u < n ? double(sv[u]) : 0.0;
             }
         }
     }
@@ -660,16 +693,18 @@ hipError_t launch_bake_cull(const BakeCullPlan& p, hipStream_t s) {
                             ? kIdxPow2
                             : (int64_t(p.N) * p.N * p.N <= int64_t(0xffffffffu) ? kIdx32 : kIdx64);
         if (p.cells) {
+            hipLaunchKernelGGL(k_bake_choose, dim3(1), dim3(1024), 0, s, p.cells, uint32_t(p.N) >> kCellLog, p.stats);
+            if ((e = hipGetLastError()) != hipSuccess) return e;
             // resident workgroups only, so that their caches of bounds serve many tiles
             const dim3 wgs(blocks.x > 4u * 2048u ? 2048u : blocks.x);
             if (idx == kIdxPow2) hipLaunchKernelGGL(k_bake_visibility_cells<kIdxPow2>, wgs, dim3(256), 0, s, v);
             else if (idx == kIdx32) hipLaunchKernelGGL(k_bake_visibility_cells<kIdx32>, wgs, dim3(256), 0, s, v);
             else hipLaunchKernelGGL(k_bake_visibility_cells<kIdx64>, wgs, dim3(256), 0, s, v);
-        } else {
-            if (idx == kIdxPow2) hipLaunchKernelGGL(k_bake_visibility<kIdxPow2>, blocks, dim3(256), 0, s, v);
-            else if (idx == kIdx32) hipLaunchKernelGGL(k_bake_visibility<kIdx32>, blocks, dim3(256), 0, s, v);
-            else hipLaunchKernelGGL(k_bake_visibility<kIdx64>, blocks, dim3(256), 0, s, v);
+            if ((e = hipGetLastError()) != hipSuccess) return e;
         }
+        if (idx == kIdxPow2) hipLaunchKernelGGL(k_bake_visibility<kIdxPow2>, blocks, dim3(256), 0, s, v);
+        else if (idx == kIdx32) hipLaunchKernelGGL(k_bake_visibility<kIdx32>, blocks, dim3(256), 0, s, v);
+        else hipLaunchKernelGGL(k_bake_visibility<kIdx64>, blocks, dim3(256), 0, s, v);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     BakeCompactArgs c;

@@ -88,7 +88,7 @@ struct BakeCullPlan {
     float* bmax;            // scratch [G^3]
     uint64_t* depth_bits;   // scratch [G^3]
     uint2* cells;           // scratch [(N/8)^3] (null: sample by sample)
-    uint32_t* stats;        // scratch [2], with cells
+    uint32_t* stats;        // scratch [3], with cells
     float* block_alpha;     // nullable
     float* block_vis;       // nullable
     int32_t* indirection;

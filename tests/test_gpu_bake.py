@@ -207,3 +207,27 @@ def test_bake_cells_of_one_value(N, B, kind):
         res = BK.BakeResult(n, ind, alpha, vis, None, None, None)
         near = _check_cull(res, ref, N, tau_vis=tau_vis)
         say(f"  tau_vis={tau_vis}: kept {n}/{G3}, near-threshold {near}")
+
+
+@pytest.mark.parametrize("N,B", [(64, 8), (96, 32), (56, 8), (128, 64), (64, 4)])
+@pytest.mark.parametrize("mixed", [0.3, 0.4, 0.5, 1.0])
+def test_bake_fields_with_mixed_cells(N, B, mixed):
+    """Cells of 8^3 that vary in every voxel, from few to all: both sides of the line
+    between the march over cells and the march by samples."""
+    say(f"bake mixed cells N={N} B={B} {mixed}")
+    rng = np.random.default_rng(N + B)
+    M = N // 8
+    cell = np.zeros(M ** 3, bool)
+    cell[rng.permutation(M ** 3)[: round(mixed * M ** 3)]] = True
+    noise = rng.uniform(0, 3, (N, N, N)).astype(np.float32)
+    sigma = np.where(np.kron(cell.reshape(M, M, M), np.ones((8, 8, 8), bool)), noise, np.float32(0.2))
+    cams = W.sphere_cameras([(40, 34, 50.0)] * 3, seed=N) + [W.look_at((0.1, 0.05, -0.2), 20, 20, 70.0)]
+    G3 = (N // B) ** 3
+    ind = torch.empty(G3, dtype=torch.int32, device="cuda")
+    alpha, vis = torch.empty(G3, device="cuda"), torch.empty(G3, device="cuda")
+    for tau_vis in (0.01, 0.9):
+        ref = K.cull(sigma, B, cams, tau_vis=tau_vis)
+        n = S.snerg_bake_cull(handle(), N, B, _dev(sigma), S.make_cameras(cams), S.make_bake_opts(tau_vis=tau_vis), ind,
+                              alpha, vis)
+        near = _check_cull(BK.BakeResult(n, ind, alpha, vis, None, None, None), ref, N, tau_vis=tau_vis)
+        say(f"  tau_vis={tau_vis}: kept {n}/{G3}, near-threshold {near}")

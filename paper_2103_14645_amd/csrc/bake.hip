@@ -361,9 +361,15 @@ __global__ __launch_bounds__(256) void k_bake_cells(const float* __restrict__ si
     if (threadIdx.x == 0) {
         bmax[lin] = m;
         depth_bits[lin] = kInfBits;
-        // reads first: after the first blocks hardly any still has to write
-        if (__hip_atomic_load(stats, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < all_hi) atomicMax(stats, all_hi);
-        if (__hip_atomic_load(stats + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < ~nz) atomicMax(stats + 1, ~nz);
+        // reads first, from the caches, then behind them: after the first blocks
+        // hardly any still has to write
+        auto raise = [](uint32_t* p, uint32_t v) {
+            if (__hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT) < v &&
+                __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < v)
+                atomicMax(p, v);
+        };
+        raise(stats, all_hi);
+        raise(stats + 1, ~nz);
     }
     const bool whole = all_lo == all_hi;
     const int32_t M = N >> kCellLog;

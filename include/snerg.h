@@ -91,7 +91,7 @@ extern "C" {
 
 /* ------------------------------------------------------------- option flags */
 #define SNERG_FLAG_MLP_FP16 (1u << 0)   /* deferred MLP on FP16 MFMA tiles, FP32 accumulation */
-#define SNERG_FLAG_PERSISTENT (1u << 1) /* one persistent launch over a global tile queue (renders small enough for several lanes to a ray, see snerg_tuning, have no queue) */
+#define SNERG_FLAG_PERSISTENT (1u << 1) /* one persistent launch over a global tile queue (renders with several lanes to a ray, see snerg_tuning, have no queue) */
 #define SNERG_FLAG_GRAPH (1u << 2)      /* replay the launch from a captured HIP graph */
 #define SNERG_FLAG_MLP_GRAD_ONLY (1u << 3) /* backward: MLP gradient only (any grid dtype) */
 /* Render variants of the paper's own viewer (they change the image):
@@ -165,9 +165,10 @@ typedef struct {
 } snerg_opts;
 
 /* Launch shape used by the forward kernels (chosen by snerg_autotune).  It
- * sets how pixels are dealt to wavefronts, never a result.  Renders of up to
- * 2^16 rays (up to 5 * 2^16 on large grids), and most of a SNERG_F32 grid, give
- * each ray several lanes of a wavefront; of the shape they use only the tile. */
+ * sets how pixels are dealt to wavefronts, never a result.  Renders of few rays
+ * (by N, B and the network: up to 2^13 to 5 * 2^16) give each ray several lanes
+ * of a wavefront, and so do most of SNERG_F32 grids in macroblocks of 16 and more,
+ * of any size; of the shape they use only the tile. */
 typedef struct {
     int32_t tile_w, tile_h;   /* pixels per wavefront tile, tile_w * tile_h == 64 */
     int32_t waves_per_group;  /* wavefronts per workgroup: 1, 2 or 4 */
@@ -407,7 +408,9 @@ int snerg_get_tuning(snerg_handle *h, snerg_tuning *t);
  * The launch mode itself (tiles or persistent) is the one opts selects.
  * out_rgba receives the last render.  best (host, nullable) receives the
  * winner and best_ms its time per render.  The winner becomes the handle's
- * tuning and is recorded for this workload (snerg_tuning_lookup).
+ * tuning and is recorded for this workload (snerg_tuning_lookup).  Where a ray
+ * has several lanes (snerg_tuning) only tiles are compared, the first candidate
+ * of each, and the handle keeps its waves_per_group and groups_per_cu.
  * Synchronises `stream`.
  */
 int snerg_autotune(snerg_handle *h, const snerg_grid *grid, const float *mlp,

@@ -1080,24 +1080,48 @@ int snerg_autotune(snerg_handle* h, const snerg_grid* grid, const float* mlp, co
     if (rc) return rc;
     if (!out_rgba) return fail(SNERG_ERR_INVALID_ARG, "out_rgba is NULL");
     if (reps < 1) return fail(SNERG_ERR_INVALID_ARG, "reps must be >= 1");
+    if (candidates && n_candidates < 1) return fail(SNERG_ERR_INVALID_ARG, "n_candidates must be >= 1");
+    for (int i = 0; candidates && i < n_candidates; ++i)
+        if ((rc = check_tuning(&candidates[i]))) return rc;
+    if (!h) return fail(SNERG_ERR_INVALID_ARG, "handle is NULL");
+    // Where a ray has several lanes only the tile counts: one candidate to a tile,
+    // and the handle keeps the fields that were not measured.
+    auto tile_only = [&](const snerg_tuning& t) {
+        RenderArgs a;
+        std::memset(&a, 0, sizeof a);
+        a.grid.N = grid->N;
+        a.grid.B = grid->B;
+        a.opts = render_opts(opts);
+        for (int32_t c = 0; c < n_cams; ++c)
+            a.total_tiles += int64_t((cams[c].W + t.tile_w - 1) / t.tile_w) * ((cams[c].H + t.tile_h - 1) / t.tile_h);
+        const int mlp_mode = !opts->mlp_on ? kMlpOff : ((opts->flags & SNERG_FLAG_MLP_FP16) ? kMlpF16 : kMlpF32);
+        return split_for(a, grid->dtype == SNERG_F32 ? 1 : 0, mlp_mode).lanes > 1;
+    };
     std::vector<snerg_tuning> cand;
+    auto add = [&](const snerg_tuning& t) {
+        const bool again = std::any_of(cand.begin(), cand.end(), [&](const snerg_tuning& c) {
+            return c.tile_w == t.tile_w && c.tile_h == t.tile_h;
+        });
+        if (!again || !tile_only(t)) cand.push_back(t);
+    };
     if (candidates) {
-        if (n_candidates < 1) return fail(SNERG_ERR_INVALID_ARG, "n_candidates must be >= 1");
-        for (int i = 0; i < n_candidates; ++i) {
-            if ((rc = check_tuning(&candidates[i]))) return rc;
-            cand.push_back(candidates[i]);
-        }
+        for (int i = 0; i < n_candidates; ++i) add(candidates[i]);
     } else {
         const int shapes[4][2] = {{8, 8}, {16, 4}, {4, 16}, {32, 2}};
         const int wpgs[3] = {1, 2, 4};
         const int gpcs[5] = {2, 3, 4, 6, 8};
         const bool persistent = (opts->flags & SNERG_FLAG_PERSISTENT) != 0;
-        for (auto& sh : shapes)
+        for (auto& sh : shapes) {
+            const snerg_tuning own = {sh[0], sh[1], h->tuning.waves_per_group, h->tuning.groups_per_cu};
+            if (tile_only(own)) {
+                cand.push_back(own);
+                continue;
+            }
             for (int w : wpgs)
                 for (int gi = 0; gi < (persistent ? 5 : 1); ++gi)
                     cand.push_back(snerg_tuning{sh[0], sh[1], w, persistent ? gpcs[gi] : 8});
+        }
     }
-    if (!h) return fail(SNERG_ERR_INVALID_ARG, "handle is NULL");
     hipStream_t s = static_cast<hipStream_t>(stream);
     hipEvent_t e0, e1;
     HIP_TRY(hipEventCreate(&e0));
@@ -1124,7 +1148,12 @@ int snerg_autotune(snerg_handle* h, const snerg_grid* grid, const float* mlp, co
     hipEventDestroy(e0);
     hipEventDestroy(e1);
     if (rc) return rc;
-    h->tuning = best_c;
+    if (tile_only(best_c)) {
+        h->tuning.tile_w = best_c.tile_w;
+        h->tuning.tile_h = best_c.tile_h;
+    } else {
+        h->tuning = best_c;
+    }
     h->tuned[tuning_signature(grid, cams, n_cams, opts)] = best_c;
     if (best) *best = best_c;
     if (best_ms) *best_ms = best_t;

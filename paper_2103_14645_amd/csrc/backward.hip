@@ -1207,7 +1207,9 @@ constexpr int kAdjTrips = 4;
 // with too many samples to list.
 template <bool FEAT, bool AGG>
 __global__ __launch_bounds__(64 * kAdjWaves) __attribute__((amdgpu_waves_per_eu(AGG ? 5 : 4))) void k_adjoint(BackwardArgs a) {
-    extern __shared__ uint2 s_occ[];
+    extern __shared__ int4 s_dyn[];  // the logs' entries set its alignment
+    uint2* s_occ = reinterpret_cast<uint2*>(s_dyn);
+    static_assert(alignof(decltype(s_dyn[0])) >= 16 && sizeof(uint2) == 8, "logs begin at an even uint2");
     __shared__ float s_max;
     __shared__ int32_t s_fresh[3], s_live[3];
     __shared__ float s_gch[AGG ? 1 : kAdjWaves][8][8];

@@ -131,6 +131,7 @@ def test_more_records_than_one_launch_holds():
     N, B = 1536, 32
     G = N // B
     n = G ** 3
+    torch.cuda.empty_cache()
     if torch.cuda.mem_get_info()[0] < 64 << 30:
         pytest.skip("needs 64 GB of device memory")
     H.say(f"pack of {n} records")
@@ -152,3 +153,5 @@ def test_more_records_than_one_launch_holds():
         for lo, hi, per in ((0, 1, 1), (1, 4, 3), (4, 8, 4)):
             want = feat[per * i * B3:per * (i + 1) * B3].view(B, B, B, per)
             assert torch.equal(vox[..., lo:hi], want), (r, lo)
+    del feat, packed, vox, want
+    torch.cuda.empty_cache()

@@ -313,8 +313,8 @@ snerg_tuning tuning_for(const snerg_handle* h, const snerg_grid* g, const snerg_
 // The counting and per-sample kernels have one lane to a ray.
 RenderSplit split_for(const RenderArgs& a, int vt, int mlp_mode) {
     if (a.counters || a.opts.per_sample_mlp) return {1, 1};
-    return render_split(a.grid.N, a.grid.B, a.ray_ids != nullptr, a.ray_ids ? a.n_rays : 64 * a.total_tiles, vt == 1,
-                        mlp_mode == kMlpF16);
+    return render_split(a.grid.N, a.grid.B, a.ray_ids != nullptr, a.ray_ids ? a.n_rays : 64 * a.total_tiles,
+                        64 * a.total_tiles, vt == 1, mlp_mode == kMlpF16);
 }
 
 int render_impl(snerg_handle* h, const snerg_grid* grid, const float* mlp, const snerg_camera* cams,

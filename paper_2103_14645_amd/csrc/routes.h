@@ -20,10 +20,9 @@ struct RenderSplit {
 // N / B), a workgroup of 256 lanes stages the whole occupancy table (8 KB at 32^3
 // macroblocks, 64 KB at 64^3, where two workgroups fill a compute unit) for 16 or
 // 64 rays, and the FP16 network's tiles run once per wavefront, however many rays
-// it holds.  One lane's list goes 16 or 32 rays to a wavefront up to 2^15 and 2^16
-// rays, so lists gain less than views.  The lines lie where the slowest of what
-// was measured (views, scattered lists; shells and random blocks; both networks)
-// still gains.  One lane's time over that of 16 / of 4, uint8, slowest to fastest:
+// it holds.  One lane's time over that of 16 / of 4, uint8, slowest to fastest of
+// shells and random blocks, both networks (a list: scattered over 40 to 160 times as
+// many pixels; one lane goes 16 or 32 rays to a wavefront there):
 //   rays            16,384             32,768             65,536             131,072
 //   N, B       view 16   view 4   view 16   list 4    view 4    list 4    view 4
 //   64, 2      1.06-1.4  0.7-1.0  0.65-0.85 0.7-0.9   0.7-1.1   0.65-0.7
@@ -39,10 +38,12 @@ struct RenderSplit {
 //   256, 32    3.1-4.2   2.6-2.8  2.1-2.6   1.8-2.1   1.7-2.4   1.6-1.7   1.3-1.6
 //   512, 32    4.0-5.5   2.2-2.6  2.9-3.7   1.75-1.9  2.1-2.4   1.5-1.7   1.4-2.0
 //   1024, 32   4.7-5.6   2.0-2.3  3.1-4.1   1.7-1.9   2.0-2.4   1.45-1.6  1.4-2.3
-// and at 313,600 (560x560) 0.9-1.1 for 512, 32 and 1.1-1.5 for 1024, 32.  Past 2^16
-// rays the wavefronts are not all resident at once, and the tile order pays for
-// its two launches, but not up to 192^3 (128^3, 120,000 rays 131 us in order, 124
-// without).
+// Lists of 131,072 scattered rays 0.78-0.9 in blocks of 16, 0.94-1.4 in blocks of 32;
+// where they take more than a sixteenth of the pixels, or come in patches, rays share
+// samples as a view's do (512, 16, 152,551 of 664,000 pixels: 523 us, 364).  Views of
+// 313,600 0.9-1.1 for 512, 32 and 1.1-1.5 for 1024, 32.  Past 2^16 rays the wavefronts
+// are not all resident at once, and the tile order pays for its two launches, but not
+// up to 192^3 (128^3, 120,000 rays 131 us in order, 124 without).
 // float32 samples are 256 bytes each and bound by the texture path; the samples of
 // one ray side by side share most of their lines, so there the split also pays
 // where the chip is full, unless macroblocks are small.  One lane over 2 lanes,
@@ -51,49 +52,76 @@ struct RenderSplit {
 // 560x560: 128, 16 1.22 / 1.13; 512, 16 1.35 / 1.23; 128, 8 1.06 / 0.98.  Over 4:
 // 560x560 192, 32 1.38 / 1.22; 512, 32 2.0 / 1.7; 512, 16 1.45 / 1.25; 512, 8 0.55 /
 // 0.4; 2^20 scattered rays 128, 32 1.3 / 1.1; 64, 32 1.05 / 0.96; 512, 16 1.2 / 0.96.
-//
-// rays: of a list its entries, of views 64 for each tile, since a wavefront is
-// launched and its tables are staged however few of them lie in the image.
-inline RenderSplit render_split(int32_t N, int32_t B, bool list, int64_t rays, bool f32, bool f16) {
+
+// For blocks under 8 and tables of more than 8 KB (G = N / B over 32).  Each network
+// counts here, so work is in rays with the FP32 one.
+inline RenderSplit render_split_small_blocks(int32_t N, int32_t B, bool list, int64_t rays, bool f32, bool f16) {
     constexpr int64_t K = 1 << 10, M = 1 << 20;
     const int32_t G = N / B;
     const int table = G <= 40 ? 0 : (G <= 56 ? 1 : 2);  // the occupancy table: up to 16, 43, 64 KB
     const int64_t work = f16 ? rays + rays / 4 : rays;
     auto at_most = [](int64_t& line, int64_t v) { line = line < v ? line : v; };
 
-    int64_t most16 = B < 8 ? 16 * K : (B < 16 || N < 256 ? 32 * K : (B < 32 || N < 512 ? 48 * K : 64 * K));
+    int64_t most16 = B < 8 ? 16 * K : (B < 16 ? 32 * K : 48 * K);
     if (table > 0) at_most(most16, B < 4 || (B < 8 && table > 1) ? 8 * K : (B < 8 ? 16 * K : 24 * K));
     if ((list ? 2 * work : work) <= most16) return {16, 0};
 
     int64_t most4 = 0, most2 = 0;
     if (!f32) {
         if (B == 4) most4 = N <= 64 ? 64 * K : 0;
-        else if (B == 8) most4 = N < 128 ? 96 * K : 80 * K;
-        else if (B == 16) most4 = N < 128 ? 96 * K : 128 * K;
-        else if (B >= 32) most4 = N < 128 ? 96 * K : (N < 512 ? 192 * K : 320 * K);
-        if (G > 32) at_most(most4, table == 0 ? 64 * K : (table > 1 ? 24 * K : (B > 8 ? 48 * K : 32 * K)));
+        else if (B >= 8) most4 = table == 0 ? 64 * K : (table > 1 ? 24 * K : (B > 8 ? 48 * K : 32 * K));
         if (list) most4 /= 2;
     } else if (list) {
-        if (B == 4 || B == 8) most4 = 64 * K;
-        else if (B >= 16) most4 = B == 16 || N < 128 ? 512 * K : 1280 * K;
+        if (B >= 4) most4 = B < 16 ? 64 * K : (B == 16 ? 512 * K : 1280 * K);
         if (table == 1) at_most(most4, B < 8 ? 32 * K : (B < 16 ? 64 * K : (f16 ? 80 * K : 512 * K)));
         if (table == 2) at_most(most4, B < 8 ? 16 * K : (B < 16 ? 32 * K : 40 * K));
-        if (B == 16) most2 = table == 0 ? M : 0;
-        else if (B >= 32) most2 = f16 ? 5 * M : 1 << 30;
+        if (B >= 16) most2 = B > 16 ? (f16 ? 5 * M : 1 << 30) : (table == 0 ? M : 0);
     } else {
-        if (B == 4) most4 = 64 * K;
-        else if (B == 8) most4 = N < 128 || G > 32 ? 96 * K : 160 * K;
-        else if (B >= 16 && N < (B == 16 ? 256 : 128)) most4 = 160 * K;
-        else if (B >= 16) most4 = B == 16 || N < 512 ? 384 * K : (N < 1024 && B == 32 ? 512 * K : 1024 * K);
+        if (B >= 4) most4 = B < 8 ? 64 * K : (B < 16 ? 96 * K : (B == 16 ? 384 * K : M));
         if (table == 1 && B < 16) at_most(most4, 64 * K);
         if (table == 2) at_most(most4, B < 8 ? 24 * K : (B < 16 ? 40 * K : (f16 ? 48 * K : 160 * K)));
-        if (B == 8 && G <= 16) most2 = N < 128 ? 160 * K : 384 * K;
-        else if (B == 16) most2 = table == 0 ? (N < 128 ? 512 * K : 768 * K) : (table == 1 || !f16 ? 384 * K : 0);
-        else if (B >= 32) most2 = N < 128 ? 512 * K : (!f16 ? 1 << 30 : (N < 512 ? 2 * M : 7 * M));
+        if (B == 16) most2 = table == 0 ? 768 * K : (table == 1 || !f16 ? 384 * K : 0);
+        else if (B > 16) most2 = f16 ? 7 * M : 1 << 30;
     }
     if (work <= most4) return {4, work > 64 * K && N > 192};
-    // (a launch holds fewer than 2^32 lanes)
     if (work <= most2) return {2, 1};
+    return {1, 1};
+}
+
+// rays: of a list its entries, of views 64 for each tile, since a wavefront is
+// launched and its tables are staged however few of them lie in the image.
+// pixels: of all cameras.
+inline RenderSplit render_split(int32_t N, int32_t B, bool list, int64_t rays, int64_t pixels, bool f32, bool f16) {
+    constexpr int64_t K = 1 << 10, M = 1 << 20;
+    if (B < 8 || N / B > 32) return render_split_small_blocks(N, B, list, rays, f32, f16);
+
+    const int64_t most16 = list ? (B == 8 ? 24 * K : 32 * K) : (N < 512 || B == 8 ? 34 * K : (B == 16 ? 48 * K : 64 * K));
+    if (rays <= most16) return {16, 0};
+
+    const bool sparse = list && rays * 16 < pixels;
+    int64_t most4, most2 = 0;
+    if (!f32) {
+        if (N < 128) most4 = sparse && B == 8 ? 64 * K : 96 * K;
+        else if (B == 8) most4 = sparse ? 40 * K : 80 * K;
+        else if (N < 192) most4 = sparse ? (B == 16 ? 80 * K : 110 * K) : 128 * K;
+        else if (B == 16) most4 = sparse ? 80 * K : (f16 ? 200 * K : 208 * K);
+        else most4 = N < 512 ? 208 * K : 336 * K;
+    } else if (list) {
+        if (B == 8) most4 = f16 ? 52 * K : 64 * K;
+        else most4 = B == 16 || N < 128 ? (f16 ? 400 * K : 512 * K) : M;
+        if (B == 16) most2 = f16 ? 0 : M;
+        else if (B > 16) most2 = f16 ? 6 * M : 1 << 30;
+    } else {
+        if (B == 8) most4 = N < 128 ? 96 * K : (f16 ? 130 * K : 160 * K);
+        else if (N < (B == 16 ? 256 : 128)) most4 = 160 * K;
+        else most4 = B == 16 || N < 512 ? 384 * K : (N < 1024 && B == 32 ? 512 * K : M);
+        if (B == 8) most2 = N / B > 16 ? 0 : (N < 128 ? 160 * K : (f16 ? 320 * K : 384 * K));
+        else if (N < 128 || (B == 16 && f16)) most2 = 512 * K;
+        else most2 = f16 ? (N < 512 ? 2 * M : 6 * M) : 1 << 30;
+    }
+    if (rays <= most4) return {4, rays > 64 * K && N > 192};
+    // (a launch holds fewer than 2^32 lanes)
+    if (rays <= most2) return {2, 1};
     return {1, 1};
 }
 

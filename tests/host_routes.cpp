@@ -11,8 +11,8 @@ int route_backward(int keys, int listed, int ids, int patch, int dense, int64_t 
     return int(backward_route(keys != 0, listed != 0, ids != 0, patch != 0, dense != 0, lds, rays));
 }
 
-int route_render(int N, int B, int list, int64_t rays, int f32, int f16) {
-    const RenderSplit s = render_split(N, B, list != 0, rays, f32 != 0, f16 != 0);
+int route_render(int N, int B, int list, int64_t rays, int64_t pixels, int f32, int f16) {
+    const RenderSplit s = render_split(N, B, list != 0, rays, pixels, f32 != 0, f16 != 0);
     return 2 * s.lanes + s.ordered;
 }
 

@@ -61,8 +61,9 @@ def test_backward_routes(lib, G, rays):
         assert got == want, (keys, listed, ids, patch, dense_)
 
 
-def split(lib, N, B, rays, list_=False, f32=False, f16=False):
-    return lib.route_render(N, B, int(list_), ctypes.c_int64(rays), int(f32), int(f16)) // 2
+def split(lib, N, B, rays, list_=False, f32=False, f16=False, pixels=5120000):
+    i64 = ctypes.c_int64
+    return lib.route_render(N, B, int(list_), i64(rays), i64(pixels), int(f32), int(f16)) // 2
 
 
 SHAPES = [(N, B) for B in (2, 4, 8, 16, 32, 64) for N in range(B, min(64 * B, 2048) + 1, B) if N // B in (1, 2, 8, 16, 32, 40, 48, 56, 64)]
@@ -90,6 +91,8 @@ def test_render_launches_hold_fewer_than_2_to_32_lanes(lib, f32, f16):
     (512, 8, 163840, dict(f32=True), 1), (512, 8, 5120000, dict(f32=True), 1),
     (64, 8, 640000, dict(f32=True, f16=True), 1), (64, 8, 5120000, dict(f32=True), 1),
     (256, 16, 2560000, dict(f32=True, f16=True), 1), (512, 32, 5120000, dict(f32=True), 2),
+    (512, 16, 152551, dict(list_=True), 1), (512, 16, 152551, dict(list_=True, pixels=664000), 4),
+    (256, 16, 110000, dict(f16=True), 4), (192, 32, 162000, dict(f16=True), 4), (48, 8, 89088, dict(f16=True), 4),
     (1024, 32, 65536, dict(f32=True, f16=True, list_=True), 4), (512, 32, 1 << 20, dict(f32=True, list_=True), 4),
 ])
 def test_render_lanes(lib, N, B, rays, kw, lanes):

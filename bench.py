@@ -63,10 +63,11 @@ MLP_FLOP = 2 * (34 * 16 + 16 * 16 + 16 * 3)
 SAMPLE_FLOP = 15 + 128 + 20
 RAY_FLOP = MLP_FLOP + 36 + 9 + 7
 KERNEL_SOURCES = ("render.hip", "render_ps.hip", "backward.hip", "march.h", "mlp.h", "snerg_dev.h",
-                  "snerg_launch.h", "api.cpp")  # the kernels and their launch order
+                  "snerg_launch.h", "routes.h", "api.cpp")  # the kernels and their launch order
 # the sources each counter figure describes: the forward render kernels, and the adjoint's
-SOURCE_GROUPS = {"render": ("render.hip", "render_ps.hip", "march.h", "mlp.h", "snerg_dev.h", "snerg_launch.h"),
-                 "backward": ("backward.hip", "march.h", "mlp.h", "snerg_dev.h", "snerg_launch.h")}
+SOURCE_GROUPS = {"render": ("render.hip", "render_ps.hip", "march.h", "mlp.h", "snerg_dev.h", "snerg_launch.h",
+                            "routes.h"),
+                 "backward": ("backward.hip", "march.h", "mlp.h", "snerg_dev.h", "snerg_launch.h", "routes.h")}
 LEG_GROUP = {"plain512": "render", "batched1024": "render", "large1024": "render", "adjoint512_fwd": "render",
              "nondeferred_fp32": "render", "nondeferred_fp16": "render", "large1024_mb_fwd": "render",
              "adjoint512_bwd": "backward", "adjoint512_mlp_bwd": "backward", "large1024_mb_mlp_bwd": "backward",

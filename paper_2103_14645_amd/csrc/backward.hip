@@ -1188,8 +1188,8 @@ struct WaveLog {
 // One lane per ray pays for every sample with eight guarded hand-over passes
 // and 256 bytes of loads per lane, at two wavefronts per SIMD (197 registers);
 // this one runs five (96).
-//   eight 800x800 views, 512^3, FP32 network   23.7 -> 17.5 ms
-// Bound by instruction issue (VALUs 82% busy, half the lanes at work: about
+//   eight 800x800 views, 512^3, FP32 network   23.7 -> 17.0 ms
+// Bound by instruction issue (VALUs 83% busy, half the lanes at work: about
 // 270 instructions per sample of 8 rays).  Six wavefronts per SIMD cost 9%
 // (spills), four 5%.
 constexpr int kAdjWaves = 4;  // wavefronts per workgroup: half a tile, 8 lanes to a ray

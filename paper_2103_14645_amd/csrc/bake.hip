@@ -407,10 +407,10 @@ __device__ __forceinline__ int32_t steps_in_cube(const int32_t P[3], const int32
 // 2^(53+e); sums stop mattering past the threshold, so four times that plus twice
 // the largest value bounds them.  Where the field does not satisfy this, only
 // cells of zeros are skipped.
-// Bound by instruction issue for many rays, by the chain of dependent loads for
-// few (the next cell's entry is read before the current step's samples): 100 views
-// of 800x800 into a 512^3 field take 5.6 ms, 30.2 sample by sample, 24 views of
-// 200x150 into 160^3 0.2 and 0.33.  Lanes that sit through a mixed cell of up to 28
+// Bound by instruction issue for many rays (VALUs 79% busy, five wavefronts per
+// SIMD), by the chain of dependent loads for few (the next cell's entry is read
+// before the current step's samples): 100 views of 800x800 into a 512^3 field take
+// 5.6 ms, 30.2 sample by sample, 24 views of 200x150 into 160^3 0.2 and 0.33.  Lanes that sit through a mixed cell of up to 28
 // samples together, as an earlier form had it, made fields with mixed cells twice
 // as slow as the march by samples.  Every first look at a macroblock by a workgroup
 // costs a global access (they took 40% of the time with 256 slots and one tile per

@@ -148,9 +148,9 @@ enum class BackwardRoute : int32_t {
 // eight-lane kernel takes (occupancy table and summing table); rays: those of the
 // list, or 64 for each tile.
 //
-// Eight lanes halve the time (eight 800x800 views, 512^3: 17.5 against 27 ms; two
-// of 160x160: 2.2 against 4.5 for the whole call; 270,000 rays in patches 3.9
-// against 1.4), but they enter the table in another order.  Where a tile's voxels
+// Eight lanes take less time (whole calls, 512^3, one lane against eight: eight
+// 800x800 views 23.4 and 16.4 ms, two of 160x160 3.0 and 0.9, 270,000 rays in patches
+// 3.1 and 1.2, scattered 4.2 and 2.9), but they enter the table in another order.  Where a tile's voxels
 // don't fit the table, order decides what overflows and goes unrounded, and the
 // feature gradients would differ by the table's own rounding: 4e-5 of their norm
 // for 160x160 views of a 512^3 grid, 2.2e-5 for 270,000 scattered rays of it, but
@@ -158,12 +158,12 @@ enum class BackwardRoute : int32_t {
 // pixels are further apart than the voxels and long scattered lists take one lane.
 //
 // At 64^3 macroblocks the occupancy table alone is 64 KB, and a workgroup of 32
-// rays has the compute unit to itself, where one lane to a ray has 256 on it: four
-// 800x800 views of 128^3 in blocks of 2 take 32.4 ms with eight lanes and 16.9 with
-// one, of 512^3 in blocks of 8 50.6 and 34.6 (at 63^3, where two workgroups fit,
-// 16.7 and 16.7, 26.1 and 34.5).  As long as the launch is a few workgroups per
-// compute unit eight lanes still win: two 160x120 views 1.0 and 1.1 ms, 2.5 and 3.9;
-// one of 256x256 1.16 and 1.07, of 1024^3 in blocks of 16 7.3 and 5.8.
+// rays has the compute unit to itself, where one lane to a ray has 256 on it: eight
+// 800x800 views of 128^3 in blocks of 2 take 65 ms with eight lanes and 32 with one,
+// of 512^3 in blocks of 8 96 and 60 (at 63^3, where two workgroups fit, 33.6 and 32,
+// 49 and 59).  As long as the launch is a few workgroups per compute unit eight
+// lanes still win: two 160x120 views 0.94 and 0.97 ms, 2.1 and 3.25; one of 256x256
+// of the 128^3 grid 1.11 and 0.94.
 constexpr int64_t kCuLds = 160 << 10;
 
 inline BackwardRoute backward_route(bool keys, bool listed, bool ids, bool patch, bool dense, int64_t lds,

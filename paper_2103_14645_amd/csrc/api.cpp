@@ -791,6 +791,9 @@ int snerg_render_backward(snerg_handle* h, const snerg_grid* grid, const float* 
     a.mlp_only = mlp_only ? 1 : 0;
     a.patch_rays = (opts->flags & SNERG_FLAG_PATCH_RAYS) ? 1 : 0;
     a.grad_packed = packed ? 1 : 0;
+    const float n = float(a.grid.N);
+    a.stop_by_t = a.opts.early_stop && a.grid.sigma_scale / n != a.grid.sigma_scale * (1.0f / n) ? 1 : 0;
+    if (!a.opts.early_stop) a.opts.t_stop = -1.0f;
     a.dense_views = 1;
     for (int32_t c = 0; c < n_cams; ++c)
         if (!dense_view(cams[c].eye, cams[c].focal, grid->N)) a.dense_views = 0;

@@ -577,6 +577,20 @@ __device__ __forceinline__ void flush_corner(const BackwardArgs& a, const AggTab
     if (vi >= 0) agg_hand_over<FEAT>(a, t, vi, a.grid.sigma_scale * D, A, gC, gV, fresh);
 }
 
+// The T under which a ray's adjoint ends, so that it ends with the forward, whose
+// last T is `t_last`.  The factor here is sigma_scale * (1 / N), the forward's
+// sigma_scale / N.  Where they differ in the last place (sigma_scale 50: N = 48, 96,
+// 192, 384, 768), T does by some 2^-20, and the line lies between the forward's last
+// T and its T before, which was t_stop or more.  (With the forward's factor the
+// gradients would be no nearer to those in 64 bits, 5e-5 of the features' norm either
+// way, but patches of 768^3 would differ from these by up to 5e-3 of a value where
+// the tables round the other way.)
+__device__ __forceinline__ float stop_below(const BackwardArgs& a, float t_last) {
+    const float t = a.opts.t_stop;
+    if (!a.stop_by_t) return t;
+    return t_last < t ? fmaxf(0.5f * (t_last + t), t_last * (1.0f + 0x1p-16f)) : -1.0f;
+}
+
 // The adjoint state of one ray's re-march: its output gradient and the
 // forward's per-ray results (E, the T_N tail), the running transmittance T
 // and prefix P_k, and the corner window.  sample() takes the samples in
@@ -588,7 +602,7 @@ struct AdjointRay {
     float gC[3], gV[4];
     float E, tail, T, Pk;
     float delta, kx, t_stop;
-    bool early, nn_gate;
+    bool nn_gate;
     CellWindow win;
     int fresh;  // this lane's new table keys since the last count
     int32_t nb_lin, nb_id;  // the last neighbouring block looked up: linear index, atlas id
@@ -621,9 +635,8 @@ struct AdjointRay {
         T = 1.0f;
         Pk = 0.0f;
         delta = 1.0f / float(a.grid.N);
-        kx = a.grid.sigma_scale / float(a.grid.N);  // the forward's, which sigma_scale * delta need not be
-        t_stop = a.opts.t_stop;
-        early = a.opts.early_stop != 0;
+        kx = a.grid.sigma_scale * delta;
+        t_stop = stop_below(a, a1.w);
         nn_gate = a.opts.nn_gate != 0;
         win.rank = -1;
         win.id = 0;
@@ -712,7 +725,7 @@ struct AdjointRay {
             win.A[c] = fmaf(wc[c], w, win.A[c]);
             win.D[c] = fmaf(wc[c], gsig, win.D[c]);
         }
-        return early && T < t_stop;
+        return T < t_stop;
     }
 
     __device__ __forceinline__ void finish(const BackwardArgs& a, const AggTable& tab) {
@@ -965,6 +978,7 @@ template <bool FEAT>
 struct CornerRay {
     float gC[3], gV[4];
     float T, rest;  // rest: E - P_k + T_N dL/dT_N
+    float t_stop;
     float A, D;
     int32_t wc;              // the window's cell, own axis
     int32_t wrank, wid, wb;  // its block's record, atlas id, coordinates
@@ -997,6 +1011,7 @@ struct CornerRay {
         const float gTN = gg.x * a.opts.bg[0] + gg.y * a.opts.bg[1] + gg.z * a.opts.bg[2] - gg.w;
         rest = E + a1.w * gTN;
         T = 1.0f;
+        t_stop = stop_below(a, a1.w);
         A = D = 0.0f;
         wc = 0;
         wrank = -1;
@@ -1083,7 +1098,7 @@ struct CornerRay {
         wc += m.move;
         A = fmaf(m.wt, m.ws, A);
         D = fmaf(m.wt, m.gsig, D);
-        return a.opts.early_stop && T < a.opts.t_stop;
+        return T < t_stop;
     }
 
     // Takes an active sample.  hand_over(leave) is called once, by all lanes of
@@ -1111,8 +1126,8 @@ __device__ __forceinline__ void add_direct(const BackwardArgs& a, int l, int lan
 }
 
 // exp(-sigma delta) of a sample in a float32 block at `vox` and whether it is
-// active, with the forward's operations in their order (gather_f32), so that
-// T, the weights and the stop are the forward's to the bit.
+// active, with the forward's operations in their order (gather_f32) but for the
+// factor (stop_below).
 __device__ __forceinline__ bool sample_decay(const GridArgs& g, const uint8_t* vox, const int32_t p[3],
                                              const int32_t fr[3], bool nn_gate, float& e) {
     const uint32_t nb = uint32_t(g.Bp), nbb = nb * nb;
@@ -1132,7 +1147,7 @@ __device__ __forceinline__ bool sample_decay(const GridArgs& g, const uint8_t* v
         dnn = c == cnn ? den[c] : dnn;
         sigma = fmaf(w[c], den[c], sigma);
     }
-    e = __expf(-sigma * (g.sigma_scale / float(g.N)));
+    e = __expf(-sigma * (g.sigma_scale * (1.0f / float(g.N))));
     return nn_gate ? dnn != 0.0f : act;
 }
 

@@ -64,6 +64,7 @@ struct BackwardArgs {
     int32_t patch_rays;    // ray list in groups of 64 neighbouring rays
     int32_t grad_packed;   // grid gradients as grad_dens[voxel][8] (grad_rgb, grad_feat unused)
     int64_t first_group;   // set by the launch: workgroup index of the launch's first
+    int32_t stop_by_t;     // the adjoint's T may differ from the forward's (stop_below)
     int32_t dense_views;   // every camera's pixels lie closer than the voxels (dense_view)
     // ray lists of at most kBackwardListMaxRays rays (null: one re-march): per
     // list entry kBackwardListCap listed samples, and their count
